@@ -118,7 +118,12 @@ typedef struct xy_obs {
  *                   default: strip 512 x 64 for a lattice whose state and
  *                   ping-pong copy exceed 256 MiB, else the first fused tile of
  *                   256 x 16, 128 x 32, 64 x 32, 64 x 16 that L allows, else
- *                   XY_PLAN_STREAM. */
+ *                   XY_PLAN_STREAM.  xy_get_plan reports that plan; where the plan
+ *                   was not asked for by kind, small lattices run schedules of the
+ *                   library's own in its place (L < 56: every sweep of a call in
+ *                   one launch, the lattice on chip; up to L = 832: several sweeps
+ *                   per launch on overlapping regions), unless xy_kernel_timer is
+ *                   on. */
 enum { XY_PLAN_AUTO = 0, XY_PLAN_STREAM = 1, XY_PLAN_FUSED = 2, XY_PLAN_STRIP = 3, XY_PLAN_RESIDENT = 4 };
 typedef struct xy_plan {
     int32_t kind;

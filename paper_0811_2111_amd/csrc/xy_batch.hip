@@ -70,8 +70,10 @@ struct LatDesc {
 // Tile shape of the lattices that take wide tiles (XY_BATCH_PASSES_WIDE, XY_BATCH_PERSISTENT):
 // the fastest single-lattice shape.
 constexpr int kWideX = 256, kWideY = 16;
-// Lattices up to this size are LDS-resident under the per-sweep schedules.
-constexpr int kBatchResidentMaxL = 32;
+// Lattices up to this size are resident in one workgroup of kResNT threads under
+// the per-sweep schedules.
+constexpr int kBatchResidentMaxL = 32, kResNT = 512;
+static_assert(resident_fits<kResNT, 1>(kBatchResidentMaxL), "one pair a thread");
 // XCDs of the GPU (workgroups of a launch are spread over all of them).
 constexpr int kXcd = 8;
 
@@ -463,7 +465,7 @@ k_batch_reduce(const LatDesc* __restrict__ lat, const Ctrl* __restrict__ ctrl, i
 // lattice ridx[b] from `state`, writes the result to `out` (the buffer that holds
 // the other lattices after the last pass) and its records to obs[i * nrec ..].
 template <typename T>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kResNT)
 k_batch_resident(const T* __restrict__ state, T* __restrict__ out, const LatDesc* __restrict__ lat,
                  const int* __restrict__ ridx, const Ctrl* __restrict__ ctrl, int npass, int me,
                  xy_obs* __restrict__ obs, int nrec)
@@ -472,7 +474,7 @@ k_batch_resident(const T* __restrict__ state, T* __restrict__ out, const LatDesc
     const int i = ridx[blockIdx.x];
     const LatDesc d = lat[i];
     const Params prm{d.delta, d.nbl2e};
-    resident_program<T, 256>(state + d.off, out + d.off, d.L, ctrl->sweep0, npass, me, d.key0, d.key1, prm,
+    resident_program<T, kResNT, 1, false, kMeasOwn>(state + d.off, out + d.off, d.L, ctrl->sweep0, npass, me, d.key0, d.key1, prm,
                              (me > 0 && obs) ? obs + (size_t)i * nrec : nullptr, smem);
 }
 
@@ -934,13 +936,13 @@ static hipError_t enqueue_passes(xy_batch* b, hipStream_t s, int npass, int32_t 
         if ((e = hipStreamWaitEvent(b->cap2, b->ev_fork, 0)) != hipSuccess) return e;
         void* out = (npass & 1) ? pp : (void*)b->state;
         const int* ridx = (const int*)(b->work + b->lo.res_off);
-        const size_t lds = resident_lds_bytes(b->res_maxL, kNT);
+        const size_t lds = resident_lds_bytes(b->res_maxL, kResNT);
         if (b->precision == XY_FP16)
-            hipLaunchKernelGGL(k_batch_resident<__half>, dim3(b->nres), dim3(kNT), lds, b->cap2,
+            hipLaunchKernelGGL(k_batch_resident<__half>, dim3(b->nres), dim3(kResNT), lds, b->cap2,
                                (const __half*)b->state, (__half*)out, desc, ridx, (const Ctrl*)ctrl, npass, me, obs,
                                nrec);
         else
-            hipLaunchKernelGGL(k_batch_resident<float>, dim3(b->nres), dim3(kNT), lds, b->cap2,
+            hipLaunchKernelGGL(k_batch_resident<float>, dim3(b->nres), dim3(kResNT), lds, b->cap2,
                                (const float*)b->state, (float*)out, desc, ridx, (const Ctrl*)ctrl, npass, me, obs,
                                nrec);
         if ((e = hipGetLastError()) != hipSuccess) return e;

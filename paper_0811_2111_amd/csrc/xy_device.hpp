@@ -114,32 +114,51 @@ struct Params {
     float nbl2e;    // -beta * log2(e), FP32
 };
 
-// One Metropolis update.  th is the angle in turns, (c, s) its (cos, sin);
-// (sx, sy) = sums of the four neighbours' (cos, sin), formed by the caller as
-// (left + right) + (up + down).  w1 drives the proposal, w2 the acceptance.
-// The proposal th + delta (2 u1 - 1) is wrapped by v_fract_f32, which returns
-// t - floor(t) rounded once and, where that rounds up to 1 (t a tiny negative
-// number), the largest float below 1.  Returns 1 if the proposal is accepted;
-// the new angle and its (cos, sin) come back in th, c, s.
+// A site's proposal: the angle th + delta (2 u1 - 1) in turns and its (cos, sin),
+// and the number u the decision compares with.  It needs the site's own angle and
+// random words only, so it can be formed before the neighbours are known.  The
+// angle is wrapped by v_fract_f32, which returns t - floor(t) rounded once and,
+// where that rounds up to 1 (t a tiny negative number), the largest float below 1.
+struct Proposal {
+    float t, c, s, u;
+};
+
+template <typename T>
+__device__ __forceinline__ Proposal propose(float th, uint32_t w1, uint32_t w2, const Params& p)
+{
+    Proposal n;
+    const float step = __fmul_rn(p.delta, sym11(w1));
+    n.t = store<T>::rnd(__builtin_amdgcn_fractf(__fadd_rn(th, step)));
+    sincos_turn(n.t, n.s, n.c);
+    n.u = u01(w2);
+    return n;
+}
+
+// The decision on a proposal of the site (th, c, s): (sx, sy) = sums of the four
+// neighbours' (cos, sin), formed by the caller as (left + right) + (up + down).
+// Returns 1 if accepted; the angle the site holds afterwards and its (cos, sin)
+// come back in th, c, s.
+__device__ __forceinline__ int decide(const Proposal& n, float& th, float& c, float& s, float sx, float sy,
+                                      const Params& p, float* dE_out = nullptr)
+{
+    const float dc = __fsub_rn(n.c, c);
+    const float ds = __fsub_rn(n.s, s);
+    const float dE = -__fmaf_rn(dc, sx, __fmul_rn(ds, sy));
+    if (dE_out) *dE_out = dE;
+    const int acc = n.u < __builtin_amdgcn_exp2f(__fmul_rn(p.nbl2e, dE));
+    th = acc ? n.t : th;
+    c = acc ? n.c : c;
+    s = acc ? n.s : s;
+    return acc;
+}
+
+// One Metropolis update: w1 drives the proposal, w2 the acceptance.
 template <typename T>
 __device__ __forceinline__ int site_update(float& th, float& c, float& s, float sx, float sy,
                                            uint32_t w1, uint32_t w2, const Params& p,
                                            float* dE_out = nullptr)
 {
-    const float step = __fmul_rn(p.delta, sym11(w1));
-    float t = __builtin_amdgcn_fractf(__fadd_rn(th, step));
-    t = store<T>::rnd(t);
-    float sn, cn;
-    sincos_turn(t, sn, cn);
-    const float dc = __fsub_rn(cn, c);
-    const float ds = __fsub_rn(sn, s);
-    const float dE = -__fmaf_rn(dc, sx, __fmul_rn(ds, sy));
-    if (dE_out) *dE_out = dE;
-    const int acc = u01(w2) < __builtin_amdgcn_exp2f(__fmul_rn(p.nbl2e, dE));
-    th = acc ? t : th;
-    c = acc ? cn : c;
-    s = acc ? sn : s;
-    return acc;
+    return decide(propose<T>(th, w1, w2, p), th, c, s, sx, sy, p, dE_out);
 }
 
 __device__ __forceinline__ float nsum(float l, float r, float u, float d)

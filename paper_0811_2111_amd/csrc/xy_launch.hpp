@@ -76,8 +76,31 @@ bool strip_supported(int L, int tile_x, int tile_y);
 // obs[0 ..] (none if me == 0 or obs == NULL).
 bool resident_supported(int L);
 hipError_t launch_resident(const SweepArgs& a, int n, int me, xy_obs* obs, hipStream_t s);
+// The same for any even L <= 62, the records' terms gathered as launch_measure does.
+hipError_t launch_resident_any(const SweepArgs& a, int n, int me, xy_obs* obs, hipStream_t s);
 hipError_t launch_strip(const SweepArgs& a, int tile_x, int tile_y, bool meas, double* partials, hipStream_t s);
 int strip_records(int L, int tile_x, int tile_y);
+
+// Several sweeps per launch (xy_deep.hip): the lattice cut into tx x ty regions,
+// each grown so that n sweeps need no other region's results.
+struct DeepPlan {
+    int tx, ty;           // cores along a row and down the lattice
+    int PC, RY, hx, hy;   // a region's pairs and rows, its halo in pairs and rows
+    int rp, full;         // measured: columns of `full` pairs `rp` rows apart (0: pair by pair)
+};
+// The regions of d's tx x ty cores for n sweeps, if they fit into the lattice.
+bool deep_region(int L, int n, DeepPlan* d);
+// The regions and the most sweeps per launch for lattices that gain from it;
+// `meas`: for passes with a measured sweep.
+bool deep_choose(int L, bool meas, DeepPlan* d, int* nmax);
+// n sweeps from a.src to a.dst (two buffers).  Sweep j (1-based) is measured when
+// me > 0 and (j + phase) % me == 0; the k-th measured one leaves a record of
+// region b at part[(k * tx * ty + b) * 8].
+hipError_t launch_deep(const SweepArgs& a, const DeepPlan& d, int n, int me, int phase, double* part, hipStream_t s);
+// nrec records of np partial records each, back to back in `part`, into out[0 ..];
+// record k's sweep count is first + k * every.
+hipError_t launch_finalize_many(const double* part, int np, int nrec, xy_obs* out, uint64_t first, int every,
+                                hipStream_t s);
 
 // ---- hybrid Monte Carlo (xy_hmc.hip)
 constexpr int kHmcMaxRecords = 65536;   // partial records of one H sum (old or new)

@@ -192,12 +192,18 @@ struct xy_lattice {
     hipStream_t stream;
     uint64_t sweep;
     xy_plan plan;
+    bool own_plan;         // the plan is the library's choice (see auto_sweep)
     xyk::Work w;
     int32_t hmc_steps;     // leap-frog steps per pass of xy_hmc (1 .. 8)
     // kernel timer (xy_kernel_timer): event pairs around the sweep kernel launches
     hipEvent_t* tev;       // 2 * tcap events, or nullptr
     int32_t tcap, tn;
 };
+
+static bool same_plan(const xy_plan& a, const xy_plan& b)
+{
+    return a.kind == b.kind && a.tile_x == b.tile_x && a.tile_y == b.tile_y && a.sweeps_per_pass == b.sweeps_per_pass;
+}
 
 static bool live(const xy_lattice* h) { return h && h->magic == kMagic; }
 
@@ -217,6 +223,18 @@ int xy_state_bytes(int32_t L, int32_t precision, size_t* state, size_t* workspac
     if (state) *state = xyk::state_bytes(L, precision);
     if (workspace) *workspace = xyk::work_bytes(L, precision);
     return XY_OK;
+}
+
+// The tuned plan if one is cached, else the default.  A tuned plan that is the
+// default one stands for the library's choice too: the autotuner stores it where
+// that was the fastest.
+static void auto_plan(xy_lattice* h)
+{
+    const xy_plan d = default_plan(h->L, h->precision);
+    xy_plan p;
+    if (!cache_lookup(env_cache_path(), h->L, h->precision, &p)) p = d;
+    h->plan = p;
+    h->own_plan = same_plan(p, d);
 }
 
 static int make_handle(xy_lattice** out, uint64_t seed, int32_t L, double beta, double delta, int32_t precision,
@@ -246,9 +264,7 @@ static int make_handle(xy_lattice** out, uint64_t seed, int32_t L, double beta, 
     h->tev = nullptr;
     h->tcap = h->tn = 0;
     h->w = xyk::carve(work_dev, L, precision);
-    xy_plan p;
-    if (!cache_lookup(env_cache_path(), L, precision, &p)) p = default_plan(L, precision);
-    h->plan = p;
+    auto_plan(h);
     *out = h;
     return XY_OK;
 }
@@ -328,6 +344,97 @@ static int stream_sweep(xy_lattice* h, bool measured, xy_obs* rec, uint8_t* dbg_
     return XY_OK;
 }
 
+// Every sweep of a call in one launch of one workgroup; calls longer than 2^30
+// sweeps are split at a multiple of measure_every.
+static int resident_sweeps(xy_lattice* h, int64_t n_sweeps, int32_t me, xy_obs* obs, bool own)
+{
+    const int64_t cap = me ? ((int64_t)1 << 30) / me * me : ((int64_t)1 << 30);
+    for (int64_t done = 0; done < n_sweeps;) {
+        const int64_t m = std::min<int64_t>(cap, n_sweeps - done);
+        xyk::SweepArgs a = args_of(h);
+        auto launch = own ? xyk::launch_resident_any : xyk::launch_resident;
+        hipError_t e = XY_LAUNCH(launch(a, (int)m, me, me ? obs + done / me : nullptr, h->stream));
+        if (e != hipSuccess) return hip_fail(e, "resident sweep launch");
+        h->sweep += (uint64_t)m;
+        done += m;
+    }
+    return XY_OK;
+}
+
+// Passes of several sweeps (xy_deep.hip) from `state` to the ping-pong buffer and
+// back (plan[0]: without a measured sweep, plan[1]: with): an even number of them,
+// as equal as can be, so that the angles end in the caller's buffer.  The records'
+// partials collect in the workspace and are summed when it is full and at the end.
+// After a failed launch the records of the sweeps that were enqueued are written
+// and the latest angles copied back.
+static int deep_sweeps(xy_lattice* h, const xyk::DeepPlan plan[2], int nmax, int64_t n_sweeps, int32_t me,
+                       xy_obs* obs)
+{
+    const int64_t q = ((n_sweeps + nmax - 1) / nmax + 1) / 2 * 2;
+    const int np = plan[1].tx * plan[1].ty, room = h->w.max_partials / np;
+    int held = 0;            // records whose partials wait in the workspace
+    int64_t out = 0, j = 0;  // records written, sweeps done
+    const uint64_t base = h->sweep;
+    auto flush = [&](bool inject) {
+        if (held == 0) return hipSuccess;
+        auto go = [&] {
+            return xyk::launch_finalize_many(h->w.partials, np, held, obs + out,
+                                             base + (uint64_t)(out + 1) * (uint64_t)me, me, h->stream);
+        };
+        hipError_t e = inject ? XY_LAUNCH(go()) : go();
+        if (e == hipSuccess) {
+            out += held;
+            held = 0;
+        }
+        return e;
+    };
+    for (int64_t k = 0; k < q; ++k) {
+        const int n = (int)(n_sweeps / q + (k < n_sweeps % q));
+        const int phase = me ? (int)(j % me) : 0, nrec = me ? (int)((j + n) / me - j / me) : 0;
+        hipError_t e = held + nrec > room ? flush(true) : hipSuccess;
+        if (e == hipSuccess) {
+            xyk::SweepArgs a = args_of(h);
+            a.src = (k & 1) ? h->w.pingpong : h->state;
+            a.dst = (k & 1) ? h->state : h->w.pingpong;
+            xyk::DeepPlan d = plan[nrec > 0];
+            e = xyk::deep_region(h->L, n, &d)
+                    ? XY_LAUNCH(xyk::launch_deep(a, d, n, me, phase, h->w.partials + (size_t)held * np * 8, h->stream))
+                    : hipErrorInvalidValue;
+        }
+        if (e != hipSuccess) {
+            const int rc = hip_fail(e, "sweep launch");
+            (void)flush(false);
+            if (k & 1)
+                (void)hipMemcpyAsync(h->state, h->w.pingpong, xyk::state_bytes(h->L, h->precision),
+                                     hipMemcpyDeviceToDevice, h->stream);
+            return rc;
+        }
+        held += nrec;
+        j += n;
+        h->sweep += (uint64_t)n;
+    }
+    hipError_t e = flush(true);
+    return e == hipSuccess ? XY_OK : hip_fail(e, "finalize launch");
+}
+
+// Schedules the library takes on its own where no plan was asked for and no
+// launches are to be timed: the whole lattice in one workgroup while that is
+// faster than any tiling (L < 56: 0.7 to 1.8 us a sweep, 1.3 to 2.8 with a record
+// every sweep; two half-sweep launches take 6, with a record 12), then passes of
+// several sweeps (a single sweep gains nothing from them).  Returns false if neither applies.
+static bool own_schedule(xy_lattice* h, int64_t n_sweeps, int32_t me, xy_obs* obs, int* rc)
+{
+    xyk::DeepPlan plan[2];
+    int nmax, nmeas = 0;
+    if (!h->own_plan || h->tcap > 0 || n_sweeps == 0) return false;
+    if (h->L < 56) *rc = resident_sweeps(h, n_sweeps, me, obs, true);
+    else if (n_sweeps >= 2 && xyk::deep_choose(h->L, true, &plan[1], &nmeas) &&
+             xyk::deep_choose(h->L, false, &plan[0], &nmax))
+        *rc = deep_sweeps(h, plan, me ? std::min(nmax, nmeas) : nmax, n_sweeps, me, obs);
+    else return false;
+    return true;
+}
+
 int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs_dev)
 {
     if (!live(h)) return XY_ESTATE;
@@ -336,6 +443,8 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
     const bool meas = measure_every > 0 && obs_dev != nullptr;
     auto measured = [&](int64_t j) { return meas && (j % measure_every) == 0; };  // j = 1-based sweep in call
     auto rec_of = [&](int64_t j) { return obs_dev + (j / measure_every - 1); };
+    int own_rc;
+    if (own_schedule(h, n_sweeps, meas ? measure_every : 0, obs_dev, &own_rc)) return own_rc;
 
     if (h->plan.kind == XY_PLAN_STREAM) {
         for (int64_t j = 1; j <= n_sweeps; ++j) {
@@ -345,22 +454,8 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
         return XY_OK;
     }
 
-    if (h->plan.kind == XY_PLAN_RESIDENT) {
-        // every sweep of the call in one launch; calls longer than 2^30 sweeps are
-        // split at a multiple of measure_every
-        const int64_t cap = meas ? ((int64_t)1 << 30) / measure_every * measure_every : ((int64_t)1 << 30);
-        for (int64_t done = 0; done < n_sweeps;) {
-            const int64_t m = std::min<int64_t>(cap, n_sweeps - done);
-            xyk::SweepArgs a = args_of(h);
-            hipError_t e = XY_LAUNCH(xyk::launch_resident(a, (int)m, meas ? measure_every : 0,
-                                                          meas ? obs_dev + done / measure_every : nullptr,
-                                                          h->stream));
-            if (e != hipSuccess) return hip_fail(e, "resident sweep launch");
-            h->sweep += (uint64_t)m;
-            done += m;
-        }
-        return XY_OK;
-    }
+    if (h->plan.kind == XY_PLAN_RESIDENT)
+        return resident_sweeps(h, n_sweeps, meas ? measure_every : 0, meas ? obs_dev : nullptr, false);
 
     // Tiled schedules: ping-pong passes (state -> pingpong -> state ...); after an
     // odd number of passes the angles are copied back from the ping-pong buffer
@@ -514,12 +609,13 @@ int xy_set_stream(xy_lattice* h, void* hip_stream)
 int xy_set_plan(xy_lattice* h, const xy_plan* plan)
 {
     if (!live(h) || !plan) return XY_ESTATE;
-    xy_plan p = *plan;
-    if (p.kind == XY_PLAN_AUTO) {
-        if (!cache_lookup(env_cache_path(), h->L, h->precision, &p)) p = default_plan(h->L, h->precision);
+    if (plan->kind == XY_PLAN_AUTO) {
+        auto_plan(h);
+        return XY_OK;
     }
-    if (!plan_ok(h->L, p)) return XY_EINVAL;
-    h->plan = p;
+    if (!plan_ok(h->L, *plan)) return XY_EINVAL;
+    h->plan = *plan;
+    h->own_plan = false;
     return XY_OK;
 }
 
@@ -624,15 +720,23 @@ int xy_autotune(xy_lattice* h, int32_t sweeps_per_trial, const char* cache_path,
         (void)hipEventDestroy(e0);
         return hip_fail(e, "hipEventCreate");
     }
+    // the library's own choice, which may run several sweeps per launch, is a
+    // candidate under the name of the plan it stands for
+    const xy_plan own = default_plan(h->L, h->precision);
+    cands.push_back({XY_PLAN_AUTO, 0, 0, 1});
     const xy_plan saved = h->plan;
+    const bool saved_own = h->own_plan;
     double best_t = 1e300;
     xy_plan best_p = saved;
+    bool best_own = saved_own;
     int rc = XY_OK;
     // two rounds over the candidates, each candidate's best trial counting, so
     // that one slow trial (a clock change, another process) does not decide
     std::vector<xy_plan> trials(cands);
     trials.insert(trials.end(), cands.begin(), cands.end());
-    for (const xy_plan& p : trials) {
+    for (const xy_plan& t : trials) {
+        h->own_plan = t.kind == XY_PLAN_AUTO;
+        const xy_plan p = h->own_plan ? own : t;
         h->plan = p;
         if (h->sweep + 2ull * (uint64_t)sweeps_per_trial + 2 >= 0xffffffffull) h->sweep = 0;
         rc = xy_sweep(h, sweeps_per_trial, 0, nullptr);  // warm-up (sets LDS attributes, caches)
@@ -647,11 +751,13 @@ int xy_autotune(xy_lattice* h, int32_t sweeps_per_trial, const char* cache_path,
         if (ms < best_t) {
             best_t = ms;
             best_p = p;
+            best_own = h->own_plan;
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     h->plan = (rc == XY_OK) ? best_p : saved;
+    h->own_plan = (rc == XY_OK) ? best_own : saved_own;
     if (rc != XY_OK) return rc;
     if (best) *best = best_p;
     if (cache_path) {
@@ -698,6 +804,7 @@ int xyr::sweep_on_work(uint64_t seed, int32_t L, double beta, double delta, int3
     h.tcap = h.tn = 0;
     h.w = xyk::carve(work, L, precision);
     h.plan = default_plan(L, precision);
+    h.own_plan = true;
     // the workspace keeps the previous call's contents: the accept and arrival
     // counters must start at zero (a kernel, so the call may be graph-captured)
     hipError_t e = XY_LAUNCH(xyk::launch_zero_u64(h.w.counter, 4, stream));
