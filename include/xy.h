@@ -122,8 +122,8 @@ typedef struct xy_obs {
  *                   was not asked for by kind, small lattices run schedules of the
  *                   library's own in its place (L < 56: every sweep of a call in
  *                   one launch, the lattice on chip; up to L = 832: several sweeps
- *                   per launch on overlapping regions), unless xy_kernel_timer is
- *                   on. */
+ *                   per launch on overlapping regions) and larger ones single-sweep
+ *                   tiles that need not divide L, unless xy_kernel_timer is on. */
 enum { XY_PLAN_AUTO = 0, XY_PLAN_STREAM = 1, XY_PLAN_FUSED = 2, XY_PLAN_STRIP = 3, XY_PLAN_RESIDENT = 4 };
 typedef struct xy_plan {
     int32_t kind;

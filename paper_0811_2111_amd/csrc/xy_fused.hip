@@ -139,4 +139,94 @@ hipError_t launch_fused(const SweepArgs& a, int tile_x, int tile_y, int m, unsig
     return hipErrorInvalidValue;
 }
 
+// ------------------------------------------------------------- ragged tiles
+// Single-sweep tiles of 256 x 16 or 128 x 16 sites for any even side.
+static int ragged_tiles(int L, int tile_x) { return ((L + tile_x - 1) / tile_x) * ((L + 15) / 16); }
+
+int ragged_records(int L, int tile_x) { return 4 * ragged_tiles(L, tile_x); }
+
+int ragged_tile_x(int L)
+{
+    if (L < 256 || L % 2 || (long long)L * L * 4 >= (1LL << 32)) return 0;
+    // Sites the tiles cover, times what each shape costs: at L = 4096 the 128 x 16
+    // tiles take 8% longer (33.2 against 30.7 us a sweep: half as much work for each
+    // tile's loads and barriers), at L = 1024 7% less (4.97 against 5.35: the 256 x 16
+    // tiles are one workgroup a CU, with nothing to run while it waits).
+    const double w = L <= 1408 ? 0.93 : 1.08;
+    return ragged_tiles(L, 128) * 0.5 * w < ragged_tiles(L, 256) ? 128 : 256;
+}
+
+// ODD: L % 4 == 2.  Tiles inside the lattice take the program without bounds, which
+// interleaves a thread's Philox chains.  Unmeasured, the last tiles are moved back
+// inside instead of cut off (both tiles then write the overlap, the same values),
+// down the lattice and, where pairs stay aligned, along it.
+template <typename T, int TX, int MEAS, bool ST, bool ODD>
+__global__ void __launch_bounds__(256)
+k_ragged(const T* __restrict__ src, T* __restrict__ dst, int L, uint32_t sweep, uint32_t k0, uint32_t k1, Params p,
+         double* __restrict__ partials)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int tiles_x = (L + TX - 1) / TX, ntiles = tiles_x * ((L + 15) / 16);
+    const int b = xcd_tile((int)blockIdx.x, (int)gridDim.x);    // a grid of a multiple of 8
+    if (b >= ntiles) return;
+    const int ty = b / tiles_x;
+    int x0 = (b - ty * tiles_x) * TX, y0 = ty * 16;
+    if constexpr (MEAS == 0) {
+        y0 = min(y0, L - 16);
+        if constexpr (!ODD) x0 = min(x0, L - TX);
+    }
+    const unsigned bytes = (unsigned)((size_t)L * L * sizeof(T));
+    double* part = partials + (size_t)b * 4 * 8;
+    constexpr int odd = ODD ? kOdd : 0;
+    if (x0 + TX <= L && y0 + 16 <= L)
+        tile1_program<T, TX, 16, 256, MEAS, ST, odd>(src, dst, bytes, L, x0, y0, sweep, k0, k1, p, MEAS != 0, part,
+                                                     smem, nullptr);
+    else if constexpr (MEAS != 0 || ODD)
+        tile1_program<T, TX, 16, 256, MEAS, ST, odd | kPart>(src, dst, bytes, L, x0, y0, sweep, k0, k1, p, MEAS != 0,
+                                                             part, smem, nullptr);
+}
+
+template <typename T, int TX, int MEAS, bool ST, bool ODD>
+static hipError_t run_ragged_k(const SweepArgs& a, double* part, hipStream_t s)
+{
+    constexpr size_t lds = Tile1<TX, 16, 256>::lds_bytes;
+    static bool attr_set = false;
+    auto kern = k_ragged<T, TX, MEAS, ST, ODD>;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const Params p{a.delta, a.nbl2e};
+    hipLaunchKernelGGL(kern, dim3((unsigned)((ragged_tiles(a.L, TX) + 7) & ~7)), dim3(256), lds, s, (const T*)a.src,
+                       (T*)a.dst, a.L, a.sweep, a.key0, a.key1, p, part);
+    return hipGetLastError();
+}
+
+template <typename T, int TX, bool ST, bool ODD>
+static hipError_t run_ragged(const SweepArgs& a, bool meas, double* part, hipStream_t s)
+{
+    return meas ? run_ragged_k<T, TX, 2, ST, ODD>(a, part, s) : run_ragged_k<T, TX, 0, ST, ODD>(a, part, s);
+}
+
+template <typename T, bool ODD>
+static hipError_t pick_ragged(const SweepArgs& a, int tile_x, bool meas, double* part, hipStream_t s)
+{
+    if (tile_x == 128) return run_ragged<T, 128, false, ODD>(a, meas, part, s);
+    const bool st = 2 * (size_t)a.L * (size_t)a.L * sizeof(T) > kStreamBytes;
+    return st ? run_ragged<T, 256, true, ODD>(a, meas, part, s) : run_ragged<T, 256, false, ODD>(a, meas, part, s);
+}
+
+hipError_t launch_ragged(const SweepArgs& a, int tile_x, bool meas, double* part, hipStream_t s)
+{
+    if (ragged_tile_x(a.L) == 0 || (tile_x != 128 && tile_x != 256)) return hipErrorInvalidValue;
+    if (a.L % tile_x == 0 && !meas)    // whole tiles
+        return launch_fused(a, tile_x, 16, 1, 0u, part, s);
+    if (a.precision == XY_FP16)
+        return a.L % 4 ? pick_ragged<__half, true>(a, tile_x, meas, part, s)
+                       : pick_ragged<__half, false>(a, tile_x, meas, part, s);
+    return a.L % 4 ? pick_ragged<float, true>(a, tile_x, meas, part, s)
+                   : pick_ragged<float, false>(a, tile_x, meas, part, s);
+}
+
 }  // namespace xyk

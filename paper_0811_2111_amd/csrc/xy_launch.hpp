@@ -63,6 +63,12 @@ hipError_t launch_finalize(const double* partials, int nparts, unsigned long lon
 hipError_t launch_fused(const SweepArgs& a, int tile_x, int tile_y, int m, unsigned meas_mask,
                         double* partials, hipStream_t s);
 int fused_tiles(int L, int tile_x, int tile_y);
+// One sweep by tiles of tile_x (128 or 256) x 16 sites that need not divide the
+// lattice; measured: ragged_records(L, tile_x) partial records, their terms
+// gathered as launch_measure does.
+int ragged_tile_x(int L);        // the faster width, 0 if the lattice is out of range
+int ragged_records(int L, int tile_x);
+hipError_t launch_ragged(const SweepArgs& a, int tile_x, bool meas, double* partials, hipStream_t s);
 // Partial records one measured sweep of a fused launch writes (the sweep's
 // records start at partials + j * fused_records(...) * 8 for sub-sweep j).
 int fused_records(int L, int tile_x, int tile_y, int m);

@@ -446,7 +446,12 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
     int own_rc;
     if (own_schedule(h, n_sweeps, meas ? measure_every : 0, obs_dev, &own_rc)) return own_rc;
 
-    if (h->plan.kind == XY_PLAN_STREAM) {
+    // Where the plan is the library's choice, single sweeps take the faster of the
+    // ragged tiles in place of half-sweeps and, unmeasured, of a slower tile shape.
+    const int own_tx = h->own_plan && h->tcap == 0 ? xyk::ragged_tile_x(h->L) : 0;
+    const bool stream = h->plan.kind == XY_PLAN_STREAM;
+
+    if (stream && !own_tx) {
         for (int64_t j = 1; j <= n_sweeps; ++j) {
             int rc = stream_sweep(h, measured(j), measured(j) ? rec_of(j) : nullptr, nullptr, nullptr);
             if (rc != XY_OK) return rc;
@@ -467,8 +472,10 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
     // stays usable.
     const bool strip = h->plan.kind == XY_PLAN_STRIP;
     const int m = strip ? 1 : h->plan.sweeps_per_pass;
-    const int64_t passes = n_sweeps / m;
-    const int nrec = strip ? xyk::strip_records(h->L, h->plan.tile_x, h->plan.tile_y)
+    // (an odd last sweep is cheaper in place than with the copy back)
+    const int64_t passes = stream && (n_sweeps & 1) && !measured(n_sweeps) ? n_sweeps - 1 : n_sweeps / m;
+    const int nrec = stream ? xyk::ragged_records(h->L, own_tx)
+                   : strip ? xyk::strip_records(h->L, h->plan.tile_x, h->plan.tile_y)
                            : xyk::fused_records(h->L, h->plan.tile_x, h->plan.tile_y, m);
     int64_t j = 0;  // sweeps done in this call
     int64_t done_passes = 0;
@@ -488,10 +495,14 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
             if (measured(j + js + 1)) mask |= 1u << js;
         const bool timing = h->tn < h->tcap;
         if (timing) (void)hipEventRecord(h->tev[2 * h->tn], h->stream);
-        hipError_t e = XY_LAUNCH(strip ? xyk::launch_strip(a, h->plan.tile_x, h->plan.tile_y, mask != 0,
-                                                           h->w.partials, h->stream)
-                                       : xyk::launch_fused(a, h->plan.tile_x, h->plan.tile_y, m, mask,
-                                                           h->w.partials, h->stream));
+        auto launch = [&] {
+            if (strip)
+                return xyk::launch_strip(a, h->plan.tile_x, h->plan.tile_y, mask != 0, h->w.partials, h->stream);
+            if (stream || (own_tx && mask == 0))
+                return xyk::launch_ragged(a, own_tx, mask != 0, h->w.partials, h->stream);
+            return xyk::launch_fused(a, h->plan.tile_x, h->plan.tile_y, m, mask, h->w.partials, h->stream);
+        };
+        hipError_t e = XY_LAUNCH(launch());
         if (e != hipSuccess) return fail(e, "fused sweep launch");
         if (timing) (void)hipEventRecord(h->tev[2 * h->tn++ + 1], h->stream);
         done_passes = q + 1;

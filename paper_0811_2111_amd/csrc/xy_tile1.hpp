@@ -48,6 +48,11 @@ template <> struct bio<float> {
         return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off_elems * 4u, 0, 0));
     }
     template <bool ST = false>
+    static __device__ __forceinline__ void st1(__amdgpu_buffer_rsrc_t r, unsigned off_elems, float a)
+    {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(a), r, off_elems * 4u, 0, ST ? kCpolNT : 0);
+    }
+    template <bool ST = false>
     static __device__ __forceinline__ void st2(__amdgpu_buffer_rsrc_t r, unsigned off_elems, float a, float b)
     {
         xu2 v;
@@ -71,6 +76,12 @@ template <> struct bio<__half> {
         return __half2float(__ushort_as_half(v));
     }
     template <bool ST = false>
+    static __device__ __forceinline__ void st1(__amdgpu_buffer_rsrc_t r, unsigned off_elems, float a)
+    {
+        __builtin_amdgcn_raw_buffer_store_b16(__half_as_ushort(__float2half_rn(a)), r, off_elems * 2u, 0,
+                                              ST ? kCpolNT : 0);
+    }
+    template <bool ST = false>
     static __device__ __forceinline__ void st2(__amdgpu_buffer_rsrc_t r, unsigned off_elems, float a, float b)
     {
         const unsigned v = (unsigned)__half_as_ushort(__float2half_rn(a)) |
@@ -79,6 +90,46 @@ template <> struct bio<__half> {
     }
     static constexpr unsigned bytes = 2;
 };
+
+// Tiles of a lattice whose side they do not divide.  kPart: the last tile of a
+// row or column, which covers what is left.  kOdd: a lattice with L % 4 == 2,
+// whose half-rows have an odd number of entries, so that the last pair of a row
+// has one entry and rows are not aligned to pairs (binary16 pairs are then read
+// and written entry by entry).
+enum { kWhole = 0, kPart = 1, kOdd = 2 };
+
+template <typename T, int RAG>
+__device__ __forceinline__ float2 ld_pair(__amdgpu_buffer_rsrc_t r, unsigned off)
+{
+    if constexpr ((RAG & kOdd) && sizeof(T) == 2) return make_float2(bio<T>::ld1(r, off), bio<T>::ld1(r, off + 1));
+    else return bio<T>::ld2(r, off);
+}
+template <typename T, int RAG, bool ST>
+__device__ __forceinline__ void st_pair(__amdgpu_buffer_rsrc_t r, unsigned off, float a, float b, bool has_b)
+{
+    if constexpr (RAG & kOdd) {
+        if (has_b && sizeof(T) == 4) {
+            bio<T>::template st2<ST>(r, off, a, b);
+        } else {
+            bio<T>::template st1<ST>(r, off, a);
+            if (has_b) bio<T>::template st1<ST>(r, off + 1, b);
+        }
+    } else {
+        bio<T>::template st2<ST>(r, off, a, b);
+    }
+}
+
+// (cos, sin) of a pair into LDS.
+template <int RAG>
+__device__ __forceinline__ void put_pair(float2* __restrict__ at, const float4& v, bool has_b)
+{
+    if constexpr (RAG == (kPart | kOdd)) {
+        at[0] = make_float2(v.x, v.y);
+        if (has_b) at[1] = make_float2(v.z, v.w);
+    } else {
+        *(float4*)at = v;
+    }
+}
 
 // Raw buffer resource over `bytes` bytes at `base` (gfx9 descriptor word 3).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, unsigned bytes)
@@ -201,6 +252,10 @@ struct T1Geom {
     int s;           // pair slot within a core half-row
     int rt;          // row offset of this thread within a pass
     bool edge_tile;  // rows wrap around the lattice
+    // kPart: core entries of a half-row and core rows inside the lattice, whether
+    // this thread's pair lies inside, and whether its second entry does
+    int ce, re;
+    bool on, has_b;
 };
 
 template <typename S> __device__ __forceinline__ bool red_valid(const T1Geom& g, int q)
@@ -222,9 +277,19 @@ template <typename S> __device__ __forceinline__ int black_row(const T1Geom& g, 
     return (q < S::RB / S::RP - 1 || r < S::RB) ? r : r - S::RB;
 }
 
+// Whether pair item q lies in a kPart tile's share of the lattice (with its ring).
+template <typename S, int RAG> __device__ __forceinline__ bool red_in(const T1Geom& g, int q)
+{
+    return !(RAG & kPart) || (g.on && red_row<S>(g, q) <= g.re + 1);
+}
+template <typename S, int RAG> __device__ __forceinline__ bool black_in(const T1Geom& g, int q)
+{
+    return !(RAG & kPart) || (g.on && black_row<S>(g, q) <= g.re + 3);
+}
+
 // Red half-sweep (rows y0-1 .. y0+TY, columns kb-1 .. kb+TX/2); O = parity of this
 // thread's red rows.
-template <typename T, int TX, int TY, int NT, int O, bool ST>
+template <typename T, int TX, int TY, int NT, int O, bool ST, int RAG>
 __device__ __forceinline__ void tile1_red(const T1Geom& g, float2* __restrict__ cs, float2 (&thr)[Tile1<TX, TY, NT>::NQR],
                                           __amdgpu_buffer_rsrc_t dst, uint32_t sweep, uint32_t k0, uint32_t k1,
                                           const Params& p, float the, int e, int e_row, int e_col, int e_red, int e_k,
@@ -240,7 +305,7 @@ __device__ __forceinline__ void tile1_red(const T1Geom& g, float2* __restrict__ 
     u32x4 rr[S::NQR];
 #pragma unroll
     for (int q = 0; q < S::NQR; ++q) {
-        if (red_valid<S>(g, q)) {
+        if (red_valid<S>(g, q) && red_in<S, RAG>(g, q)) {
             const int y = g.y0 - 1 + red_row<S>(g, q);
             const int yw = g.edge_tile ? wrapi(y, g.L) : y;
             rr[q] = philox10(sweep, 0u, 0u, (uint32_t)yw * (uint32_t)g.P + jb, k0, k1);
@@ -248,7 +313,7 @@ __device__ __forceinline__ void tile1_red(const T1Geom& g, float2* __restrict__ 
     }
 #pragma unroll
     for (int q = 0; q < S::NQR; ++q) {
-        if (red_valid<S>(g, q)) {
+        if (red_valid<S>(g, q) && red_in<S, RAG>(g, q)) {
             const int row = red_row<S>(g, q);
             const PairNb<O> n(blk, S::WS, row + 1, c0);
             float4 own = *(const float4*)&cs[row * S::WS + c0];
@@ -258,25 +323,28 @@ __device__ __forceinline__ void tile1_red(const T1Geom& g, float2* __restrict__ 
                                           nsum(n.la.y, n.ra.y, n.ua.y, n.da.y), r.x, r.y, p);
             const int ab = site_update<T>(tb, own.z, own.w, nsum(n.lb.x, n.rb.x, n.ub.x, n.db.x),
                                           nsum(n.lb.y, n.rb.y, n.ub.y, n.db.y), r.z, r.w, p);
-            *(float4*)&cs[row * S::WS + c0] = own;
-            if (q < FULL || (row >= 1 && row <= TY)) {
-                acc += aa + ab;
-                bio<T>::template st2<ST>(dst, (unsigned)(g.y0 - 1 + row) * (unsigned)g.Hh +
-                                                  (unsigned)(g.kb + 2 * g.s), ta, tb);
+            put_pair<RAG>(&cs[row * S::WS + c0], own, g.has_b);
+            if ((RAG & kPart) ? row >= 1 && row <= g.re : q < FULL || (row >= 1 && row <= TY)) {
+                acc += aa + ((RAG & kOdd) && !g.has_b ? 0 : ab);
+                st_pair<T, RAG, ST>(dst, (unsigned)(g.y0 - 1 + row) * (unsigned)g.Hh + (unsigned)(g.kb + 2 * g.s), ta,
+                                    tb, g.has_b);
             }
         }
     }
     if (e < S::NEDGE && e_red) {          // the one ring entry of red row e_row
         const int y = g.y0 - 1 + e_row;
         const int o = y & 1;
-        const int j = e_k >> 1;            // e_k = kb-1 (odd: words 2, 3) or kb+TX/2 (even: words 0, 1)
+        // the entry kb-1 (odd: words 2, 3; across the edge of an odd half-row even) or
+        // the one after the core's last (even: words 0, 1)
+        const int kw = (RAG & kOdd) ? wrapi(e_k, g.Hh) : e_k;
+        const int j = kw >> 1;
         const u32x4 r = philox10(sweep, 0u, 0u, (uint32_t)wrapi(y, g.L) * (uint32_t)g.P + (uint32_t)wrapi(j, g.P),
                                  k0, k1);
         const int b = e_row + 1;           // black row of the same y
         const float2 l = blk[b * S::WS + e_col + o - 1], rt = blk[b * S::WS + e_col + o];
         const float2 u = blk[(b - 1) * S::WS + e_col], d = blk[(b + 1) * S::WS + e_col];
         float2 own = cs[e_row * S::WS + e_col];
-        const bool odd = (e_k & 1) != 0;
+        const bool odd = (kw & 1) != 0;
         site_update<T>(the, own.x, own.y, nsum(l.x, rt.x, u.x, d.x), nsum(l.y, rt.y, u.y, d.y), odd ? r.z : r.x,
                        odd ? r.w : r.y, p);
         cs[e_row * S::WS + e_col] = own;
@@ -285,11 +353,11 @@ __device__ __forceinline__ void tile1_red(const T1Geom& g, float2* __restrict__ 
 
 // Black half-sweep of the interior rows y0 .. y0+TY-1 (black LDS rows 2 .. TY+1);
 // O = parity of this thread's black rows.
-template <typename T, int TX, int TY, int NT, int O, bool MEAS, bool ST>
+template <typename T, int TX, int TY, int NT, int O, int MEAS, bool ST, int RAG>
 __device__ __forceinline__ void tile1_black(const T1Geom& g, const float2* __restrict__ cs,
                                             float2 (&thb)[Tile1<TX, TY, NT>::NQB], __amdgpu_buffer_rsrc_t dst,
                                             uint32_t sweep, uint32_t k0, uint32_t k1, const Params& p, int& acc,
-                                            MeasAcc& m)
+                                            MeasAcc& m, double (&v)[7])
 {
     using S = Tile1<TX, TY, NT>;
     constexpr int FULL = TY / S::RP;           // passes entirely inside rows 2 .. TY+1
@@ -300,13 +368,15 @@ __device__ __forceinline__ void tile1_black(const T1Geom& g, const float2* __res
 #pragma unroll
     for (int q = 0; q < S::NQB; ++q) {
         const int row = black_row<S>(g, q);
-        if (q < FULL || (black_valid<S>(g, q) && row >= 2 && row < TY + 2))
+        if ((RAG & kPart) ? black_valid<S>(g, q) && g.on && row >= 2 && row < g.re + 2
+                          : q < FULL || (black_valid<S>(g, q) && row >= 2 && row < TY + 2))
             rb[q] = philox10(sweep, 1u, 0u, (uint32_t)(g.y0 - 2 + row) * (uint32_t)g.P + jb, k0, k1);
     }
 #pragma unroll
     for (int q = 0; q < S::NQB; ++q) {
         const int row = black_row<S>(g, q);
-        if (q < FULL || (black_valid<S>(g, q) && row >= 2 && row < TY + 2)) {
+        if ((RAG & kPart) ? black_valid<S>(g, q) && g.on && row >= 2 && row < g.re + 2
+                          : q < FULL || (black_valid<S>(g, q) && row >= 2 && row < TY + 2)) {
             const int y = g.y0 - 2 + row;  // interior: never wraps
             const PairNb<O> n(cs, S::WS, row - 1, c0);
             const float4 own = *(const float4*)&blk[row * S::WS + c0];
@@ -317,10 +387,17 @@ __device__ __forceinline__ void tile1_black(const T1Geom& g, const float2* __res
                                           nsum(n.la.y, n.ra.y, n.ua.y, n.da.y), r.x, r.y, p);
             const int ab = site_update<T>(tb, cb, sb, nsum(n.lb.x, n.rb.x, n.ub.x, n.db.x),
                                           nsum(n.lb.y, n.rb.y, n.ub.y, n.db.y), r.z, r.w, p);
-            acc += aa + ab;
-            bio<T>::template st2<ST>(dst, ((unsigned)g.L + (unsigned)y) * (unsigned)g.Hh + (unsigned)(g.kb + 2 * g.s),
-                                     ta, tb);
-            if constexpr (MEAS) {
+            acc += aa + ((RAG & kOdd) && !g.has_b ? 0 : ab);
+            st_pair<T, RAG, ST>(dst, ((unsigned)g.L + (unsigned)y) * (unsigned)g.Hh + (unsigned)(g.kb + 2 * g.s), ta,
+                                tb, g.has_b);
+            if constexpr (MEAS == 2) {
+                Meas t{0, 0, 0, 0, 0, 0};
+                meas_black(t, ca, sa, n.la.x, n.la.y, n.ra.x, n.ra.y, n.ua.x, n.ua.y, n.da.x, n.da.y);
+                if (!(RAG & kOdd) || g.has_b)
+                    meas_black(t, cb, sb, n.lb.x, n.lb.y, n.rb.x, n.rb.y, n.ub.x, n.ub.y, n.db.x, n.db.y);
+                v[0] += (double)t.cx; v[1] += (double)t.cy; v[2] += (double)t.ix;
+                v[3] += (double)t.iy; v[4] += (double)t.mx; v[5] += (double)t.my;
+            } else if constexpr (MEAS == 1) {
                 meas_acc(m, ca, sa, n.la, n.ra, n.ua, n.da);
                 meas_acc(m, cb, sb, n.lb, n.rb, n.ub, n.db);
             }
@@ -329,7 +406,7 @@ __device__ __forceinline__ void tile1_black(const T1Geom& g, const float2* __res
 }
 
 // Per-tile geometry: the tile at (x0, y0) of an L x L lattice.
-template <int TX, int TY, int NT>
+template <int TX, int TY, int NT, int RAG = kWhole>
 __device__ __forceinline__ T1Geom tile1_geom(int L, int x0, int y0)
 {
     using S = Tile1<TX, TY, NT>;
@@ -337,7 +414,7 @@ __device__ __forceinline__ T1Geom tile1_geom(int L, int x0, int y0)
     T1Geom g;
     g.L = L;
     g.Hh = L >> 1;
-    g.P = g.Hh >> 1;
+    g.P = ((RAG & kOdd) ? g.Hh + 1 : g.Hh) >> 1;
     g.kb = x0 >> 1;
     g.x0 = x0;
     g.y0 = y0;
@@ -349,6 +426,11 @@ __device__ __forceinline__ T1Geom tile1_geom(int L, int x0, int y0)
     const int i = lane >> S::LGQ;
     g.rt = 2 * (i * (S::NW / 2) + (w >> 1)) + (w & 1);   // parity of the wave
     g.edge_tile = (y0 < 2) || (y0 + TY + 2 > L);
+    constexpr bool part = (RAG & kPart) != 0;
+    g.ce = part ? min(TX / 2, g.Hh - g.kb) : TX / 2;
+    g.re = part ? min(TY, L - y0) : TY;
+    g.on = !part || 2 * g.s < g.ce;
+    g.has_b = !part || 2 * g.s + 1 < g.ce;
     return g;
 }
 
@@ -360,10 +442,11 @@ struct T1Regs {
     float2 thr[Tile1<TX, TY, NT>::NQR], thb[Tile1<TX, TY, NT>::NQB];
     float the;
     int e_row, e_col, e_red, e_k;
+    bool e_on;
 };
 
 // Issue every load of the tile (no wait).
-template <typename T, int TX, int TY, int NT>
+template <typename T, int TX, int TY, int NT, int RAG = kWhole>
 __device__ __forceinline__ void tile1_load(const T1Geom& g, __amdgpu_buffer_rsrc_t rs, T1Regs<TX, TY, NT>& a)
 {
     using S = Tile1<TX, TY, NT>;
@@ -371,24 +454,25 @@ __device__ __forceinline__ void tile1_load(const T1Geom& g, __amdgpu_buffer_rsrc
     const unsigned col = (unsigned)(g.kb + 2 * g.s);
 #pragma unroll
     for (int q = 0; q < S::NQR; ++q) {
-        if (red_valid<S>(g, q)) {
+        if (red_valid<S>(g, q) && red_in<S, RAG>(g, q)) {
             const int y0r = y0 - 1 + red_row<S>(g, q);
             const int y = g.edge_tile ? wrapi(y0r, L) : y0r;
-            a.thr[q] = bio<T>::ld2(rs, (unsigned)y * (unsigned)g.Hh + col);
+            a.thr[q] = ld_pair<T, RAG>(rs, (unsigned)y * (unsigned)g.Hh + col);
         }
     }
 #pragma unroll
     for (int q = 0; q < S::NQB; ++q) {
-        if (black_valid<S>(g, q)) {
+        if (black_valid<S>(g, q) && black_in<S, RAG>(g, q)) {
             const int y0b = y0 - 2 + black_row<S>(g, q);
             const int y = g.edge_tile ? wrapi(y0b, L) : y0b;
-            a.thb[q] = bio<T>::ld2(rs, ((unsigned)L + (unsigned)y) * (unsigned)g.Hh + col);
+            a.thb[q] = ld_pair<T, RAG>(rs, ((unsigned)L + (unsigned)y) * (unsigned)g.Hh + col);
         }
     }
     const int e = NT - 1 - (int)threadIdx.x;
     a.the = 0.0f;
     a.e_row = 0; a.e_col = 0; a.e_red = 0; a.e_k = 0;
-    if (e < S::NEDGE) {
+    a.e_on = e < S::NEDGE && (!(RAG & kPart) || (e < S::RR ? e <= g.re + 1 : ((e - S::RR) >> 1) <= g.re + 3));
+    if (a.e_on) {
         int yl, side;
         if (e < S::RR) {                   // red row y0-1+e: the side its ring update needs
             a.e_red = 1;
@@ -401,8 +485,8 @@ __device__ __forceinline__ void tile1_load(const T1Geom& g, __amdgpu_buffer_rsrc
             yl = y0 - 2 + a.e_row;
             side = e2 & 1;
         }
-        a.e_k = side ? g.kb + TX / 2 : g.kb - 1;
-        a.e_col = side ? TX / 2 + 2 : 1;
+        a.e_k = side ? g.kb + g.ce : g.kb - 1;
+        a.e_col = side ? g.ce + 2 : 1;
         a.the = bio<T>::ld1(rs, ((unsigned)(a.e_red ? 0 : L) + (unsigned)wrapi(yl, L)) * (unsigned)g.Hh +
                                     (unsigned)wrapi(a.e_k, g.Hh));
     }
@@ -410,29 +494,30 @@ __device__ __forceinline__ void tile1_load(const T1Geom& g, __amdgpu_buffer_rsrc
 
 // (cos, sin) of every loaded entry into LDS (waits for the loads); the caller
 // places the barrier.
-template <int TX, int TY, int NT>
+template <int TX, int TY, int NT, int RAG = kWhole>
 __device__ __forceinline__ void tile1_fill(const T1Geom& g, float2* __restrict__ cs, const T1Regs<TX, TY, NT>& a)
 {
     using S = Tile1<TX, TY, NT>;
 #pragma unroll
     for (int q = 0; q < S::NQR; ++q) {
-        if (red_valid<S>(g, q)) {
+        if (red_valid<S>(g, q) && red_in<S, RAG>(g, q)) {
             float sa, ca, sb, cb;
             sincos_turn(a.thr[q].x, sa, ca);
             sincos_turn(a.thr[q].y, sb, cb);
-            *(float4*)&cs[red_row<S>(g, q) * S::WS + 2 * g.s + 2] = make_float4(ca, sa, cb, sb);
+            put_pair<RAG>(&cs[red_row<S>(g, q) * S::WS + 2 * g.s + 2], make_float4(ca, sa, cb, sb), g.has_b);
         }
     }
 #pragma unroll
     for (int q = 0; q < S::NQB; ++q) {
-        if (black_valid<S>(g, q)) {
+        if (black_valid<S>(g, q) && black_in<S, RAG>(g, q)) {
             float sa, ca, sb, cb;
             sincos_turn(a.thb[q].x, sa, ca);
             sincos_turn(a.thb[q].y, sb, cb);
-            *(float4*)&cs[S::BLACK0 + black_row<S>(g, q) * S::WS + 2 * g.s + 2] = make_float4(ca, sa, cb, sb);
+            put_pair<RAG>(&cs[S::BLACK0 + black_row<S>(g, q) * S::WS + 2 * g.s + 2], make_float4(ca, sa, cb, sb),
+                          g.has_b);
         }
     }
-    if (NT - 1 - (int)threadIdx.x < S::NEDGE) {
+    if (a.e_on) {
         float s_, c_;
         sincos_turn(a.the, s_, c_);
         cs[(a.e_red ? 0 : S::BLACK0) + a.e_row * S::WS + a.e_col] = make_float2(c_, s_);
@@ -441,7 +526,7 @@ __device__ __forceinline__ void tile1_fill(const T1Geom& g, float2* __restrict__
 
 // Both half-sweeps of a filled tile (after the fill's barrier); the updated angles
 // go to rd.  MEAS and ST as for tile1_program.  Ends with the black updates (no barrier).
-template <typename T, int TX, int TY, int NT, int MEAS, bool ST = false>
+template <typename T, int TX, int TY, int NT, int MEAS, bool ST = false, int RAG = kWhole>
 __device__ __forceinline__ void tile1_sweep(const T1Geom& g, float2* __restrict__ cs, T1Regs<TX, TY, NT>& a,
                                             __amdgpu_buffer_rsrc_t rd, uint32_t sweep, uint32_t k0, uint32_t k1,
                                             const Params& p, bool meas, double* part, double* red)
@@ -450,24 +535,29 @@ __device__ __forceinline__ void tile1_sweep(const T1Geom& g, float2* __restrict_
     const int e = NT - 1 - tid;
     int acc = 0;
     MeasAcc m;
+    double v[7] = {0, 0, 0, 0, 0, 0, 0};
     // wave-uniform (rt has the wave's parity): made scalar so both phases branch per
     // wave instead of running both parity variants under exec masks
     const bool red_odd = __builtin_amdgcn_readfirstlane((g.y0 + g.rt) & 1) != 0;
     if (red_odd)
-        tile1_red<T, TX, TY, NT, 1, ST>(g, cs, a.thr, rd, sweep, k0, k1, p, a.the, e, a.e_row, a.e_col, a.e_red, a.e_k,
+        tile1_red<T, TX, TY, NT, 1, ST, RAG>(g, cs, a.thr, rd, sweep, k0, k1, p, a.the, e, a.e_row, a.e_col, a.e_red, a.e_k,
                                     acc);
     else
-        tile1_red<T, TX, TY, NT, 0, ST>(g, cs, a.thr, rd, sweep, k0, k1, p, a.the, e, a.e_row, a.e_col, a.e_red, a.e_k,
+        tile1_red<T, TX, TY, NT, 0, ST, RAG>(g, cs, a.thr, rd, sweep, k0, k1, p, a.the, e, a.e_row, a.e_col, a.e_red, a.e_k,
                                     acc);
     __syncthreads();
-    if (MEAS == 1 || (MEAS == -1 && meas)) {
+    if (MEAS > 0 || (MEAS == -1 && meas)) {
+        constexpr int how = MEAS == 2 ? 2 : 1;
         if (red_odd)
-            tile1_black<T, TX, TY, NT, 0, true, ST>(g, cs, a.thb, rd, sweep, k0, k1, p, acc, m);
+            tile1_black<T, TX, TY, NT, 0, how, ST, RAG>(g, cs, a.thb, rd, sweep, k0, k1, p, acc, m, v);
         else
-            tile1_black<T, TX, TY, NT, 1, true, ST>(g, cs, a.thb, rd, sweep, k0, k1, p, acc, m);
-        double v[7] = {(double)m.cx, (double)m.cy, (double)m.ix, (double)m.iy, (double)m.mx, (double)m.my,
-                       (double)acc};
-        if constexpr (MEAS == 1) {
+            tile1_black<T, TX, TY, NT, 1, how, ST, RAG>(g, cs, a.thb, rd, sweep, k0, k1, p, acc, m, v);
+        if constexpr (how == 1) {
+            v[0] = (double)m.cx; v[1] = (double)m.cy; v[2] = (double)m.ix;
+            v[3] = (double)m.iy; v[4] = (double)m.mx; v[5] = (double)m.my;
+        }
+        v[6] = (double)acc;
+        if constexpr (MEAS > 0) {
 #pragma unroll
             for (int q = 0; q < 7; ++q) v[q] = wave_sum_last(v[q]);
             if ((tid & 63) == 63) {
@@ -486,9 +576,9 @@ __device__ __forceinline__ void tile1_sweep(const T1Geom& g, float2* __restrict_
         }
     } else {
         if (red_odd)
-            tile1_black<T, TX, TY, NT, 0, false, ST>(g, cs, a.thb, rd, sweep, k0, k1, p, acc, m);
+            tile1_black<T, TX, TY, NT, 0, 0, ST, RAG>(g, cs, a.thb, rd, sweep, k0, k1, p, acc, m, v);
         else
-            tile1_black<T, TX, TY, NT, 1, false, ST>(g, cs, a.thb, rd, sweep, k0, k1, p, acc, m);
+            tile1_black<T, TX, TY, NT, 1, 0, ST, RAG>(g, cs, a.thb, rd, sweep, k0, k1, p, acc, m, v);
     }
 }
 
@@ -498,27 +588,29 @@ __device__ __forceinline__ void tile1_sweep(const T1Geom& g, float2* __restrict_
 //   MEAS = 1 : always measure, one partial record per wave at part[wave * 8 ..]
 //              (no barrier and no cross-wave step: the records are summed later in
 //              a fixed order);
+//   MEAS = 2 : the same, each pair's FP32 terms by themselves as k_measure gathers
+//              them (MEAS = 1: a thread's pairs one after another);
 //   MEAS = -1: measure if `meas`, one partial record per tile at part[0 .. 8].
 // A record is (Cx, Cy, Ix, Iy, Mx, My, accepts, 0).
 // ST: the updated angles are stored with the non-temporal hint (for lattices
 // larger than the caches: the stored lines are read again only a sweep later).
-template <typename T, int TX, int TY, int NT, int MEAS = -1, bool ST = false>
+template <typename T, int TX, int TY, int NT, int MEAS = -1, bool ST = false, int RAG = kWhole>
 __device__ __forceinline__ void tile1_program(const T* __restrict__ src, T* __restrict__ dst, unsigned state_bytes,
                                               int L, int x0, int y0, uint32_t sweep, uint32_t k0, uint32_t k1,
                                               const Params& p, bool meas, double* part, char* smem, double* red)
 {
     float2* cs = (float2*)smem;
-    const T1Geom g = tile1_geom<TX, TY, NT>(L, x0, y0);
+    const T1Geom g = tile1_geom<TX, TY, NT, RAG>(L, x0, y0);
     T1Regs<TX, TY, NT> a;
     // The fill (loads, sin/cos, LDS writes) holds up the whole workgroup at its
     // barrier; its waves issue ahead of other workgroups' update work on the same
     // SIMD (measured: +2% on a sweep with records every 10, neutral otherwise).
     __builtin_amdgcn_s_setprio(2);
-    tile1_load<T, TX, TY, NT>(g, make_rsrc(src, state_bytes), a);
-    tile1_fill<TX, TY, NT>(g, cs, a);
+    tile1_load<T, TX, TY, NT, RAG>(g, make_rsrc(src, state_bytes), a);
+    tile1_fill<TX, TY, NT, RAG>(g, cs, a);
     __syncthreads();
     __builtin_amdgcn_s_setprio(0);
-    tile1_sweep<T, TX, TY, NT, MEAS, ST>(g, cs, a, make_rsrc(dst, state_bytes), sweep, k0, k1, p, meas, part,
+    tile1_sweep<T, TX, TY, NT, MEAS, ST, RAG>(g, cs, a, make_rsrc(dst, state_bytes), sweep, k0, k1, p, meas, part,
                                          red);
 }
 
