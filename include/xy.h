@@ -304,12 +304,12 @@ int xy_hmc(xy_lattice* h, int64_t n_traj, int32_t n_md, double eps, void* hmc_wo
            xy_hmc_obs* obs_dev);
 
 /* Leap-frog steps per pass over the lattice (1 .. 8, default 7; XY_EINVAL
- * otherwise).  With more than one, for L % 32 == 0, a workgroup loads a 64 x 64
- * tile (32 x 32 if L % 64 != 0) grown by that many sites on every side, runs the
- * steps on it (the grown part shrinking by one site per step) and writes the
- * tile back, so HBM traffic per site and step falls by that factor; the
- * trajectory is bit for bit the same.  xy_hmc_get_steps_per_pass reports what
- * runs (1 if L % 32 != 0). */
+ * otherwise).  With more than one a workgroup loads a region of the lattice (128
+ * sites wide, 32 or 64 high) into registers, runs the steps on it and writes back
+ * the core that is that many sites away from its edge, so HBM traffic per site and
+ * step falls by that factor; the trajectory is bit for bit the same.
+ * xy_hmc_get_steps_per_pass reports the setting where L % 32 == 0, else 1 (such
+ * lattices take the same passes). */
 int xy_hmc_set_steps_per_pass(xy_lattice* h, int32_t steps);
 int xy_hmc_get_steps_per_pass(const xy_lattice* h, int32_t* steps);
 
@@ -349,10 +349,8 @@ int xy_quad_hmc_get_steps_per_pass(const xy_quad* q, int32_t* steps);
  * lattice), so every lattice follows bit for bit the trajectory that xy_hmc
  * gives a single lattice with the same seed, beta, counter, n_md, eps and leap-
  * frog steps per pass.  One trajectory of all lattices is captured once into a
- * HIP graph and replayed: with passes of several leap-frog steps, the lattices
- * with L % 64 == 0 share one launch per stage of the trajectory (ends, passes,
- * decide, restore); the others run their own launches, spread over four
- * concurrent branches.  The graph is rebuilt when n_traj, n_md, eps, the steps
+ * HIP graph and replayed: the lattices share one launch per stage of the
+ * trajectory (ends, passes, decide, restore).  The graph is rebuilt when n_traj, n_md, eps, the steps
  * per pass, the workspace or obs_dev change, and after xy_batch_tempering has
  * moved betas between lattices.
  * hmc_work: caller-owned device memory of xy_batch_hmc_work_bytes bytes (per

@@ -565,8 +565,6 @@ struct Shape {
 // the small ones exist so that any batch of L % 4 == 0 lattices can run.
 static const Shape kShapes[] = {{64, 32}, {64, 16}, {32, 16}, {16, 16}, {8, 8}, {4, 4}};
 static constexpr int kNT = 256;
-// Streams a batched HMC trajectory forks into (lattices run side by side).
-static constexpr int kHmcStreams = 4;
 // Longest per-sweep launch sequence captured in one graph (longer calls replay it).
 static constexpr int kMaxGraphPasses = 16384;
 
@@ -716,10 +714,8 @@ struct xy_batch {
     int g_nrec;
     int g_grid;
     int g_sched;
-    // batched HMC: extra capture streams, join events and the cached graph of one
-    // trajectory of every lattice (key: n_md, eps, steps per pass, workspace, records on/off)
-    hipStream_t hs[kHmcStreams];
-    hipEvent_t hev[kHmcStreams];
+    // batched HMC: the cached graph of one trajectory of every lattice (key: n_md,
+    // eps, steps per pass, workspace, records on/off)
     hipGraph_t hgraph;
     hipGraphExec_t hexec;
     int32_t h_nmd, h_steps;
@@ -758,10 +754,6 @@ static void release(xy_batch* b)
 {
     drop_graph(b);
     drop_hmc_graph(b);
-    for (int k = 0; k < kHmcStreams; ++k) {
-        if (b->hs[k]) (void)hipStreamDestroy(b->hs[k]);
-        if (b->hev[k]) (void)hipEventDestroy(b->hev[k]);
-    }
     if (b->cap) (void)hipStreamDestroy(b->cap);
     if (b->cap2) (void)hipStreamDestroy(b->cap2);
     if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
@@ -1036,10 +1028,6 @@ int xy_batch_init(xy_batch** out, int32_t n, const uint64_t* seeds, const int32_
     b->g_obs = nullptr;
     b->g_grid = 0;
     b->g_sched = -1;
-    for (int k = 0; k < kHmcStreams; ++k) {
-        b->hs[k] = nullptr;
-        b->hev[k] = nullptr;
-    }
     b->hgraph = nullptr;
     b->hexec = nullptr;
     b->h_nmd = -1;
@@ -1364,16 +1352,6 @@ int xy_batch_hmc(xy_batch* b, int64_t n_traj, int32_t n_md, double eps, void* hm
     if (b->sweep + (uint64_t)n_traj >= 0xffffffffull || n_traj > INT32_MAX) return XY_ERANGE;
     if (n_traj == 0) return XY_OK;
     hipError_t e;
-    for (int k = 1; k < kHmcStreams; ++k) {
-        if (!b->hs[k] && (e = hipStreamCreateWithFlags(&b->hs[k], hipStreamNonBlocking)) != hipSuccess) {
-            b->hs[k] = nullptr;
-            return xyr::hip_fail(e, "xy_batch_hmc: hipStreamCreate");
-        }
-        if (!b->hev[k] && (e = hipEventCreateWithFlags(&b->hev[k], hipEventDisableTiming)) != hipSuccess) {
-            b->hev[k] = nullptr;
-            return xyr::hip_fail(e, "xy_batch_hmc: hipEventCreate");
-        }
-    }
     Ctrl* ctrl = (Ctrl*)(b->work + b->lo.ctrl_off);
     char* hw = (char*)hmc_work;
     xy_hmc_obs* stage = (xy_hmc_obs*)(hw + staging);
@@ -1382,81 +1360,47 @@ int xy_batch_hmc(xy_batch* b, int64_t n_traj, int32_t n_md, double eps, void* hm
     if (!b->hexec || b->h_nmd != n_md || b->h_eps != eps || b->h_steps != b->hmc_steps || b->h_work != hmc_work ||
         b->h_obs != obs_dev || b->h_ntraj != n_traj || b->h_pgen != b->pgen) {
         // one trajectory of every lattice, captured once and replayed per
-        // trajectory; the kernels read the trajectory index from the batch's device
-        // counter.  Lattices with L % 64 == 0 (with passes of several steps) go
-        // through the batched stages, one launch per stage for all of them; the
-        // others are spread over kHmcStreams branches (greedy by L^2) with their
-        // own single-lattice launches.
+        // trajectory, one launch per stage for all of them; the kernels read the
+        // trajectory index from the batch's device counter
         if ((e = hipStreamSynchronize(b->stream)) != hipSuccess)     // a copy may still read the host descriptors
             return xyr::hip_fail(e, "xy_batch_hmc: hipStreamSynchronize");
         drop_hmc_graph(b);
-        std::vector<int> fast;
-        if (b->hmc_steps > 1)
-            for (int i = 0; i < b->n; ++i)
-                if (xyk::hmc_batch_supported(b->L[i])) fast.push_back(i);
-        const int nf = (int)fast.size();
+        const int kh = xyk::hmc_batch_steps(n_md, b->hmc_steps);
+        const int rows = xyk::hmc_batch_rows(b->n, b->L.data(), kh);
         uint32_t totals[3] = {0, 0, 0};
-        std::vector<char> isfast(b->n, 0);
-        double load[kHmcStreams] = {0.0};
-        const size_t eb = sizeof(float);
-        if (nf > 0) {
-            std::vector<xyk::BhLat>& hd = b->h_desc;
-            std::vector<uint32_t>& hs = b->h_start;
-            hd.assign(nf, xyk::BhLat{});
-            hs.assign(3 * (size_t)(nf + 1), 0u);
-            for (int f = 0; f < nf; ++f) {
-                const int i = fast[f];
-                isfast[i] = 1;
-                const LatDesc& ld = b->desc[i];
-                xyk::BhLat& q = hd[f];
-                q.st = (float*)(b->state + (size_t)ld.off * eb);
-                q.pp = (float*)(b->work + b->lo.pp_off + (size_t)ld.off * eb);
-                q.w = xyk::hmc_carve_compact(hw + off[i], b->L[i]);
-                q.obs = stage + i;
-                q.k0 = ld.key0;
-                q.k1 = ld.key1;
-                xyk::hmc_batch_describe(q, b->L[i], b->beta[i], eps);
-                uint32_t nb[3];
-                xyk::hmc_batch_blocks(b->L[i], nb);
-                for (int g = 0; g < 3; ++g) {
-                    hs[(size_t)g * (nf + 1) + f] = totals[g];
-                    if ((uint64_t)totals[g] + nb[g] > 0x7fffffffull) {
-                        drop_hmc_graph(b);
-                        return XY_ESIZE;
-                    }
-                    totals[g] += nb[g];
+        const size_t eb = sizeof(float), stride = (size_t)b->n + 1;
+        std::vector<xyk::BhLat>& hd = b->h_desc;
+        std::vector<uint32_t>& hs = b->h_start;
+        hd.assign(b->n, xyk::BhLat{});
+        hs.assign(3 * stride, 0u);
+        for (int i = 0; i < b->n; ++i) {
+            const LatDesc& ld = b->desc[i];
+            xyk::BhLat& q = hd[i];
+            q.st = (float*)(b->state + (size_t)ld.off * eb);
+            q.pp = (float*)(b->work + b->lo.pp_off + (size_t)ld.off * eb);
+            q.w = xyk::hmc_carve_compact(hw + off[i], b->L[i]);
+            q.obs = stage + i;
+            q.k0 = ld.key0;
+            q.k1 = ld.key1;
+            xyk::hmc_batch_describe(q, b->L[i], b->beta[i], eps);
+            uint32_t nb[3];
+            xyk::hmc_batch_blocks(b->L[i], rows, kh, nb);
+            for (int g = 0; g < 3; ++g) {
+                hs[g * stride + i] = totals[g];
+                if ((uint64_t)totals[g] + nb[g] > 0x7fffffffull) {
+                    drop_hmc_graph(b);
+                    return XY_ESIZE;
                 }
-                load[0] += (double)b->L[i] * b->L[i];
+                totals[g] += nb[g];
             }
-            for (int g = 0; g < 3; ++g) hs[(size_t)g * (nf + 1) + nf] = totals[g];
         }
+        for (int g = 0; g < 3; ++g) hs[g * stride + b->n] = totals[g];
         if ((e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal)) != hipSuccess) {
             drop_hmc_graph(b);
             return xyr::hip_fail(e, "xy_batch_hmc: hipStreamBeginCapture");
         }
-        hipError_t le = hipEventRecord(b->ev_fork, b->cap);
-        for (int k = 1; k < kHmcStreams && le == hipSuccess; ++k) le = hipStreamWaitEvent(b->hs[k], b->ev_fork, 0);
-        if (le == hipSuccess && nf > 0)
-            le = xyk::launch_hmc_batch_trajectory(d_desc, d_start, nf, totals, eps, n_md, b->hmc_steps,
-                                                  &ctrl->sweep0, b->cap);
-        for (int i = 0; i < b->n && le == hipSuccess; ++i) {
-            if (isfast[i]) continue;
-            int k = 0;
-            for (int q = 1; q < kHmcStreams; ++q)
-                if (load[q] < load[k]) k = q;
-            load[k] += (double)b->L[i] * b->L[i];
-            hipStream_t sk = k == 0 ? b->cap : b->hs[k];
-            const LatDesc& d = b->desc[i];
-            float* st = (float*)(b->state + (size_t)d.off * eb);
-            float* pp = (float*)(b->work + b->lo.pp_off + (size_t)d.off * eb);
-            const xyk::HmcWork w = xyk::hmc_carve_compact(hw + off[i], b->L[i]);
-            le = xyk::launch_hmc_trajectory(st, pp, w, b->L[i], b->beta[i], eps, n_md, b->hmc_steps, 0u, d.key0,
-                                            d.key1, stage + i, sk, &ctrl->sweep0);
-        }
-        for (int k = 1; k < kHmcStreams && le == hipSuccess; ++k) {
-            le = hipEventRecord(b->hev[k], b->hs[k]);
-            if (le == hipSuccess) le = hipStreamWaitEvent(b->cap, b->hev[k], 0);
-        }
+        hipError_t le = xyk::launch_hmc_batch_trajectory(d_desc, d_start, b->n, totals, eps, n_md, b->hmc_steps, rows,
+                                                         &ctrl->sweep0, b->cap);
         if (le == hipSuccess) {
             hipLaunchKernelGGL(k_bhmc_finish, dim3(1), dim3(kNT), 0, b->cap, (const xy_hmc_obs*)stage, obs_dev, b->n,
                                (int)n_traj, ctrl);

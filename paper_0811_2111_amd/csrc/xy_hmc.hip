@@ -19,7 +19,10 @@
 // are updated in place.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "xy_device.hpp"
+#include "xy_hmc_pass.hpp"
 #include "xy_hmc_site.hpp"
 #include "xy_launch.hpp"
 #include "xy_reduce.hpp"
@@ -32,8 +35,6 @@ namespace xyk {
 namespace {
 
 constexpr int kThreads = 256;
-
-__device__ __forceinline__ int wrapi(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
 // The angle of entry (c, y, k) and the (cos, sin) of it and of its four
 // neighbours in the other plane.
@@ -99,10 +100,9 @@ __device__ __forceinline__ unsigned xcd_band(unsigned b, unsigned nb)
 // Momenta, saved angles and the partial records of H_old.
 __global__ void __launch_bounds__(kThreads)
 k_hmc_begin(const float* __restrict__ st, float* __restrict__ p, float* __restrict__ saved, int L, uint32_t traj,
-            const uint32_t* __restrict__ traj_dev, uint32_t k0, uint32_t k1, int cols, int rb,
-            double* __restrict__ rec)
+            uint32_t k0, uint32_t k1, int cols, int rb, unsigned* __restrict__ flag, double* __restrict__ rec)
 {
-    if (traj_dev) traj = *traj_dev;
+    if (blockIdx.x == 0 && threadIdx.x == 0) flag[1] = 0u;
     const int Hh = L >> 1, P = (Hh + 1) >> 1;
     const unsigned t = xcd_band(blockIdx.x, gridDim.x);
     const int col = (int)(t % (unsigned)cols);
@@ -211,218 +211,40 @@ k_hmc_step2(const float* __restrict__ src, float* __restrict__ dst, float* __res
 
 constexpr int kStepRows = 4;               // rows per thread of k_hmc_step2
 
-// K leap-frog steps per pass (temporal blocking), for L % 32 == 0.  A workgroup
-// owns a 32 x 32 tile of sites (natural coordinates) and loads the angles and
-// momenta of the tile grown by K sites on every side (both colours) into
-// registers (ceil((32 + 2K)^2 / 256) sites per thread); step q updates the sites
-// more than q sites from the edge of the grown tile, whose neighbours are then all
-// up to date, so after K steps the tile itself is exact and is written to dst / pdst
-// (the momenta ping-pong too: other tiles read this tile's old momenta as
-// their halo).  (cos, sin) of the angles live in two LDS buffers (read one,
-// write the other, one barrier per step).  Every site is updated with exactly
-// the arithmetic of k_hmc_step (neighbour sums (left + right) + (up + down),
-// the same fma), so the trajectory is bit for bit the one-step-per-launch one.
-// kick0: the first step's kick (-beta eps/2 on a trajectory's first step),
-// kick: the others'.  Grid (L/32)^2 workgroups, XCD bands of tile rows.
-constexpr int kMultiTile = 32;
-
-template <int K>
-__global__ void __launch_bounds__(kThreads)
-k_hmc_multi(const float* __restrict__ src, float* __restrict__ dst, const float* __restrict__ psrc,
-            float* __restrict__ pdst, int L, float kick0, float kick, float drift)
-{
-    constexpr int T = kMultiTile, E = T + 2 * K, NE = E * E, M = (NE + kThreads - 1) / kThreads;
-    __shared__ float2 cs[2][NE];
-    const int Hh = L >> 1, nt = L / T;
-    const int b = (int)xcd_band(blockIdx.x, gridDim.x);
-    const int ty = b / nt, tx = b - ty * nt;
-    const int x0 = tx * T - K, y0 = ty * T - K;
-    float th[M], pm[M];
-    unsigned off[M];
-    int dep[M];       // distance of the slot's site from the grown tile's edge (-1: no site)
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const int i = threadIdx.x + m * kThreads;
-        dep[m] = -1;
-        if (i < NE) {
-            const int ye = i / E, xe = i - ye * E;
-            dep[m] = min(min(xe, E - 1 - xe), min(ye, E - 1 - ye));
-            const int x = wrapi(x0 + xe, L), y = wrapi(y0 + ye, L);
-            off[m] = (unsigned)((((x + y) & 1) * L + y) * Hh + (x >> 1));
-            th[m] = src[off[m]];
-            pm[m] = psrc[off[m]];
-        }
-    }
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const int i = threadIdx.x + m * kThreads;
-        if (i < NE) {
-            float sn, cn;
-            sincos_turn(th[m], sn, cn);
-            cs[0][i] = make_float2(cn, sn);
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-        const float2* cur = cs[q & 1];
-        float2* nxt = cs[(q + 1) & 1];
-        const float kq = q == 0 ? kick0 : kick;
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const int i = threadIdx.x + m * kThreads;
-            if (dep[m] > q) {
-                const float2 own = cur[i], l = cur[i - 1], r = cur[i + 1], u = cur[i - E], d = cur[i + E];
-                Nb n;
-                n.c = own.x; n.s = own.y;
-                n.cl = l.x; n.sl = l.y; n.cr = r.x; n.sr = r.y;
-                n.cu = u.x; n.su = u.y; n.cd = d.x; n.sd = d.y;
-                pm[m] = __fmaf_rn(kq, sin_sum(n), pm[m]);
-                th[m] = __builtin_amdgcn_fractf(__fmaf_rn(drift, pm[m], th[m]));
-                if (q + 1 < K) {
-                    float sn, cn;
-                    sincos_turn(th[m], sn, cn);
-                    nxt[i] = make_float2(cn, sn);
-                }
-            }
-        }
-        if (q + 1 < K) __syncthreads();
-    }
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        if (dep[m] >= K) {           // the tile itself
-            dst[off[m]] = th[m];
-            pdst[off[m]] = pm[m];
-        }
-    }
-}
-
-// The same pass on larger tiles: T x T sites grown by K, NT threads, and with
-// SINGLE one LDS buffer of (cos, sin) (every update of a step reads its
-// neighbours, barrier, the new values are written, barrier), which halves the LDS
-// so that 64 x 64 tiles keep two workgroups of 1024 threads on a CU.  The grown
-// tile is 1.27 times the tile at T = 64, K = 4 (1.56 at T = 32), so less of the
-// work goes to the halo.  Per site the arithmetic is that of k_hmc_step.
-// The pass on tile b (after the XCD remap) of one lattice; cs: the LDS buffer(s),
-// (SINGLE ? 1 : 2) (T + 2K)^2 float2.
-template <int K, int T, int NT, bool SINGLE>
-__device__ __forceinline__ void multi_g_body(const float* __restrict__ src, float* __restrict__ dst,
-                                             const float* __restrict__ psrc, float* __restrict__ pdst, int L,
-                                             float kick0, float kick, float drift, int b, float2* cs)
-{
-    constexpr int E = T + 2 * K, NE = E * E, M = (NE + NT - 1) / NT;
-    const int Hh = L >> 1, nt = L / T;
-    const int ty = b / nt, tx = b - ty * nt;
-    const int x0 = tx * T - K, y0 = ty * T - K;
-    float th[M], pm[M];
-    unsigned off[M];
-    int dep[M];       // distance of the slot's site from the grown tile's edge (-1: no site)
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const int i = threadIdx.x + m * NT;
-        dep[m] = -1;
-        if (i < NE) {
-            const int ye = i / E, xe = i - ye * E;
-            dep[m] = min(min(xe, E - 1 - xe), min(ye, E - 1 - ye));
-            const int x = wrapi(x0 + xe, L), y = wrapi(y0 + ye, L);
-            off[m] = (unsigned)((((x + y) & 1) * L + y) * Hh + (x >> 1));
-            th[m] = src[off[m]];
-            pm[m] = psrc[off[m]];
-        }
-    }
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const int i = threadIdx.x + m * NT;
-        if (i < NE) {
-            float sn, cn;
-            sincos_turn(th[m], sn, cn);
-            cs[i] = make_float2(cn, sn);
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-        const float2* cur = cs + (SINGLE ? 0 : (q & 1)) * NE;
-        float2* nxt = cs + (SINGLE ? 0 : ((q + 1) & 1)) * NE;
-        const float kq = q == 0 ? kick0 : kick;
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const int i = threadIdx.x + m * NT;
-            if (dep[m] > q) {
-                const float2 own = cur[i], l = cur[i - 1], r = cur[i + 1], u = cur[i - E], d = cur[i + E];
-                Nb n;
-                n.c = own.x; n.s = own.y;
-                n.cl = l.x; n.sl = l.y; n.cr = r.x; n.sr = r.y;
-                n.cu = u.x; n.su = u.y; n.cd = d.x; n.sd = d.y;
-                pm[m] = __fmaf_rn(kq, sin_sum(n), pm[m]);
-                th[m] = __builtin_amdgcn_fractf(__fmaf_rn(drift, pm[m], th[m]));
-            }
-        }
-        if (q + 1 < K) {
-            if constexpr (SINGLE) __syncthreads();
-#pragma unroll
-            for (int m = 0; m < M; ++m) {
-                const int i = threadIdx.x + m * NT;
-                if (dep[m] > q) {
-                    float sn, cn;
-                    sincos_turn(th[m], sn, cn);
-                    nxt[i] = make_float2(cn, sn);
-                }
-            }
-            __syncthreads();
-        }
-    }
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        if (dep[m] >= K) {           // the tile itself
-            dst[off[m]] = th[m];
-            pdst[off[m]] = pm[m];
-        }
-    }
-}
-
-template <int K, int T, int NT, bool SINGLE>
-__global__ void __launch_bounds__(NT)
-k_hmc_multi_g(const float* __restrict__ src, float* __restrict__ dst, const float* __restrict__ psrc,
-              float* __restrict__ pdst, int L, float kick0, float kick, float drift)
-{
-    constexpr int NE = (T + 2 * K) * (T + 2 * K);
-    __shared__ float2 cs[(SINGLE ? 1 : 2) * NE];
-    multi_g_body<K, T, NT, SINGLE>(src, dst, psrc, pdst, L, kick0, kick, drift,
-                                   (int)xcd_band(blockIdx.x, gridDim.x), cs);
-}
-
+// Several leap-frog steps per pass (xy_hmc_pass.hpp) for any even L: 512 threads,
+// eight rows a thread (64 x 128 sites a region; 104 VGPRs, two workgroups a CU), or
+// four while those regions are about one a CU, when a pass is as long as one wave's
+// work (L = 512, 145 regions: 7.6 us against 11.5; L = 1024, 570 regions: 13.9
+// against 11.5).
+// A pass of 7 steps, eight rows: L = 4096 90 us, L = 8192 325 us (64 x 64 tiles with
+// (cos, sin) in LDS: 134 and 503); four rows: L = 256 6.4 us (12.4).  Other shapes at
+// L = 4096, 7 steps: 12 waves of six rows 95 us, 16 of four 97, 16 of eight 117 (one
+// workgroup a CU).
 constexpr int kMaxStepsPerPass = 8;
+constexpr int kPassWaves = 8;
+constexpr int kPassFewRegions = 320;    // four rows a thread up to this many regions
 
-constexpr int kWideTile = 64, kWideThreads = 1024;
-
-// L % 64 == 0: 64 x 64 tiles, 1024 threads, one LDS buffer; else 32 x 32 tiles.
-template <int K>
-static void launch_multi(unsigned nb, hipStream_t s, const float* src, float* dst, const float* psrc, float* pdst,
-                         int L, float kick0, float kick, float drift)
+template <int R>
+__global__ void __launch_bounds__(kPassWaves * 64)
+k_hmc_pass(const float* __restrict__ src, float* __restrict__ dst, const float* __restrict__ psrc,
+           float* __restrict__ pdst, int L, int K, float kick0, float kick, float drift)
 {
-    if (L % kWideTile == 0) {
-        const unsigned nbw = (unsigned)((L / kWideTile) * (L / kWideTile));
-        hipLaunchKernelGGL((k_hmc_multi_g<K, kWideTile, kWideThreads, true>), dim3(nbw), dim3(kWideThreads), 0, s, src,
-                           dst, psrc, pdst, L, kick0, kick, drift);
-        return;
-    }
-    hipLaunchKernelGGL(k_hmc_multi<K>, dim3(nb), dim3(kThreads), 0, s, src, dst, psrc, pdst, L, kick0, kick, drift);
+    __shared__ float4 lds[2 * kPassWaves * 2 * 64];
+    const int b = (int)xcd_band(blockIdx.x, gridDim.x);       // a grid of a multiple of 8
+    if (b >= pass_tiles<kPassWaves, R>(L, K)) return;
+    pass_body<kPassWaves, R>(src, dst, psrc, pdst, L, K, K, kick0, kick, drift, b, lds);
 }
 
-static void launch_multi_k(int k, unsigned nb, hipStream_t s, const float* src, float* dst, const float* psrc,
-                           float* pdst, int L, float kick0, float kick, float drift)
+static void launch_pass(hipStream_t s, const float* src, float* dst, const float* psrc, float* pdst, int L, int k,
+                        float kick0, float kick, float drift)
 {
-    switch (k) {
-    case 1: launch_multi<1>(nb, s, src, dst, psrc, pdst, L, kick0, kick, drift); break;
-    case 2: launch_multi<2>(nb, s, src, dst, psrc, pdst, L, kick0, kick, drift); break;
-    case 3: launch_multi<3>(nb, s, src, dst, psrc, pdst, L, kick0, kick, drift); break;
-    case 4: launch_multi<4>(nb, s, src, dst, psrc, pdst, L, kick0, kick, drift); break;
-    case 5: launch_multi<5>(nb, s, src, dst, psrc, pdst, L, kick0, kick, drift); break;
-    case 6: launch_multi<6>(nb, s, src, dst, psrc, pdst, L, kick0, kick, drift); break;
-    case 7: launch_multi<7>(nb, s, src, dst, psrc, pdst, L, kick0, kick, drift); break;
-    default: launch_multi<8>(nb, s, src, dst, psrc, pdst, L, kick0, kick, drift); break;
-    }
+    const bool tall = pass_tiles<kPassWaves, 4>(L, k) > kPassFewRegions;
+    const int nt = tall ? pass_tiles<kPassWaves, 8>(L, k) : pass_tiles<kPassWaves, 4>(L, k);
+    const dim3 grid((unsigned)((nt + 7) & ~7)), block(kPassWaves * 64);
+    if (tall)
+        hipLaunchKernelGGL(k_hmc_pass<8>, grid, block, 0, s, src, dst, psrc, pdst, L, k, kick0, kick, drift);
+    else
+        hipLaunchKernelGGL(k_hmc_pass<4>, grid, block, 0, s, src, dst, psrc, pdst, L, k, kick0, kick, drift);
 }
 
 // Final half kick and the partial records of H_new; `copy` != NULL receives the
@@ -573,10 +395,10 @@ __device__ __forceinline__ void ends2_body(const float* __restrict__ st, float* 
 template <bool BEGIN>
 __global__ void __launch_bounds__(kThreads)
 k_hmc_ends2(const float* __restrict__ st, float* __restrict__ p, float* __restrict__ copy, int L, uint32_t traj,
-            const uint32_t* __restrict__ traj_dev, uint32_t k0, uint32_t k1, float nbeta_kick, int cols, int rb,
+            uint32_t k0, uint32_t k1, float nbeta_kick, int cols, int rb, unsigned* __restrict__ flag,
             double* __restrict__ rec)
 {
-    if (BEGIN && traj_dev) traj = *traj_dev;
+    if (BEGIN && blockIdx.x == 0 && threadIdx.x == 0) flag[1] = 0u;
     ends2_body<BEGIN>(st, p, copy, L, traj, k0, k1, nbeta_kick, cols, rb, rec, xcd_band(blockIdx.x, gridDim.x));
 }
 
@@ -600,18 +422,41 @@ __device__ void sum_records(const double* __restrict__ rec, int nrec, double out
     __syncthreads();
 }
 
-// Metropolis step of the trajectory: one workgroup, on the chunk sums of the two
-// record sets.
+// Metropolis step of the trajectory.  Workgroup b sums chunk b % nchunk (256
+// records) of the old records, or of the new ones from nchunk on; the one that
+// arrives last (a counter behind the flag, zeroed by the begin kernel; released and
+// acquired at device scope) sums the chunk results in their order and decides.
+// Three launches of 2.8 us each otherwise.
 __global__ void __launch_bounds__(kThreads)
-k_hmc_decide(const double* __restrict__ rec_old, const double* __restrict__ rec_new, int nrec, double beta,
-             uint32_t traj, const uint32_t* __restrict__ traj_dev, uint32_t k0, uint32_t k1,
-             unsigned* __restrict__ flag, xy_hmc_obs* __restrict__ obs)
+k_hmc_decide(const double* __restrict__ rec_old, const double* __restrict__ rec_new, int nrec, int nchunk,
+             double* __restrict__ chunk_old, double* __restrict__ chunk_new, double beta, uint32_t traj, uint32_t k0,
+             uint32_t k1, unsigned* __restrict__ flag, xy_hmc_obs* __restrict__ obs)
 {
-    if (traj_dev) traj = *traj_dev;
     __shared__ double red[4 * 7];
+    __shared__ int last;
+    const bool fresh = (int)blockIdx.x >= nchunk;
+    const int ch = (int)blockIdx.x - (fresh ? nchunk : 0), i = ch * 256 + (int)threadIdx.x;
+    double v[7] = {0, 0, 0, 0, 0, 0, 0};
+    if (i < nrec) {
+        const double* q = (fresh ? rec_new : rec_old) + (size_t)i * 8;
+#pragma unroll
+        for (int k = 0; k < 7; ++k) v[k] = q[k];
+    }
+    block_sum7_256(v, red);
+    if (threadIdx.x == 0) {
+        double* o = (fresh ? chunk_new : chunk_old) + (size_t)ch * 8;
+#pragma unroll
+        for (int k = 0; k < 7; ++k) o[k] = v[k];
+        o[7] = 0.0;
+        __threadfence();
+        last = atomicAdd(flag + 1, 1u) == gridDim.x - 1u;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
     double o[7], n[7];
-    sum_records(rec_old, nrec, o, red);
-    sum_records(rec_new, nrec, n, red);
+    sum_records(chunk_old, nchunk, o, red);
+    sum_records(chunk_new, nchunk, n, red);
     if (threadIdx.x == 0) decide_core(o, n, beta, traj, k0, k1, flag, obs);
 }
 
@@ -666,24 +511,22 @@ k_bhmc_ends(const BhLat* __restrict__ d, const uint32_t* __restrict__ start, int
                           q.k1, q.kick_half, q.cols, q.rb, q.w.rec_new, t);
 }
 
-// K leap-frog steps of every lattice on 64 x 64 tiles; parity odd: the angles and
-// momenta are read from the second buffers and written to the first.
-template <int K>
-__global__ void __launch_bounds__(kWideThreads)
-k_bhmc_multi(const BhLat* __restrict__ d, const uint32_t* __restrict__ start, int n, int parity, int first,
-             float drift)
+// K leap-frog steps of every lattice, on regions cut for passes of KH; parity odd:
+// the angles and momenta are read from the second buffers and written to the first.
+template <int R>
+__global__ void __launch_bounds__(kPassWaves * 64)
+k_bhmc_pass(const BhLat* __restrict__ d, const uint32_t* __restrict__ start, int n, int KH, int K, int parity,
+            int first, float drift)
 {
-    constexpr int NE = (kWideTile + 2 * K) * (kWideTile + 2 * K);
-    __shared__ float2 cs[NE];
+    __shared__ float4 lds[2 * kPassWaves * 2 * 64];
     const int i = bh_find(start, n, blockIdx.x);
     const BhLat& q = d[i];
-    const int nt = q.L / kWideTile;
-    const unsigned nb = (unsigned)(nt * nt), lb = blockIdx.x - start[i];
-    if (lb >= nb) return;
-    multi_g_body<K, kWideTile, kWideThreads, true>(parity ? q.pp : q.st, parity ? q.st : q.pp,
-                                                   parity ? q.w.p2 : q.w.p, parity ? q.w.p : q.w.p2, q.L,
-                                                   first ? q.kick_half : q.kick_full, q.kick_full, drift,
-                                                   (int)xcd_band(lb, nb), cs);
+    const unsigned lb = blockIdx.x - start[i];
+    const int b = (int)xcd_band(lb, start[i + 1] - start[i]);
+    if (b >= pass_tiles<kPassWaves, R>(q.L, KH)) return;
+    pass_body<kPassWaves, R>(parity ? q.pp : q.st, parity ? q.st : q.pp, parity ? q.w.p2 : q.w.p,
+                             parity ? q.w.p : q.w.p2, q.L, KH, K, first ? q.kick_half : q.kick_full, q.kick_full,
+                             drift, b, lds);
 }
 
 // One lattice's records summed as the single-lattice trajectory sums them: chunks
@@ -737,28 +580,6 @@ k_bhmc_restore(const BhLat* __restrict__ d, const uint32_t* __restrict__ start, 
         q.st[j] = q.w.saved[j];
 }
 
-template <int K>
-static void launch_bmulti(uint32_t nb, hipStream_t s, const BhLat* d, const uint32_t* start, int n, int parity,
-                          int first, float drift)
-{
-    hipLaunchKernelGGL(k_bhmc_multi<K>, dim3(nb), dim3(kWideThreads), 0, s, d, start, n, parity, first, drift);
-}
-
-static void launch_bmulti_k(int k, uint32_t nb, hipStream_t s, const BhLat* d, const uint32_t* start, int n,
-                            int parity, int first, float drift)
-{
-    switch (k) {
-    case 1: launch_bmulti<1>(nb, s, d, start, n, parity, first, drift); break;
-    case 2: launch_bmulti<2>(nb, s, d, start, n, parity, first, drift); break;
-    case 3: launch_bmulti<3>(nb, s, d, start, n, parity, first, drift); break;
-    case 4: launch_bmulti<4>(nb, s, d, start, n, parity, first, drift); break;
-    case 5: launch_bmulti<5>(nb, s, d, start, n, parity, first, drift); break;
-    case 6: launch_bmulti<6>(nb, s, d, start, n, parity, first, drift); break;
-    case 7: launch_bmulti<7>(nb, s, d, start, n, parity, first, drift); break;
-    default: launch_bmulti<8>(nb, s, d, start, n, parity, first, drift); break;
-    }
-}
-
 }  // namespace
 
 // Block columns (both colours) and row blocks of the record-writing kernels: as
@@ -779,12 +600,14 @@ static int hmc_cols2(int L) { return ((L >> 2) + kThreads - 1) / kThreads; }
 // cosines, so short runs cost traffic and arithmetic.  Lattices of more than one
 // column block (L > 1024): runs of up to 32 rows, but at least about 2048
 // workgroups while L allows, and at most one record per wave within the record
-// buffer.  One column block (L <= 1024, where batches of many lattices supply
-// the parallelism): runs of 8 rows.
+// buffer.  One column block (L <= 1024): runs of 8 rows where batches of many
+// lattices supply the parallelism (runs of 4 cost the 96-lattice scan 1.8%), of 4 or
+// 2 where a lattice is a few workgroups whose runs are one long chain (L = 256: 35 us
+// a trajectory of 20 steps against 47).
 static int hmc_runs2(int L)
 {
     const int cols = hmc_cols2(L);
-    if (cols == 1) return (L + 7) / 8;
+    if (cols == 1) return L <= 256 ? L / 2 : L <= 512 ? (L + 3) / 4 : (L + 7) / 8;
     int gy = (2048 + cols - 1) / cols;
     if (gy < L / 32) gy = L / 32;
     const int cap = kHmcMaxRecords / (cols * (kThreads / 64));
@@ -866,11 +689,9 @@ HmcWork hmc_carve_compact(void* work, int L)
     return w;
 }
 
-bool hmc_multi_supported(int L) { return L >= kMultiTile && L % kMultiTile == 0; }
-
 hipError_t launch_hmc_trajectory(float* state, float* pingpong, const HmcWork& w, int L, double beta, double eps,
                                  int n_md, int steps_per_pass, uint32_t traj, uint32_t k0, uint32_t k1,
-                                 xy_hmc_obs* obs, hipStream_t s, const uint32_t* traj_dev)
+                                 xy_hmc_obs* obs, hipStream_t s)
 {
     const bool pairs2 = hmc_pairs(L);
     const int cols = pairs2 ? hmc_cols2(L) : hmc_cols(L), rb = pairs2 ? hmc_runs2(L) : hmc_row_blocks(L);
@@ -880,23 +701,22 @@ hipError_t launch_hmc_trajectory(float* state, float* pingpong, const HmcWork& w
     const int nchunk = (nrec + 255) / 256;
     const float drift = (float)(eps / (2.0 * 3.14159265358979323846));
     if (pairs2)
-        hipLaunchKernelGGL(k_hmc_ends2<true>, grec, block, 0, s, state, w.p, w.saved, L, traj, traj_dev, k0, k1, 0.0f,
-                           cols, rb, w.rec_old);
+        hipLaunchKernelGGL(k_hmc_ends2<true>, grec, block, 0, s, state, w.p, w.saved, L, traj, k0, k1, 0.0f, cols, rb,
+                           w.flag, w.rec_old);
     else
-        hipLaunchKernelGGL(k_hmc_begin, grec, block, 0, s, state, w.p, w.saved, L, traj, traj_dev, k0, k1, cols, rb,
+        hipLaunchKernelGGL(k_hmc_begin, grec, block, 0, s, state, w.p, w.saved, L, traj, k0, k1, cols, rb, w.flag,
                            w.rec_old);
     float* src = state;
     float* dst = pingpong;
     float* p = w.p;
     const float kick_half = (float)(-beta * 0.5 * eps), kick_full = (float)(-beta * eps);
-    if (steps_per_pass > 1 && hmc_multi_supported(L)) {
+    if (steps_per_pass > 1) {
         // passes of up to steps_per_pass steps; the momenta ping-pong between p and p2
         float* pn = w.p2;
-        const unsigned nb = (unsigned)((L / kMultiTile) * (L / kMultiTile));
         const int kmax = steps_per_pass < kMaxStepsPerPass ? steps_per_pass : kMaxStepsPerPass;
         for (int q = 0; q < n_md;) {
             const int k = n_md - q < kmax ? n_md - q : kmax;
-            launch_multi_k(k, nb, s, src, dst, p, pn, L, q == 0 ? kick_half : kick_full, kick_full, drift);
+            launch_pass(s, src, dst, p, pn, L, k, q == 0 ? kick_half : kick_full, kick_full, drift);
             float* t = src;
             src = dst;
             dst = t;
@@ -920,23 +740,18 @@ hipError_t launch_hmc_trajectory(float* state, float* pingpong, const HmcWork& w
         }
     }
     if (pairs2)
-        hipLaunchKernelGGL(k_hmc_ends2<false>, grec, block, 0, s, src, p, src == state ? nullptr : state, L, traj,
-                           traj_dev, k0, k1, kick_half, cols, rb, w.rec_new);
+        hipLaunchKernelGGL(k_hmc_ends2<false>, grec, block, 0, s, src, p, src == state ? nullptr : state, L, traj, k0,
+                           k1, kick_half, cols, rb, w.flag, w.rec_new);
     else
         hipLaunchKernelGGL(k_hmc_end, grec, block, 0, s, src, src == state ? nullptr : state, p, L, kick_half, cols,
                            rb, w.rec_new);
-    hipError_t e = launch_reduce_chunks(w.rec_old, nrec, w.chunk_old, s);
-    if (e == hipSuccess) e = launch_reduce_chunks(w.rec_new, nrec, w.chunk_new, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_hmc_decide, dim3(1), block, 0, s, w.chunk_old, w.chunk_new, nchunk, beta, traj, traj_dev,
-                       k0, k1, w.flag, obs);
+    hipLaunchKernelGGL(k_hmc_decide, dim3(2 * (unsigned)nchunk), block, 0, s, w.rec_old, w.rec_new, nrec, nchunk,
+                       w.chunk_old, w.chunk_new, beta, traj, k0, k1, w.flag, obs);
     const size_t n = (size_t)L * (size_t)L;
     const unsigned nb = (unsigned)((n + kThreads * 8 - 1) / (kThreads * 8));
     hipLaunchKernelGGL(k_hmc_restore, dim3(nb < 4096 ? nb : 4096), block, 0, s, w.flag, w.saved, state, n);
     return hipGetLastError();
 }
-
-bool hmc_batch_supported(int L) { return L >= kWideTile && L % kWideTile == 0; }
 
 void hmc_batch_describe(BhLat& d, int L, double beta, double eps)
 {
@@ -951,31 +766,46 @@ void hmc_batch_describe(BhLat& d, int L, double beta, double eps)
 
 static uint32_t pad8(uint32_t v) { return (v + 7u) & ~7u; }
 
-void hmc_batch_blocks(int L, uint32_t nb[3])
+int hmc_batch_steps(int n_md, int steps_per_pass)
+{
+    return std::min(n_md, std::min(steps_per_pass, kMaxStepsPerPass));
+}
+
+int hmc_batch_rows(int n, const int32_t* L, int kh)
+{
+    long long tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += pass_tiles<kPassWaves, 4>(L[i], kh);
+    return tiles > kPassFewRegions ? 8 : 4;
+}
+
+void hmc_batch_blocks(int L, int rows, int kh, uint32_t nb[3])
 {
     nb[0] = pad8((uint32_t)(hmc_cols2(L) * hmc_row_blocks2(L)));
-    nb[1] = pad8((uint32_t)((L / kWideTile) * (L / kWideTile)));
+    nb[1] = pad8((uint32_t)(rows == 8 ? pass_tiles<kPassWaves, 8>(L, kh) : pass_tiles<kPassWaves, 4>(L, kh)));
     const size_t n = (size_t)L * (size_t)L;
     const size_t r = (n + kThreads * 8 - 1) / (kThreads * 8);
     nb[2] = pad8((uint32_t)(r < 4096 ? r : 4096));
 }
 
 hipError_t launch_hmc_batch_trajectory(const BhLat* d, const uint32_t* start, int n, const uint32_t totals[3],
-                                       double eps, int n_md, int steps_per_pass, const uint32_t* traj_dev,
+                                       double eps, int n_md, int steps_per_pass, int rows, const uint32_t* traj_dev,
                                        hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
     const uint32_t* s_ends = start;
     const uint32_t* s_pass = start + (n + 1);
     const uint32_t* s_rest = start + 2 * (n + 1);
     const float drift = (float)(eps / (2.0 * 3.14159265358979323846));
     const dim3 block(kThreads);
     hipLaunchKernelGGL(k_bhmc_ends<true>, dim3(totals[0]), block, 0, s, d, s_ends, n, traj_dev, 0);
-    const int kmax = steps_per_pass < kMaxStepsPerPass ? steps_per_pass : kMaxStepsPerPass;
+    const int kh = hmc_batch_steps(n_md, steps_per_pass);
+    const dim3 bpass(kPassWaves * 64);
     int parity = 0;
     for (int q = 0; q < n_md;) {
-        const int k = n_md - q < kmax ? n_md - q : kmax;
-        launch_bmulti_k(k, totals[1], s, d, s_pass, n, parity, q == 0, drift);
+        const int k = n_md - q < kh ? n_md - q : kh;
+        if (rows == 8)
+            hipLaunchKernelGGL(k_bhmc_pass<8>, dim3(totals[1]), bpass, 0, s, d, s_pass, n, kh, k, parity, q == 0, drift);
+        else
+            hipLaunchKernelGGL(k_bhmc_pass<4>, dim3(totals[1]), bpass, 0, s, d, s_pass, n, kh, k, parity, q == 0, drift);
         parity ^= 1;
         q += k;
     }

@@ -582,7 +582,7 @@ int xy_hmc_set_steps_per_pass(xy_lattice* h, int32_t steps)
 int xy_hmc_get_steps_per_pass(const xy_lattice* h, int32_t* steps)
 {
     if (!live(h) || !steps) return XY_ESTATE;
-    *steps = xyk::hmc_multi_supported(h->L) ? h->hmc_steps : 1;
+    *steps = h->L % 32 == 0 ? h->hmc_steps : 1;
     return XY_OK;
 }
 

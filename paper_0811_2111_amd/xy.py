@@ -305,7 +305,7 @@ class Lattice:
 
     @property
     def hmc_steps_per_pass(self) -> int:
-        """Leap-frog steps per pass that xy_hmc runs (1 if L % 32 != 0)."""
+        """The leap-frog steps per pass that are set (reported as 1 if L % 32 != 0)."""
         v = ctypes.c_int32()
         check(_lib.xy_hmc_get_steps_per_pass(self.h, ctypes.byref(v)), "xy_hmc_get_steps_per_pass")
         return v.value
