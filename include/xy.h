@@ -314,9 +314,8 @@ int xy_hmc_set_steps_per_pass(xy_lattice* h, int32_t steps);
 int xy_hmc_get_steps_per_pass(const xy_lattice* h, int32_t* steps);
 
 /* Hybrid Monte Carlo on the four-replica texel (sections 1.2 and 3.2): the four
- * replicas of a quad run their trajectories together (each pass over the
- * float4 state advances all four by the same leap-frog steps; see
- * xy_quad_hmc_set_steps_per_pass), and the Metropolis step is a vector of four
+ * replicas of a quad run their trajectories together (split into four lattices
+ * for the duration of the call, each stage one launch for all four), and the Metropolis step is a vector of four
  * decisions z_r, each from the replica's own FP64 dH; replica r keeps
  * z_r theta_new + (1 - z_r) theta_old.  Replica r follows bit for bit the
  * trajectory that xy_hmc gives a single lattice with (seed_r, L, beta_r) and the
@@ -332,10 +331,8 @@ int xy_quad_hmc_work_bytes(int32_t L, size_t* bytes);
 int xy_quad_hmc(xy_quad* q, int64_t n_traj, int32_t n_md, double eps, void* hmc_work, size_t hmc_len,
                 xy_hmc_obs* obs_dev);
 /* Leap-frog steps per pass of xy_quad_hmc (1 .. 4, default 4; XY_EINVAL
- * otherwise): with more than one, a workgroup loads a 32 x 32 tile grown by that
- * many sites on every side, runs the steps on it and writes the tile back, as
- * xy_hmc_set_steps_per_pass does for a lattice; 1: one step per pass over the
- * state.  The trajectory is bit for bit the same. */
+ * otherwise), as xy_hmc_set_steps_per_pass; 4 stands for that call's default, 7.
+ * The trajectory is bit for bit the same. */
 int xy_quad_hmc_set_steps_per_pass(xy_quad* q, int32_t steps);
 int xy_quad_hmc_get_steps_per_pass(const xy_quad* q, int32_t* steps);
 

@@ -427,10 +427,10 @@ __device__ void sum_records(const double* __restrict__ rec, int nrec, double out
 // arrives last (a counter behind the flag, zeroed by the begin kernel; released and
 // acquired at device scope) sums the chunk results in their order and decides.
 // Three launches of 2.8 us each otherwise.
-__global__ void __launch_bounds__(kThreads)
-k_hmc_decide(const double* __restrict__ rec_old, const double* __restrict__ rec_new, int nrec, int nchunk,
-             double* __restrict__ chunk_old, double* __restrict__ chunk_new, double beta, uint32_t traj, uint32_t k0,
-             uint32_t k1, unsigned* __restrict__ flag, xy_hmc_obs* __restrict__ obs)
+__device__ __forceinline__ void decide_body(const double* __restrict__ rec_old, const double* __restrict__ rec_new,
+                                            int nrec, int nchunk, double* __restrict__ chunk_old,
+                                            double* __restrict__ chunk_new, double beta, uint32_t traj, uint32_t k0,
+                                            uint32_t k1, unsigned* __restrict__ flag, xy_hmc_obs* __restrict__ obs)
 {
     __shared__ double red[4 * 7];
     __shared__ int last;
@@ -460,6 +460,14 @@ k_hmc_decide(const double* __restrict__ rec_old, const double* __restrict__ rec_
     if (threadIdx.x == 0) decide_core(o, n, beta, traj, k0, k1, flag, obs);
 }
 
+__global__ void __launch_bounds__(kThreads)
+k_hmc_decide(const double* __restrict__ rec_old, const double* __restrict__ rec_new, int nrec, int nchunk,
+             double* __restrict__ chunk_old, double* __restrict__ chunk_new, double beta, uint32_t traj, uint32_t k0,
+             uint32_t k1, unsigned* __restrict__ flag, xy_hmc_obs* __restrict__ obs)
+{
+    decide_body(rec_old, rec_new, nrec, nchunk, chunk_old, chunk_new, beta, traj, k0, k1, flag, obs);
+}
+
 // Rejected trajectory: the saved angles back into the state.
 __global__ void __launch_bounds__(kThreads)
 k_hmc_restore(const unsigned* __restrict__ flag, const float* __restrict__ saved, float* __restrict__ st, size_t n)
@@ -467,6 +475,77 @@ k_hmc_restore(const unsigned* __restrict__ flag, const float* __restrict__ saved
     if (*flag) return;
     for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kThreads)
         st[i] = saved[i];
+}
+
+// ----------------------------------------------------- four replicas of a quad
+// The four lattices of a quad back to back (n floats each), taken by blockIdx.y:
+// each stage is one launch of the single-lattice pass on all four.  Replica r's
+// flag and arrival counter are flag[16 r], flag[16 r + 1].
+__global__ void __launch_bounds__(kThreads)
+k_quad_split(const float4* __restrict__ st, float* __restrict__ planes, size_t n)
+{
+    const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i >= n) return;
+    const float4 v = st[i];
+    planes[i] = v.x;
+    planes[n + i] = v.y;
+    planes[2 * n + i] = v.z;
+    planes[3 * n + i] = v.w;
+}
+
+__global__ void __launch_bounds__(kThreads)
+k_quad_join(const float* __restrict__ planes, float4* __restrict__ st, size_t n)
+{
+    const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i < n) st[i] = make_float4(planes[i], planes[n + i], planes[2 * n + i], planes[3 * n + i]);
+}
+
+template <bool BEGIN>
+__global__ void __launch_bounds__(kThreads)
+k_qhmc_ends(const float* __restrict__ st, float* __restrict__ p, float* __restrict__ copy, int L, uint32_t traj,
+            QHmcKeys keys, float4 kick, int cols, int runs, unsigned* __restrict__ flag, double* __restrict__ rec,
+            int nrec)
+{
+    const int r = (int)blockIdx.y;
+    const size_t o = (size_t)r * L * L;
+    if (BEGIN && blockIdx.x == 0 && threadIdx.x == 0) flag[16 * r + 1] = 0u;
+    ends2_body<BEGIN>(st + o, p + o, copy ? copy + o : nullptr, L, traj, keys.k0[r], keys.k1[r],
+                      r == 0 ? kick.x : r == 1 ? kick.y : r == 2 ? kick.z : kick.w, cols, runs,
+                      rec + (size_t)r * nrec * 8, xcd_band(blockIdx.x, gridDim.x));
+}
+
+template <int R>
+__global__ void __launch_bounds__(kPassWaves * 64)
+k_qhmc_pass(const float* __restrict__ src, float* __restrict__ dst, const float* __restrict__ psrc,
+            float* __restrict__ pdst, int L, int K, float4 kick0, float4 kick, float drift)
+{
+    __shared__ float4 lds[2 * kPassWaves * 2 * 64];
+    const int b = (int)xcd_band(blockIdx.x, gridDim.x), r = (int)blockIdx.y;
+    if (b >= pass_tiles<kPassWaves, R>(L, K)) return;
+    const size_t o = (size_t)r * L * L;
+    const float ka = r == 0 ? kick0.x : r == 1 ? kick0.y : r == 2 ? kick0.z : kick0.w;
+    const float kb = r == 0 ? kick.x : r == 1 ? kick.y : r == 2 ? kick.z : kick.w;
+    pass_body<kPassWaves, R>(src + o, dst + o, psrc + o, pdst + o, L, K, K, ka, kb, drift, b, lds);
+}
+
+__global__ void __launch_bounds__(kThreads)
+k_qhmc_decide(const double* __restrict__ rec_old, const double* __restrict__ rec_new, int nrec, int nchunk,
+              double* __restrict__ chunk_old, double* __restrict__ chunk_new, QHmcBeta beta, uint32_t traj,
+              QHmcKeys keys, unsigned* __restrict__ flag, xy_hmc_obs* __restrict__ obs)
+{
+    const int r = (int)blockIdx.y;
+    const size_t o = (size_t)r * nrec * 8, c = (size_t)r * nchunk * 8;
+    decide_body(rec_old + o, rec_new + o, nrec, nchunk, chunk_old + c, chunk_new + c, beta.b[r], traj, keys.k0[r],
+                keys.k1[r], flag + 16 * r, obs ? obs + r : nullptr);
+}
+
+__global__ void __launch_bounds__(kThreads)
+k_qhmc_restore(const unsigned* __restrict__ flag, const float* __restrict__ saved, float* __restrict__ st, size_t n)
+{
+    const int r = (int)blockIdx.y;
+    if (flag[16 * r]) return;
+    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kThreads)
+        st[r * n + i] = saved[r * n + i];
 }
 
 // ---------------------------------------------------------------- batches
@@ -604,13 +683,13 @@ static int hmc_cols2(int L) { return ((L >> 2) + kThreads - 1) / kThreads; }
 // lattices supply the parallelism (runs of 4 cost the 96-lattice scan 1.8%), of 4 or
 // 2 where a lattice is a few workgroups whose runs are one long chain (L = 256: 35 us
 // a trajectory of 20 steps against 47).
-static int hmc_runs2(int L)
+static int hmc_runs2(int L, int max_records = kHmcMaxRecords)
 {
     const int cols = hmc_cols2(L);
     if (cols == 1) return L <= 256 ? L / 2 : L <= 512 ? (L + 3) / 4 : (L + 7) / 8;
     int gy = (2048 + cols - 1) / cols;
     if (gy < L / 32) gy = L / 32;
-    const int cap = kHmcMaxRecords / (cols * (kThreads / 64));
+    const int cap = max_records / (cols * (kThreads / 64));
     if (gy > cap) gy = cap;
     if (gy > L) gy = L;
     return gy < 1 ? 1 : gy;
@@ -812,6 +891,108 @@ hipError_t launch_hmc_batch_trajectory(const BhLat* d, const uint32_t* start, in
     hipLaunchKernelGGL(k_bhmc_ends<false>, dim3(totals[0]), block, 0, s, d, s_ends, n, traj_dev, parity);
     hipLaunchKernelGGL(k_bhmc_decide, dim3((unsigned)n), block, 0, s, d, traj_dev);
     hipLaunchKernelGGL(k_bhmc_restore, dim3(totals[2]), block, 0, s, d, s_rest, n);
+    return hipGetLastError();
+}
+
+// ----------------------------------------------------- four replicas of a quad
+// Partial records a quad's workspace holds per replica and H sum.
+int quad_hmc_records(int L)
+{
+    const int cols = 2 * (((L >> 1) + kThreads - 1) / kThreads), rb = 4096 / cols;
+    return cols * (rb < L ? (rb > 0 ? rb : 1) : L) * (kThreads / 64);
+}
+
+size_t quad_hmc_work_bytes(int L)
+{
+    const size_t st = ((size_t)L * L * sizeof(float4) + 255) & ~(size_t)255;
+    const size_t nrec = (size_t)quad_hmc_records(L), nch = (nrec + 255) / 256;
+    return 3 * st + 256 + 2 * 4 * (nrec + nch) * 8 * sizeof(double);
+}
+
+QuadHmcWork quad_hmc_carve(void* work, int L)
+{
+    const size_t st = ((size_t)L * L * sizeof(float4) + 255) & ~(size_t)255;
+    const size_t nrec = (size_t)quad_hmc_records(L), nch = (nrec + 255) / 256;
+    char* b = (char*)work;
+    QuadHmcWork w;
+    w.p = (float*)b;
+    b += st;
+    w.saved = (float*)b;
+    b += st;
+    w.p2 = (float*)b;
+    b += st;
+    w.flag = (unsigned*)b;
+    b += 256;
+    w.rec_old = (double*)b;
+    b += 4 * nrec * 8 * sizeof(double);
+    w.rec_new = (double*)b;
+    b += 4 * nrec * 8 * sizeof(double);
+    w.chunk_old = (double*)b;
+    b += 4 * nch * 8 * sizeof(double);
+    w.chunk_new = (double*)b;
+    return w;
+}
+
+hipError_t launch_quad_split(const float4* state, float* planes, int L, hipStream_t s)
+{
+    const size_t n = (size_t)L * L;
+    hipLaunchKernelGGL(k_quad_split, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, state,
+                       planes, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_quad_join(const float* planes, float4* state, int L, hipStream_t s)
+{
+    const size_t n = (size_t)L * L;
+    hipLaunchKernelGGL(k_quad_join, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, planes,
+                       state, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_quad_hmc_trajectory(float* planes, float* second, const QuadHmcWork& w, int L, const double beta[4],
+                                      double eps, int n_md, int steps_per_pass, uint32_t traj, const QHmcKeys& keys,
+                                      xy_hmc_obs* obs, hipStream_t s)
+{
+    const int cols = hmc_cols2(L), runs = hmc_runs2(L, quad_hmc_records(L));
+    const int G = ends_group(L), nbr = (runs + G - 1) / G;
+    const int nrec = cols * nbr * (kThreads / 64), nchunk = (nrec + 255) / 256;
+    const dim3 grec((unsigned)(cols * nbr), 4), block(kThreads), bpass(kPassWaves * 64);
+    // the single-lattice launcher's FP32 constants, per replica
+    const float drift = (float)(eps / (2.0 * 3.14159265358979323846));
+    float kh[4], kf[4];
+    QHmcBeta qb;
+    for (int r = 0; r < 4; ++r) {
+        kh[r] = (float)(-beta[r] * 0.5 * eps);
+        kf[r] = (float)(-beta[r] * eps);
+        qb.b[r] = beta[r];
+    }
+    const float4 kick_half = make_float4(kh[0], kh[1], kh[2], kh[3]);
+    const float4 kick_full = make_float4(kf[0], kf[1], kf[2], kf[3]);
+    hipLaunchKernelGGL(k_qhmc_ends<true>, grec, block, 0, s, planes, w.p, w.saved, L, traj, keys, kick_half, cols, runs,
+                       w.flag, w.rec_old, nrec);
+    float *src = planes, *dst = second, *p = w.p, *pn = w.p2;
+    const int kmax = std::min(steps_per_pass, kMaxStepsPerPass);
+    for (int q = 0; q < n_md;) {
+        const int k = std::min(n_md - q, kmax);
+        const bool tall = 4 * pass_tiles<kPassWaves, 4>(L, k) > kPassFewRegions;
+        const int nt = tall ? pass_tiles<kPassWaves, 8>(L, k) : pass_tiles<kPassWaves, 4>(L, k);
+        const dim3 grid((unsigned)((nt + 7) & ~7), 4);
+        const float4 k0 = q == 0 ? kick_half : kick_full;
+        if (tall)
+            hipLaunchKernelGGL(k_qhmc_pass<8>, grid, bpass, 0, s, src, dst, p, pn, L, k, k0, kick_full, drift);
+        else
+            hipLaunchKernelGGL(k_qhmc_pass<4>, grid, bpass, 0, s, src, dst, p, pn, L, k, k0, kick_full, drift);
+        std::swap(src, dst);
+        std::swap(p, pn);
+        q += k;
+    }
+    hipLaunchKernelGGL(k_qhmc_ends<false>, grec, block, 0, s, src, p, src == planes ? nullptr : planes, L, traj, keys,
+                       kick_half, cols, runs, w.flag, w.rec_new, nrec);
+    hipLaunchKernelGGL(k_qhmc_decide, dim3(2 * (unsigned)nchunk, 4), block, 0, s, w.rec_old, w.rec_new, nrec, nchunk,
+                       w.chunk_old, w.chunk_new, qb, traj, keys, w.flag, obs);
+    const size_t n = (size_t)L * (size_t)L;
+    const unsigned nb = (unsigned)((n + kThreads * 8 - 1) / (kThreads * 8));
+    hipLaunchKernelGGL(k_qhmc_restore, dim3(nb < 2048 ? nb : 2048, 4), block, 0, s, w.flag, w.saved, planes, n);
     return hipGetLastError();
 }
 

@@ -165,33 +165,35 @@ hipError_t launch_hmc_batch_trajectory(const BhLat* d, const uint32_t* start, in
                                        hipStream_t s);
 bool fused_supported(int L, int tile_x, int tile_y, int m);
 
-// ---- hybrid Monte Carlo on the four-replica texel (xy_quad_hmc.hip)
+// ---- the four replicas of a quad as four lattices back to back
 struct QHmcKeys {
     uint32_t k0[4], k1[4];        // Philox keys of the four replicas
 };
 struct QHmcBeta {
     double b[4];
 };
+// The float4 state's components into four lattices of L^2 floats each, and back.
+hipError_t launch_quad_split(const float4* state, float* planes, int L, hipStream_t s);
+hipError_t launch_quad_join(const float* planes, float4* state, int L, hipStream_t s);
+
+// ---- hybrid Monte Carlo on them (xy_hmc.hip)
 struct QuadHmcWork {
-    float4* p;          // momenta, one float4 per entry
-    float4* saved;      // angles at the start of the trajectory
-    float4* p2;         // second momentum buffer (passes of several steps)
-    unsigned* flag;     // the four accept decisions of the last trajectory
+    float* p;           // momenta, as the lattices
+    float* saved;       // angles at the start of the trajectory
+    float* p2;          // second momentum buffer
+    unsigned* flag;     // per replica (16 words apart) the last decision and an arrival counter
     double* rec_old;    // partial records of H_old: replica r's at rec_old + r * records * 8
     double* rec_new;
     double* chunk_old;  // sums of 256 records each, per replica
     double* chunk_new;
 };
-int quad_hmc_records(int L);          // partial records per replica and H sum
 size_t quad_hmc_work_bytes(int L);
 QuadHmcWork quad_hmc_carve(void* work, int L);
-// One trajectory of all four replicas of the float4 state (result back in
-// `state`, `pingpong` a second state-sized buffer); obs: NULL or 4 records.
-// steps_per_pass > 1: leap-frog steps in passes of up to min(steps_per_pass, 4)
-// (L % 32 == 0, as every quad); 1: one step per launch.  Same trajectory.
-hipError_t launch_quad_hmc_trajectory(float4* state, float4* pingpong, const QuadHmcWork& w, int L,
-                                      const double beta[4], double eps, int n_md, int steps_per_pass, uint32_t traj,
-                                      const QHmcKeys& keys, xy_hmc_obs* obs, hipStream_t s);
+// One trajectory of all four replicas, each bit for bit launch_hmc_trajectory's of
+// its lattice (its FP64 sums may be cut differently); obs: NULL or 4 records.
+hipError_t launch_quad_hmc_trajectory(float* planes, float* second, const QuadHmcWork& w, int L, const double beta[4],
+                                      double eps, int n_md, int steps_per_pass, uint32_t traj, const QHmcKeys& keys,
+                                      xy_hmc_obs* obs, hipStream_t s);
 
 // Fill n u64 words with zero (kernel, not a memset node: safe inside graphs).
 hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t s);

@@ -123,6 +123,7 @@ static hipError_t launch_quad(const float4* src, float4* dst, int L, int tx, int
 namespace {
 
 constexpr uint32_t kQuadMagic = 0x51554144u;   // "QUAD"
+constexpr int kQuadHmcSteps = 4;               // largest (and default) steps-per-pass setting
 
 size_t quad_state_bytes(int L) { return (size_t)L * (size_t)L * sizeof(float4); }
 // one partial record per wave (4 per 256-thread tile) and replica; the smallest
@@ -216,7 +217,7 @@ int xy_quad_init(xy_quad** out, const uint64_t* seeds, int32_t L, const double* 
     q->sweep = 0;
     q->tile_x = L % 128 == 0 ? 128 : 32;
     q->tile_y = L % 128 == 0 ? 8 : 16;
-    q->hmc_steps = 4;
+    q->hmc_steps = kQuadHmcSteps;
     const int Hh = L / 2, P = (Hh + 1) / 2;
     hipLaunchKernelGGL(xyk::k_quad_init, dim3((P + 63) / 64, (L + 3) / 4, 2), dim3(64, 4), 0, q->stream, q->state, L,
                        quad_params(q), start == XY_HOT ? 1 : 0);
@@ -334,22 +335,34 @@ int xy_quad_hmc(xy_quad* q, int64_t n_traj, int32_t n_md, double eps, void* hmc_
         keys.k0[r] = p.k0[r];
         keys.k1[r] = p.k1[r];
     }
+    if (n_traj == 0) return XY_OK;
     const xyk::QuadHmcWork w = xyk::quad_hmc_carve(hmc_work, q->L);
-    for (int64_t j = 0; j < n_traj; ++j) {
-        hipError_t e = XY_LAUNCH(xyk::launch_quad_hmc_trajectory(q->state, q->pingpong, w, q->L, q->beta, eps, n_md,
-                                                                 q->hmc_steps, (uint32_t)q->sweep, keys,
-                                                                 obs_dev ? obs_dev + (size_t)j * 4 : nullptr,
-                                                                 q->stream));
-        if (e != hipSuccess) return xyr::hip_fail(e, "xy_quad_hmc: launch");
-        q->sweep += 1;
+    // The replicas run as four lattices: split into the second buffer at the start of
+    // the call, joined into the state at its end; the state is the second angle
+    // buffer of the trajectories meanwhile.  The setting's largest value stands for
+    // the passes xy_hmc takes by default.
+    const int steps = q->hmc_steps == kQuadHmcSteps ? 7 : q->hmc_steps;
+    float* planes = (float*)q->pingpong;
+    hipError_t e = XY_LAUNCH(xyk::launch_quad_split(q->state, planes, q->L, q->stream));
+    if (e != hipSuccess) return xyr::hip_fail(e, "xy_quad_hmc: launch");
+    int rc = XY_OK;
+    for (int64_t j = 0; j < n_traj && rc == XY_OK; ++j) {
+        e = XY_LAUNCH(xyk::launch_quad_hmc_trajectory(planes, (float*)q->state, w, q->L, q->beta, eps, n_md, steps,
+                                                      (uint32_t)q->sweep, keys,
+                                                      obs_dev ? obs_dev + (size_t)j * 4 : nullptr, q->stream));
+        if (e != hipSuccess) rc = xyr::hip_fail(e, "xy_quad_hmc: launch");
+        else q->sweep += 1;
     }
-    return XY_OK;
+    // also after a failed trajectory, so that the state agrees with the counter
+    e = xyk::launch_quad_join(planes, q->state, q->L, q->stream);
+    if (rc == XY_OK && e != hipSuccess) rc = xyr::hip_fail(e, "xy_quad_hmc: launch");
+    return rc;
 }
 
 int xy_quad_hmc_set_steps_per_pass(xy_quad* q, int32_t steps)
 {
     if (!quad_live(q)) return XY_ESTATE;
-    if (steps < 1 || steps > 4) return XY_EINVAL;
+    if (steps < 1 || steps > kQuadHmcSteps) return XY_EINVAL;
     q->hmc_steps = steps;
     return XY_OK;
 }
