@@ -419,7 +419,9 @@ int xy_tuned_plan(const char* cache_path, int32_t L, int32_t precision, xy_plan*
  *   XY_BATCH_PASSES: one launch per sweep over all tiles of all lattices, one
  *     workgroup per tile; the kernel boundary orders the sweeps;
  *   XY_BATCH_PASSES_WIDE (default): the same, with 256 x 16 tiles for every
- *     lattice whose L is a multiple of 256 (the batch's shape for the others). */
+ *     lattice whose L is a multiple of 256 (the batch's shape for the others, or,
+ *     where that has 512 sites or fewer and xy_batch_set_tile did not ask for it,
+ *     256 x 16 or 64 x 16 tiles that need not divide L). */
 enum { XY_BATCH_PERSISTENT = 0, XY_BATCH_PASSES = 1, XY_BATCH_PASSES_WIDE = 2 };
 /* Device bytes of a batch (section 3.2's replicas, here of any sizes): *state =
  * sum of the lattices' state bytes (lattices back to back), *workspace = the

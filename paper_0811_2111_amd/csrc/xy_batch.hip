@@ -62,6 +62,7 @@ struct LatDesc {
     int xfirst;           // persistent schedule: first tile within its XCD group's list
     int xcd;              // persistent schedule: the XCD group
     int wide;             // tiles of kWideX x kWideY instead of the batch's shape (not under XY_BATCH_PASSES)
+    int rag;              // tiles that need not divide the lattice: 1: 64 x 16, 2: 256 x 16 sites
     int resident;         // held in one workgroup's LDS for a whole call (per-sweep schedules, L <= 32)
     uint32_t key0, key1;
     float delta, nbl2e;
@@ -448,6 +449,67 @@ k_batch_pass(const T* __restrict__ src, T* __restrict__ dst, const LatDesc* __re
                                             d.key1, prm, MEAS != 0, part + (size_t)t * 8, smem, red);
 }
 
+// The same over a work list of tiles that need not divide their lattices (d.rag;
+// 256 x 16 tiles only if BIG) beside the wide ones.  Tiles inside the lattice take
+// the program without bounds; unmeasured, the last ones are moved back inside
+// where the lattice is as large as a tile (both tiles then write the overlap, the
+// same values), otherwise they are cut off.  Records gather their terms pair by
+// pair, as the batch's own shape would (its tiles hold at most one pair a thread).
+template <typename T, int TX, int MEAS>
+__device__ __forceinline__ void ragged_tile(const T* __restrict__ src, T* __restrict__ dst, unsigned bytes, int L,
+                                            int x0, int y0, uint32_t sweep, const LatDesc& d, const Params& prm,
+                                            double* part, char* smem, double* red)
+{
+    if constexpr (MEAS == 0) {
+        if (L >= TX) x0 = min(x0, L - TX);
+        if (L >= 16) y0 = min(y0, L - 16);
+    }
+    if (x0 + TX <= L && y0 + 16 <= L)
+        tile1_program<T, TX, 16, 256, MEAS>(src, dst, bytes, L, x0, y0, sweep, d.key0, d.key1, prm, MEAS != 0, part,
+                                            smem, red);
+    else
+        tile1_program<T, TX, 16, 256, MEAS, false, kPart>(src, dst, bytes, L, x0, y0, sweep, d.key0, d.key1, prm,
+                                                          MEAS != 0, part, smem, red);
+}
+
+template <bool BIG>
+constexpr size_t ragged_lds()
+{
+    constexpr size_t a = Tile1<64, 16, 256>::lds_bytes, w = Tile1<kWideX, kWideY, 256>::lds_bytes;
+    return (BIG ? w : a) + Tile1<64, 16, 256>::red_bytes;
+}
+
+template <typename T, bool MEAS, bool BIG>
+__global__ void __launch_bounds__(256)
+k_batch_ragged(const T* __restrict__ src, T* __restrict__ dst, const LatDesc* __restrict__ lat,
+               const int* __restrict__ tile_lat, int total_tiles, const Ctrl* __restrict__ ctrl, int p,
+               double* __restrict__ part)
+{
+    extern __shared__ __align__(16) char smem[];
+    double* red = (double*)(smem + ragged_lds<BIG>() - Tile1<64, 16, 256>::red_bytes);
+    const int b = (int)blockIdx.x;
+    const int t = (b & 7) * (int)(gridDim.x >> 3) + (b >> 3);
+    if (t >= total_tiles) return;
+    const LatDesc d = lat[tile_lat[t]];
+    const int lt = t - d.first_tile;
+    const int ty = lt / d.tiles_x, tx = lt - ty * d.tiles_x;
+    const Params prm{d.delta, d.nbl2e};
+    const unsigned bytes = (unsigned)((size_t)d.L * d.L * sizeof(T));
+    const uint32_t sweep = ctrl->sweep0 + (uint32_t)p;
+    const T* s = src + d.off;
+    T* o = dst + d.off;
+    double* rec = part + (size_t)t * 8;
+    if (d.rag == 1)
+        ragged_tile<T, 64, MEAS ? -3 : 0>(s, o, bytes, d.L, tx * 64, ty * 16, sweep, d, prm, rec, smem, red);
+    else if constexpr (BIG) {
+        if (d.rag == 2)
+            ragged_tile<T, 256, MEAS ? -3 : 0>(s, o, bytes, d.L, tx * 256, ty * 16, sweep, d, prm, rec, smem, red);
+        else
+            tile1_program<T, kWideX, kWideY, 256, MEAS ? -1 : 0>(s, o, bytes, d.L, tx * kWideX, ty * kWideY, sweep,
+                                                                 d.key0, d.key1, prm, MEAS, rec, smem, red);
+    }
+}
+
 // Records of measured pass p (one workgroup per lattice, fixed order): record r of
 // lattice i at obs[i * nrec + r], sweep count sweep0 + p + 1.  LDS-resident
 // lattices write their own records.
@@ -660,6 +722,19 @@ static void* pass_kernel(int precision, Shape s, bool wide, bool meas, size_t* l
     return nullptr;
 }
 
+template <typename T>
+static void* ragged_kernel_ptr(bool meas, bool big)
+{
+    if (big) return meas ? (void*)k_batch_ragged<T, true, true> : (void*)k_batch_ragged<T, false, true>;
+    return meas ? (void*)k_batch_ragged<T, true, false> : (void*)k_batch_ragged<T, false, false>;
+}
+
+static void* ragged_kernel(int precision, bool meas, bool big, size_t* lds)
+{
+    *lds = big ? ragged_lds<true>() : ragged_lds<false>();
+    return precision == XY_FP16 ? ragged_kernel_ptr<__half>(meas, big) : ragged_kernel_ptr<float>(meas, big);
+}
+
 static void* batch_kernel(int precision, Shape s, size_t* lds)
 {
 #define XYB_CASE(TXV, TYV)                                                                         \
@@ -699,6 +774,8 @@ struct xy_batch {
     uint64_t sweep;
     Layout lo;
     Shape shape;
+    bool tile_set;         // the shape was asked for (xy_batch_set_tile)
+    bool ragged, rag_big;  // the work list holds ragged tiles, 256-wide ones among them
     int sched;             // XY_BATCH_PERSISTENT, XY_BATCH_PASSES or XY_BATCH_PASSES_WIDE
     hipStream_t cap2;      // second capture stream: the LDS-resident lattices
     hipEvent_t ev_fork, ev_join;
@@ -793,6 +870,19 @@ static int plan_batch(xy_batch* b, Shape s)
     if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kNT, lds)) != hipSuccess)
         return xyr::hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (per_cu < 1) return XY_EINVAL;
+    // A batch whose sides share no shape of more than 512 sites (L = 100, 200, 400:
+    // 4 x 4; L = 32, 64, 96: 32 x 16) takes tiles that need not divide them, 256 x 16
+    // sites from L = 512 on and 64 x 16 below (the narrower tile covers a small
+    // lattice with less left over), unless its shape was asked for.  150 lattices of
+    // L = 100, 200, 400: 36 us a sweep (4 x 4 tiles: 1700); 8 of L = 1000: 20 (8 x 8: 340).
+    b->ragged = b->sched == XY_BATCH_PASSES_WIDE && !b->tile_set && s.tx * s.ty <= 512;
+    b->rag_big = false;
+    for (int m = 0; m < 4 && b->ragged; ++m) {
+        size_t pl = 0;
+        void* pk = ragged_kernel(b->precision, (m & 1) != 0, (m & 2) != 0, &pl);
+        if ((e = hipFuncSetAttribute(pk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl)) != hipSuccess)
+            return xyr::hip_fail(e, "hipFuncSetAttribute");
+    }
     int total = 0;
     b->desc.assign(b->n, LatDesc{});
     long long off = 0;
@@ -802,10 +892,12 @@ static int plan_batch(xy_batch* b, Shape s)
         d.L = b->L[i];
         d.resident = b->sched != XY_BATCH_PERSISTENT && d.L <= kBatchResidentMaxL && xyk::resident_supported(d.L);
         d.wide = b->sched != XY_BATCH_PASSES && d.L % kWideX == 0 && d.L % kWideY == 0;
-        const int tx = d.wide ? kWideX : s.tx, ty = d.wide ? kWideY : s.ty;
-        d.tiles_x = d.L / tx;
+        d.rag = b->ragged && !d.wide && !d.resident ? (d.L >= 512 ? 2 : 1) : 0;
+        b->rag_big = b->rag_big || d.wide || d.rag == 2;
+        const int tx = d.wide || d.rag == 2 ? kWideX : d.rag ? 64 : s.tx, ty = d.wide || d.rag ? kWideY : s.ty;
+        d.tiles_x = (d.L + tx - 1) / tx;
         d.first_tile = total;
-        d.ntiles = d.resident ? 0 : (d.L / tx) * (d.L / ty);
+        d.ntiles = d.resident ? 0 : d.tiles_x * ((d.L + ty - 1) / ty);
         xyk::SweepArgs a = xyr::sweep_args(b->seed[i], d.L, b->precision, b->beta[i], b->delta[i]);
         d.key0 = a.key0;
         d.key1 = a.key1;
@@ -943,7 +1035,8 @@ static hipError_t enqueue_passes(xy_batch* b, hipStream_t s, int npass, int32_t 
     for (int p = 0; p < npass && tt > 0; ++p) {
         const bool meas = me > 0 && ((p + 1) % me) == 0;
         size_t lds = 0;
-        void* k = pass_kernel(b->precision, b->shape, b->sched == XY_BATCH_PASSES_WIDE, meas, &lds);
+        void* k = b->ragged ? ragged_kernel(b->precision, meas, b->rag_big, &lds)
+                            : pass_kernel(b->precision, b->shape, b->sched == XY_BATCH_PASSES_WIDE, meas, &lds);
         void* src = (p & 1) ? pp : (void*)b->state;
         void* dst = (p & 1) ? (void*)b->state : pp;
         int pv = p;
@@ -1017,6 +1110,7 @@ int xy_batch_init(xy_batch** out, int32_t n, const uint64_t* seeds, const int32_
     b->ev_join = nullptr;
     b->nres = 0;
     b->res_maxL = 0;
+    b->tile_set = b->ragged = b->rag_big = false;
     b->sweep = 0;
     b->pt_round = 0;
     b->lo = layout(n, L, precision);
@@ -1197,7 +1291,13 @@ int xy_batch_set_tile(xy_batch* b, int32_t tile_x, int32_t tile_y)
 {
     if (!blive(b)) return XY_ESTATE;
     for (const Shape& s : candidates(b->n, b->L.data()))
-        if (s.tx == tile_x && s.ty == tile_y) return plan_batch(b, s);
+        if (s.tx == tile_x && s.ty == tile_y) {
+            const bool old = b->tile_set;
+            b->tile_set = true;
+            const int rc = plan_batch(b, s);
+            if (rc != XY_OK) b->tile_set = old;
+            return rc;
+        }
     return XY_EINVAL;
 }
 

@@ -397,6 +397,12 @@ __device__ __forceinline__ void tile1_black(const T1Geom& g, const float2* __res
                     meas_black(t, cb, sb, n.lb.x, n.lb.y, n.rb.x, n.rb.y, n.ub.x, n.ub.y, n.db.x, n.db.y);
                 v[0] += (double)t.cx; v[1] += (double)t.cy; v[2] += (double)t.ix;
                 v[3] += (double)t.iy; v[4] += (double)t.mx; v[5] += (double)t.my;
+            } else if constexpr (MEAS == 3) {
+                MeasAcc t;
+                meas_acc(t, ca, sa, n.la, n.ra, n.ua, n.da);
+                if (!(RAG & kOdd) || g.has_b) meas_acc(t, cb, sb, n.lb, n.rb, n.ub, n.db);
+                v[0] += (double)t.cx; v[1] += (double)t.cy; v[2] += (double)t.ix;
+                v[3] += (double)t.iy; v[4] += (double)t.mx; v[5] += (double)t.my;
             } else if constexpr (MEAS == 1) {
                 meas_acc(m, ca, sa, n.la, n.ra, n.ua, n.da);
                 meas_acc(m, cb, sb, n.lb, n.rb, n.ub, n.db);
@@ -546,8 +552,8 @@ __device__ __forceinline__ void tile1_sweep(const T1Geom& g, float2* __restrict_
         tile1_red<T, TX, TY, NT, 0, ST, RAG>(g, cs, a.thr, rd, sweep, k0, k1, p, a.the, e, a.e_row, a.e_col, a.e_red, a.e_k,
                                     acc);
     __syncthreads();
-    if (MEAS > 0 || (MEAS == -1 && meas)) {
-        constexpr int how = MEAS == 2 ? 2 : 1;
+    if (MEAS > 0 || MEAS == -3 || (MEAS == -1 && meas)) {
+        constexpr int how = MEAS == 2 ? 2 : MEAS == 3 || MEAS == -3 ? 3 : 1;
         if (red_odd)
             tile1_black<T, TX, TY, NT, 0, how, ST, RAG>(g, cs, a.thb, rd, sweep, k0, k1, p, acc, m, v);
         else
@@ -590,7 +596,10 @@ __device__ __forceinline__ void tile1_sweep(const T1Geom& g, float2* __restrict_
 //              a fixed order);
 //   MEAS = 2 : the same, each pair's FP32 terms by themselves as k_measure gathers
 //              them (MEAS = 1: a thread's pairs one after another);
-//   MEAS = -1: measure if `meas`, one partial record per tile at part[0 .. 8].
+//   MEAS = 3 : the same, each pair by itself in the arithmetic of MEAS = 1 (what a
+//              tile with one pair a thread gathers);
+//   MEAS = -1: measure if `meas`, one partial record per tile at part[0 .. 8];
+//   MEAS = -3: always measure, pairs as MEAS = 3, one partial record per tile.
 // A record is (Cx, Cy, Ix, Iy, Mx, My, accepts, 0).
 // ST: the updated angles are stored with the non-temporal hint (for lattices
 // larger than the caches: the stored lines are read again only a sweep later).
