@@ -256,7 +256,9 @@ int xy_quad_get_sweep(const xy_quad* q, uint64_t* sweep);
 int xy_quad_set_sweep(xy_quad* q, uint64_t sweep);
 /* Tile shape of the fused sweep: (32, 16), (64, 8), (64, 16), (128, 4), (128, 8),
  * dividing L (default (128, 8), or (32, 16) if 128 does not divide L).  The
- * trajectory does not depend on it. */
+ * trajectory does not depend on it.  Every sweep after the call takes that tile;
+ * before it the library chooses (the whole quad in four workgroups, several sweeps
+ * per launch, or the four lattices apart between the first and the last sweep). */
 int xy_quad_set_tile(xy_quad* q, int32_t tile_x, int32_t tile_y);
 int xy_quad_get_tile(const xy_quad* q, int32_t* tile_x, int32_t* tile_y);
 int xy_quad_free(xy_quad* q);

@@ -8,6 +8,7 @@
 #include "xy_deep.hpp"
 #include "xy_launch.hpp"
 #include "xy_reduce.hpp"
+#include "xy_tile4.hpp"
 
 using namespace xyd;
 
@@ -15,14 +16,8 @@ namespace xyk {
 
 // The lattice's pairs and rows are cut into tx x ty cores whose sides differ by
 // at most one.
-template <typename T, int NT, int R, bool ODD, int MEAS>
-__global__ void __launch_bounds__(NT)
-k_deep(const T* __restrict__ src, T* __restrict__ dst, int L, int tx, int ty, int PC, int RY, int hx, int hy,
-       uint32_t sweep0, int n, int me, int phase, int rp, int full, uint32_t k0, uint32_t k1, Params p,
-       double* __restrict__ part)
+__device__ __forceinline__ DeepRegion region_of(int b, int L, int tx, int ty, int PC, int RY, int hx, int hy)
 {
-    extern __shared__ __align__(16) char smem[];
-    const int nb = (int)gridDim.x, b = (int)blockIdx.x;
     const int by = b / tx, bx = b - by * tx;
     DeepRegion g;
     g.L = L;
@@ -38,7 +33,19 @@ k_deep(const T* __restrict__ src, T* __restrict__ dst, int L, int tx, int ty, in
     g.hy = hy;
     g.cp = c1 - c0;
     g.cr = r1 - r0;
-    deep_program<T, NT, R, ODD, false, MEAS>(src, dst, g, sweep0, n, me, phase, rp, full, k0, k1, p, smem,
+    return g;
+}
+
+template <typename T, int NT, int R, bool ODD, int MEAS>
+__global__ void __launch_bounds__(NT)
+k_deep(const T* __restrict__ src, T* __restrict__ dst, int L, int tx, int ty, int PC, int RY, int hx, int hy,
+       uint32_t sweep0, int n, int me, int phase, int rp, int full, uint32_t k0, uint32_t k1, Params p,
+       double* __restrict__ part)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int nb = (int)gridDim.x, b = (int)blockIdx.x;
+    const DeepRegion g = region_of(b, L, tx, ty, PC, RY, hx, hy);
+    deep_program<T, NT, R, ODD, false, MEAS, false>(src, dst, g, sweep0, n, me, phase, rp, full, k0, k1, p, smem,
                                              [&](int k, double s) { part[((size_t)k * nb + b) * 8 + threadIdx.x] = s; });
 }
 
@@ -73,6 +80,20 @@ static bool deep_fits(const DeepPlan& d)
     return d.RY / 2 * d.PC <= kDeepPairs<NT, R> && deep_lds_bytes(d.PC, d.RY, NT) <= 160 * 1024;
 }
 
+// The most sweeps of d's cores in the smallest workgroup that takes at least four.
+static int deep_depth(int L, DeepPlan* d)
+{
+    auto depth = [&](auto fits) {
+        int n = kDeepMaxSweeps;
+        while (n > 0 && !(deep_region(L, n, d) && fits(*d))) --n;
+        return n;
+    };
+    int n = depth(deep_fits<512, 1>);
+    if (n < 4) n = depth(deep_fits<1024, 1>);
+    if (n < 4) n = depth(deep_fits<1024, 2>);
+    return n;
+}
+
 bool deep_choose(int L, bool meas, DeepPlan* d, int* nmax)
 {
     if (L < kDeepMinL || L > kDeepMaxL || L % 2) return false;
@@ -90,16 +111,8 @@ bool deep_choose(int L, bool meas, DeepPlan* d, int* nmax)
             d->tx = std::min(P / 2, std::max(8192 / L, (P + 11) / 12));
         }
     }
-    auto depth = [&](auto fits) {
-        int n = kDeepMaxSweeps;
-        while (n > 0 && !(deep_region(L, n, d) && fits(*d))) --n;
-        return n;
-    };
-    int n = depth(deep_fits<512, 1>);
-    if (n < 4) n = depth(deep_fits<1024, 1>);
-    if (n < 4) n = depth(deep_fits<1024, 2>);
-    *nmax = n;
-    return n > 0;
+    *nmax = deep_depth(L, d);
+    return *nmax > 0;
 }
 
 template <typename T, int NT, int R, bool ODD, int MEAS>
@@ -152,10 +165,112 @@ hipError_t launch_deep(const SweepArgs& a, const DeepPlan& d, int n, int me, int
                                   : go_deep<float>(a, d, n, me, phase, part, s);
 }
 
-// Workgroup k: record k from its np partial records (fixed order), sweep count
-// first + k * every.
+// ------------------------------------------------------ four replicas of a quad
+// Replica blockIdx.y of a quad: its regions are those of a lattice of its own, read
+// from and written to its components of the float4 states (the replicas of a region
+// fall on one XCD where a lattice's regions are a multiple of 8, so their stores
+// merge in its L2).
+template <int NT, int R, int MEAS>
+__global__ void __launch_bounds__(NT)
+k_deep_quad(const float* __restrict__ src, float* __restrict__ dst, int L, int tx, int ty, int PC, int RY, int hx,
+            int hy, uint32_t sweep0, int n, int me, int phase, Params4 p, double* __restrict__ part)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int nb = (int)gridDim.x, b = (int)blockIdx.x, r = (int)blockIdx.y;
+    const DeepRegion g = region_of(b, L, tx, ty, PC, RY, hx, hy);
+    const Params pr{p.delta[r], p.nbl2e[r]};
+    deep_program<float, NT, R, false, false, MEAS, true>(
+        src + r, dst + r, g, sweep0, n, me, phase, 0, 0, p.k0[r], p.k1[r], pr, smem,
+        [&](int k, double s) { part[((size_t)(4 * k + r) * nb + b) * 8 + threadIdx.x] = s; });
+}
+
+// The same with the whole lattice in one workgroup (L = 32): any number of sweeps
+// in place; the partial record is the record.
+template <int NT, int MEAS>
+__global__ void __launch_bounds__(NT)
+k_resident_quad(float* __restrict__ st, int L, uint32_t sweep0, int n, int me, Params4 p, xy_obs* __restrict__ obs)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int r = (int)blockIdx.x;
+    const Params pr{p.delta[r], p.nbl2e[r]};
+    const DeepRegion g{L, L >> 1, L >> 2, 0, 0, L >> 2, L, 0, 0, L >> 2, L};
+    deep_program<float, NT, 1, false, true, MEAS, true>(
+        st + r, st + r, g, sweep0, n, me, 0, 0, 0, p.k0[r], p.k1[r], pr, smem, [&](int k, double s) {
+            // xy_obs: sweep, n_accept, then the six sums, eight bytes each
+            const int t = (int)threadIdx.x;
+            unsigned long long* o = (unsigned long long*)(obs + (size_t)k * 4 + r);
+            if (t < 6) o[2 + t] = (unsigned long long)__double_as_longlong(s);
+            else if (t == 6) o[1] = (unsigned long long)s;
+            else o[0] = (uint64_t)sweep0 + (uint64_t)(k + 1) * (uint64_t)me;
+        });
+}
+
+// A quad's replicas share the device, a quarter of it each: 8 x 8 regions, up to
+// the side where those hold four sweeps.  Measured, us for ten sweeps, against
+// single sweeps by tiles: L = 96 19.0 (64.8 one kernel for the four), L = 256 23.0
+// (53.9), L = 384 38.4 (53.2); 16 x 16 regions beyond take longer than the tiles
+// (L = 512 76.4 against 60.6).
+constexpr int kDeepQuadMaxL = 384;
+
+bool deep_choose_quad(int L, DeepPlan* d, int* nmax)
+{
+    if (L < kDeepMinL || L > kDeepQuadMaxL || L % 4) return false;
+    d->rp = d->full = 0;
+    d->tx = d->ty = std::min(8, (L + 15) / 16);
+    *nmax = deep_depth(L, d);
+    return *nmax > 0;
+}
+
+template <int NT, int R, int MEAS>
+static hipError_t run_deep_quad(const float4* src, float4* dst, int L, uint32_t sweep, const Params4& p,
+                                const DeepPlan& d, int n, int me, int phase, double* part, hipStream_t s)
+{
+    static bool attr_set = false;
+    auto kern = k_deep_quad<NT, R, MEAS>;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           160 * 1024);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(d.tx * d.ty, 4), dim3(NT), deep_lds_bytes(d.PC, d.RY, NT), s, (const float*)src,
+                       (float*)dst, L, d.tx, d.ty, d.PC, d.RY, d.hx, d.hy, sweep, n, me, phase, p, part);
+    return hipGetLastError();
+}
+
+hipError_t launch_deep_quad(const float4* src, float4* dst, int L, uint32_t sweep, const Params4& p, const DeepPlan& d,
+                            int n, int me, int phase, double* part, hipStream_t s)
+{
+    const bool meas = me > 0 && (n + phase) / me > phase / me;
+#define XY_DEEP(nt, r)                                                                                           \
+    if (deep_fits<nt, r>(d))                                                                                     \
+        return meas ? run_deep_quad<nt, r, kMeasQuad>(src, dst, L, sweep, p, d, n, me, phase, part, s)            \
+                    : run_deep_quad<nt, r, kMeasNone>(src, dst, L, sweep, p, d, n, me, phase, part, s)
+    XY_DEEP(512, 1);
+    XY_DEEP(1024, 1);
+    XY_DEEP(1024, 2);
+#undef XY_DEEP
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_resident_quad(float4* state, int L, uint32_t sweep, const Params4& p, int n, int me, xy_obs* obs,
+                                hipStream_t s)
+{
+    if (L % 4 || (L / 2) * (L / 4) > kDeepPairs<512, 1>) return hipErrorInvalidValue;
+    const size_t lds = deep_lds_bytes(L / 4, L, 512);
+    if (me > 0 && obs)
+        hipLaunchKernelGGL((k_resident_quad<512, kMeasQuad>), dim3(4), dim3(512), lds, s, (float*)state, L, sweep, n, me,
+                           p, obs);
+    else
+        hipLaunchKernelGGL((k_resident_quad<512, kMeasNone>), dim3(4), dim3(512), lds, s, (float*)state, L, sweep, n, 0,
+                           p, obs);
+    return hipGetLastError();
+}
+
+// Workgroup k: record k from its np partial records (fixed order); every `group`
+// records share a sweep count, first, first + every, ...
 __global__ void __launch_bounds__(256)
-k_finalize_many(const double* __restrict__ part, int np, xy_obs* __restrict__ out, uint64_t first, int every)
+k_finalize_many(const double* __restrict__ part, int np, xy_obs* __restrict__ out, uint64_t first, int every, int group)
 {
     __shared__ double red[4 * 7];
     const int k = (int)blockIdx.x;
@@ -168,7 +283,7 @@ k_finalize_many(const double* __restrict__ part, int np, xy_obs* __restrict__ ou
     block_sum7_256(v, red);
     if (threadIdx.x == 0) {
         xy_obs o;
-        o.sweep = first + (uint64_t)k * (uint64_t)every;
+        o.sweep = first + (uint64_t)(k / group) * (uint64_t)every;
         o.n_accept = (unsigned long long)v[6];
         o.cx = v[0]; o.cy = v[1]; o.ix = v[2]; o.iy = v[3]; o.mx = v[4]; o.my = v[5];
         out[k] = o;
@@ -176,9 +291,9 @@ k_finalize_many(const double* __restrict__ part, int np, xy_obs* __restrict__ ou
 }
 
 hipError_t launch_finalize_many(const double* part, int np, int nrec, xy_obs* out, uint64_t first, int every,
-                                hipStream_t s)
+                                hipStream_t s, int group)
 {
-    hipLaunchKernelGGL(k_finalize_many, dim3(nrec), dim3(256), 0, s, part, np, out, first, every);
+    hipLaunchKernelGGL(k_finalize_many, dim3(nrec), dim3(256), 0, s, part, np, out, first, every, group);
     return hipGetLastError();
 }
 

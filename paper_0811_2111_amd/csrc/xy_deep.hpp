@@ -66,16 +66,23 @@ __host__ __device__ constexpr size_t deep_lds_bytes(int PC, int RY, int nt)
 
 // The two entries of a pair.  The caller's state is aligned to an entry, not
 // necessarily to a pair: the copies leave the choice of loads to the compiler.
-template <typename T>
+// Q: entries lie four apart (one replica of a quad's float4 state).
+template <typename T, bool Q>
 __device__ __forceinline__ float2 pair_ld(const T* e)
 {
+    if constexpr (Q) return make_float2(store<T>::ld(e[0]), store<T>::ld(e[4]));
     T v[2];
     __builtin_memcpy(v, e, sizeof(v));
     return make_float2(store<T>::ld(v[0]), store<T>::ld(v[1]));
 }
-template <typename T>
+template <typename T, bool Q>
 __device__ __forceinline__ void pair_st(T* e, float2 f)
 {
+    if constexpr (Q) {
+        e[0] = store<T>::st(f.x);
+        e[4] = store<T>::st(f.y);
+        return;
+    }
     const T v[2] = {store<T>::st(f.x), store<T>::st(f.y)};
     __builtin_memcpy(e, v, sizeof(v));
 }
@@ -122,10 +129,11 @@ struct DeepItems {
 // sums (another order in FP32 shows at 1e-8 of the record at L = 32).
 //   kMeasOwn  : a thread's own pairs one after another (the LDS-resident plan);
 //   kMeasPair : each pair by itself (k_measure, the streaming plan);
+//   kMeasQuad : each pair by itself, in the arithmetic of the tiles (a quad's plan);
 //   kMeasChain: columns of `full` pairs, `rp` rows apart, from blocks of rp * full
 //               rows (a thread's black pairs in the single-sweep tile), read back
 //               from LDS after the black half-sweep.
-enum DeepMeas { kMeasNone, kMeasOwn, kMeasPair, kMeasChain };
+enum DeepMeas { kMeasNone, kMeasOwn, kMeasPair, kMeasChain, kMeasQuad };
 
 // What a half-sweep can prepare before its neighbours are known, as far as it fits
 // into registers beside the angles: with one pair a thread its two proposals; with
@@ -207,6 +215,12 @@ __device__ __forceinline__ void deep_half(float2* __restrict__ own, const float2
             if constexpr (MEAS == kMeasOwn) {
                 meas_acc(m, cs[q].x, cs[q].y, n.la, n.ra, n.ua, n.da);
                 if (b) meas_acc(m, cs[q].z, cs[q].w, n.lb, n.rb, n.ub, n.db);
+            } else if constexpr (MEAS == kMeasQuad) {
+                MeasAcc t;
+                meas_acc(t, cs[q].x, cs[q].y, n.la, n.ra, n.ua, n.da);
+                meas_acc(t, cs[q].z, cs[q].w, n.lb, n.rb, n.ub, n.db);
+                v[0] += (double)t.cx; v[1] += (double)t.cy; v[2] += (double)t.ix;
+                v[3] += (double)t.iy; v[4] += (double)t.mx; v[5] += (double)t.my;
             } else if constexpr (MEAS == kMeasPair) {
                 Meas t{0, 0, 0, 0, 0, 0};
                 meas_black(t, cs[q].x, cs[q].y, n.la.x, n.la.y, n.ra.x, n.ra.y, n.ua.x, n.ua.y, n.da.x, n.da.y);
@@ -251,7 +265,8 @@ template <int NT, int R> constexpr int kDeepPairs = NT / 4 * R;
 // == 0 (rp, full: kMeasChain only); `put(k, s)` is then called by the threads 0 .. 7 for the k-th measured
 // sweep of this call (s: their value: six sums, accepts, 0).  smem:
 // deep_lds_bytes(PC, RY, NT).
-template <typename T, int NT, int R, bool ODD, bool WRAP, int MEAS, typename Put>
+// Q: src and dst are one replica's components of float4 states.
+template <typename T, int NT, int R, bool ODD, bool WRAP, int MEAS, bool Q, typename Put>
 __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __restrict__ dst, const DeepRegion& g,
                                              uint32_t sweep0, int n, int me, int phase, int rp, int full, uint32_t k0,
                                              uint32_t k1, const Params& p, char* smem, Put put)
@@ -297,9 +312,9 @@ __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __res
         it.elem[q] = half + (unsigned)(y * g.Hh + 2 * pp);
         th[q] = make_float2(0.f, 0.f);
         if (f & kOn) {
-            const T* e = src + it.elem[q];
+            const T* e = src + (size_t)it.elem[q] * (Q ? 4 : 1);
             if constexpr (ODD) th[q] = make_float2(store<T>::ld(e[0]), store<T>::ld(e[(f & kHasB) ? 1 : 0]));
-            else th[q] = pair_ld<T>(e);
+            else th[q] = pair_ld<T, Q>(e);
         }
     }
     DeepDraw dr{sweep0, (uint32_t)col, k0, k1};
@@ -372,12 +387,12 @@ __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __res
 #pragma unroll
     for (int q = 0; q < R; ++q) {
         if (!(it.flag[q] & kCore)) continue;
-        T* e = dst + it.elem[q];
+        T* e = dst + (size_t)it.elem[q] * (Q ? 4 : 1);
         if constexpr (ODD) {
             e[0] = store<T>::st(th[q].x);
             if (it.flag[q] & kHasB) e[1] = store<T>::st(th[q].y);
         } else {
-            pair_st<T>(e, th[q]);
+            pair_st<T, Q>(e, th[q]);
         }
     }
 }

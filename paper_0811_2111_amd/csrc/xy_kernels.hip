@@ -347,6 +347,8 @@ hipError_t launch_reduce_chunks(const double* partials, int nparts, double* out,
 // scope) sums the chunk results as k_finalize does, writes the record and sets
 // the counter back to zero.  The sums, and their order, are those of the two
 // separate kernels.
+// blockIdx.y: one of several records, whose partials, chunks, counters and results
+// lie one after another.
 __global__ void __launch_bounds__(256)
 k_reduce_finalize(const double* __restrict__ partials, int nparts, double* __restrict__ chunks,
                   unsigned* __restrict__ arrive, unsigned long long* __restrict__ counter, xy_obs* __restrict__ out,
@@ -354,6 +356,10 @@ k_reduce_finalize(const double* __restrict__ partials, int nparts, double* __res
 {
     __shared__ double red[4 * 7];
     __shared__ int last;
+    partials += (size_t)blockIdx.y * nparts * 8;
+    chunks += (size_t)blockIdx.y * gridDim.x * 8;
+    arrive += blockIdx.y;
+    out += blockIdx.y;
     const int i = blockIdx.x * 256 + threadIdx.x;
     double v[7] = {0, 0, 0, 0, 0, 0, 0};
     if (i < nparts) {
@@ -406,6 +412,14 @@ hipError_t launch_finalize(const double* partials, int nparts, unsigned long lon
     } else {
         hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, s, partials, nparts, counter, out, sweep_after);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_finalize_quad(const double* partials, int nrec, xy_obs* out, uint64_t sweep_after, double* chunks,
+                                unsigned* arrive, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_reduce_finalize, dim3((nrec + 255) / 256, 4), dim3(256), 0, s, partials, nrec, chunks, arrive,
+                       (unsigned long long*)nullptr, out, sweep_after);
     return hipGetLastError();
 }
 

@@ -7,6 +7,10 @@
 
 #include "xy.h"
 
+namespace xyd {
+struct Params4;       // xy_tile4.hpp
+}
+
 namespace xyk {
 
 struct SweepArgs {
@@ -104,9 +108,9 @@ bool deep_choose(int L, bool meas, DeepPlan* d, int* nmax);
 // region b at part[(k * tx * ty + b) * 8].
 hipError_t launch_deep(const SweepArgs& a, const DeepPlan& d, int n, int me, int phase, double* part, hipStream_t s);
 // nrec records of np partial records each, back to back in `part`, into out[0 ..];
-// record k's sweep count is first + k * every.
+// record k's sweep count is first + (k / group) * every.
 hipError_t launch_finalize_many(const double* part, int np, int nrec, xy_obs* out, uint64_t first, int every,
-                                hipStream_t s);
+                                hipStream_t s, int group = 1);
 
 // ---- hybrid Monte Carlo (xy_hmc.hip)
 constexpr int kHmcMaxRecords = 65536;   // partial records of one H sum (old or new)
@@ -164,6 +168,23 @@ hipError_t launch_hmc_batch_trajectory(const BhLat* d, const uint32_t* start, in
                                        double eps, int n_md, int steps_per_pass, int rows, const uint32_t* traj_dev,
                                        hipStream_t s);
 bool fused_supported(int L, int tile_x, int tile_y, int m);
+
+// ---- sweeps of the four replicas of a quad
+// Several sweeps per launch as launch_deep, from one float4 state to another; the
+// k-th measured sweep leaves a record of replica r, region b at
+// part[((4 k + r) * tx * ty + b) * 8].
+bool deep_choose_quad(int L, DeepPlan* d, int* nmax);
+hipError_t launch_deep_quad(const float4* src, float4* dst, int L, uint32_t sweep, const xyd::Params4& p,
+                            const DeepPlan& d, int n, int me, int phase, double* part, hipStream_t s);
+// The whole quad in four workgroups (L <= 32): n sweeps in place, records of every
+// me-th one to obs[0 .. 3], obs[4 .. 7] ... (none if me == 0 or obs == NULL).
+hipError_t launch_resident_quad(float4* state, int L, uint32_t sweep, const xyd::Params4& p, int n, int me, xy_obs* obs,
+                                hipStream_t s);
+// The four records of one sweep, replica r's from the nrec partial records at
+// partials + r * nrec * 8, through `chunks` (4 * ceil(nrec / 256) records) and the
+// arrival counters arrive[0 .. 3].
+hipError_t launch_finalize_quad(const double* partials, int nrec, xy_obs* out, uint64_t sweep_after, double* chunks,
+                                unsigned* arrive, hipStream_t s);
 
 // ---- the four replicas of a quad as four lattices back to back
 struct QHmcKeys {

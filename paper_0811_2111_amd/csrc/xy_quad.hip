@@ -1,7 +1,9 @@
 // xy_quad.hip -- four replicas of one lattice in one float4 state: hot start,
-// fused sweeps, measurement records, and the xy_quad_* C ABI.
+// fused sweeps, sweeps of the four lattices apart, measurement records, and the
+// xy_quad_* C ABI.  (Several sweeps per launch: xy_deep.hip.)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <new>
 
@@ -53,9 +55,9 @@ __device__ __forceinline__ int xcd_tile4(int b, int ntiles)
     return (b & 7) * per + (b >> 3);
 }
 
-template <int TX, int TY, bool MEAS>
+template <int TX, int TY, bool MEAS, bool IN, bool OUT>
 __global__ void __launch_bounds__(256)
-k_quad_fused(const float4* __restrict__ src, float4* __restrict__ dst, int L, uint32_t sweep, Params4 p,
+k_quad_fused(const void* __restrict__ src, void* __restrict__ dst, int L, uint32_t sweep, Params4 p,
              double* __restrict__ partials)
 {
     extern __shared__ __align__(16) char smem[];
@@ -63,17 +65,17 @@ k_quad_fused(const float4* __restrict__ src, float4* __restrict__ dst, int L, ui
     const int ntiles = tiles_x * (L / TY);
     const int b = xcd_tile4((int)blockIdx.x, ntiles);
     const int ty = b / tiles_x, tx = b - ty * tiles_x;
-    tile4_program<TX, TY, 256, MEAS>(src, dst, (unsigned)((size_t)L * L * sizeof(float4)), L, tx * TX, ty * TY, sweep,
+    tile4_program<TX, TY, 256, MEAS, IN, OUT>(src, dst, (unsigned)((size_t)L * L * sizeof(float4)), L, tx * TX, ty * TY, sweep,
                                      p, partials + (size_t)b * 4 * 8, (size_t)ntiles * 4, smem);
 }
 
-template <int TX, int TY, bool MEAS>
-hipError_t run_quad(const float4* src, float4* dst, int L, uint32_t sweep, const Params4& p, double* partials,
+template <int TX, int TY, bool MEAS, bool IN = false, bool OUT = false>
+hipError_t run_quad(const void* src, void* dst, int L, uint32_t sweep, const Params4& p, double* partials,
                     hipStream_t s)
 {
     constexpr size_t lds = Tile4<TX, TY, 256>::lds_bytes;
     static bool attr_set = false;
-    auto kern = k_quad_fused<TX, TY, MEAS>;
+    auto kern = k_quad_fused<TX, TY, MEAS, IN, OUT>;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -82,6 +84,85 @@ hipError_t run_quad(const float4* src, float4* dst, int L, uint32_t sweep, const
     const int ntiles = (L / TX) * (L / TY);
     hipLaunchKernelGGL(kern, dim3(ntiles), dim3(256), lds, s, src, dst, L, sweep, p, partials);
     return hipGetLastError();
+}
+
+// One sweep of the four lattices of a quad back to back (blockIdx.y: the replica)
+// by TX x 16 tiles; the last ones are cut off at the lattice's edge when measured
+// and moved back inside otherwise.  Records as tile4_program's: each pair's terms by
+// themselves, a record per wave.
+//
+// Bound by the vector unit, as the single-lattice tiles.  A float4 tile moves 16
+// bytes of (cos, sin) through LDS for every 4 updates' one, holds two to three times the
+// registers and runs three workgroups a CU to this one's four: measured, us a sweep
+// of all four, k_quad_fused against this: L = 1024 13.5 and 12.0, L = 2048 42.5 and
+// 31, L = 4096 160 and 123.5; measured sweeps 35 and 19 at L = 1024, 290 and 148 at
+// L = 4096.
+template <int TX, bool MEAS, bool ST>
+__global__ void __launch_bounds__(256)
+k_planes(const float* __restrict__ src, float* __restrict__ dst, int L, uint32_t sweep, Params4 p,
+         double* __restrict__ partials)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int tiles_x = (L + TX - 1) / TX, ntiles = tiles_x * ((L + 15) / 16);
+    const int b = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);   // a multiple of 8
+    if (b >= ntiles) return;
+    const int r = (int)blockIdx.y;
+    const int ty = b / tiles_x;
+    int x0 = (b - ty * tiles_x) * TX, y0 = ty * 16;
+    if constexpr (!MEAS) {
+        y0 = min(y0, L - 16);
+        x0 = min(x0, L - TX);
+    }
+    const size_t n = (size_t)L * L;
+    const Params pr{p.delta[r], p.nbl2e[r]};
+    double* part = partials + ((size_t)r * ntiles + b) * 4 * 8;
+    if (!MEAS || (x0 + TX <= L && y0 + 16 <= L))
+        tile1_program<float, TX, 16, 256, MEAS ? 3 : 0, ST>(src + r * n, dst + r * n, (unsigned)(n * 4), L, x0, y0,
+                                                            sweep, p.k0[r], p.k1[r], pr, MEAS, part, smem, nullptr);
+    else if constexpr (MEAS)
+        tile1_program<float, TX, 16, 256, 3, ST, kPart>(src + r * n, dst + r * n, (unsigned)(n * 4), L, x0, y0, sweep,
+                                                        p.k0[r], p.k1[r], pr, true, part, smem, nullptr);
+}
+
+template <int TX, bool MEAS, bool ST>
+hipError_t run_planes(const float* src, float* dst, int L, uint32_t sweep, const Params4& p, double* part,
+                      hipStream_t s)
+{
+    constexpr size_t lds = Tile1<TX, 16, 256>::lds_bytes;
+    static bool attr_set = false;
+    auto kern = k_planes<TX, MEAS, ST>;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const unsigned tiles = (unsigned)(((L + TX - 1) / TX) * ((L + 15) / 16));
+    hipLaunchKernelGGL(kern, dim3((tiles + 7) & ~7u, 4), dim3(256), lds, s, src, dst, L, sweep, p, part);
+    return hipGetLastError();
+}
+
+// Sites the tiles cover, the 128 x 16 ones at 8% more each (as for a single lattice).
+int planes_tile_x(int L)
+{
+    const int t128 = (L + 127) / 128, t256 = (L + 255) / 256;
+    return t128 * 0.54 < t256 ? 128 : 256;
+}
+int planes_records(int L) { return 4 * ((L + planes_tile_x(L) - 1) / planes_tile_x(L)) * ((L + 15) / 16); }
+
+hipError_t launch_planes(const float* src, float* dst, int L, uint32_t sweep, const Params4& p, bool meas,
+                         double* part, hipStream_t s)
+{
+    const bool st = 2 * (size_t)L * L * sizeof(float4) > (size_t)256 << 20;     // beyond the MALL
+#define X(tx)                                                                                               \
+    if (planes_tile_x(L) == tx)                                                                             \
+        return meas ? st ? run_planes<tx, true, true>(src, dst, L, sweep, p, part, s)               \
+                         : run_planes<tx, true, false>(src, dst, L, sweep, p, part, s)              \
+                    : st ? run_planes<tx, false, true>(src, dst, L, sweep, p, part, s)              \
+                         : run_planes<tx, false, false>(src, dst, L, sweep, p, part, s)
+    X(128);
+    X(256);
+#undef X
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -102,6 +183,21 @@ static bool quad_shape_ok(int L, int tx, int ty)
     XY_QUAD_SHAPES(X)
 #undef X
     return false;
+}
+
+// One sweep between the float4 layout and the four lattices (`in`: src holds the
+// lattices, else dst does), by the default tiles.
+static hipError_t launch_quad_convert(const void* src, void* dst, int L, uint32_t sweep, const Params4& p, bool in,
+                                      bool meas, double* part, hipStream_t s)
+{
+#define X(a, b)                                                                                   \
+    return in ? meas ? run_quad<a, b, true, true, false>(src, dst, L, sweep, p, part, s)          \
+                     : run_quad<a, b, false, true, false>(src, dst, L, sweep, p, part, s)         \
+              : meas ? run_quad<a, b, true, false, true>(src, dst, L, sweep, p, part, s)          \
+                     : run_quad<a, b, false, false, true>(src, dst, L, sweep, p, part, s)
+    if (L % 128 == 0) X(128, 8);
+    X(32, 16);
+#undef X
 }
 
 static hipError_t launch_quad(const float4* src, float4* dst, int L, int tx, int ty, uint32_t sweep,
@@ -158,6 +254,7 @@ struct xy_quad {
     hipStream_t stream;
     uint64_t sweep;
     int32_t tile_x, tile_y;
+    bool tile_set;         // the caller chose the tile: every sweep takes it
     int32_t hmc_steps;     // leap-frog steps per pass of xy_quad_hmc (1 .. 4)
 };
 
@@ -174,6 +271,122 @@ static xyd::Params4 quad_params(const xy_quad* q)
         p.k1[r] = a.key1;
     }
     return p;
+}
+
+// Every sweep in one launch of four workgroups (L = 32).
+static int quad_resident_sweeps(xy_quad* q, int64_t n_sweeps, int32_t me, xy_obs* obs)
+{
+    const xyd::Params4 p = quad_params(q);
+    const int64_t cap = me ? ((int64_t)1 << 30) / me * me : ((int64_t)1 << 30);
+    for (int64_t done = 0; done < n_sweeps;) {
+        const int64_t m = std::min<int64_t>(cap, n_sweeps - done);
+        hipError_t e = XY_LAUNCH(xyk::launch_resident_quad(q->state, q->L, (uint32_t)q->sweep, p, (int)m, me,
+                                                           me ? obs + done / me * 4 : nullptr, q->stream));
+        if (e != hipSuccess) return xyr::hip_fail(e, "xy_quad_sweep: launch");
+        q->sweep += (uint64_t)m;
+        done += m;
+    }
+    return XY_OK;
+}
+
+// Passes of several sweeps from `state` to the ping-pong buffer and back, an even
+// number of them, as a single lattice's (deep_sweeps of the lattice calls).
+static int quad_deep_sweeps(xy_quad* q, const xyk::DeepPlan& plan, int nmax, int64_t n_sweeps, int32_t me, xy_obs* obs)
+{
+    const xyd::Params4 p = quad_params(q);
+    const int np = plan.tx * plan.ty, room = (int)(quad_max_records(q->L) / 4 / np);
+    // a pass measures no more sweeps than the workspace holds records of
+    if (me && (int64_t)room * me < nmax) nmax = room * me;
+    const int64_t passes = ((n_sweeps + nmax - 1) / nmax + 1) / 2 * 2;
+    const uint64_t base = q->sweep;
+    int held = 0;            // sweeps whose partials wait in the workspace
+    int64_t out = 0, j = 0;  // sweeps whose records are written, sweeps done
+    auto flush = [&] {
+        if (held == 0) return hipSuccess;
+        hipError_t e = xyk::launch_finalize_many(q->partials, np, 4 * held, obs + out * 4,
+                                                 base + (uint64_t)(out + 1) * (uint64_t)me, me, q->stream, 4);
+        out += held;
+        held = 0;
+        return e;
+    };
+    for (int64_t k = 0; k < passes; ++k) {
+        const int n = (int)(n_sweeps / passes + (k < n_sweeps % passes));
+        const int phase = me ? (int)(j % me) : 0, nrec = me ? (int)((j + n) / me - j / me) : 0;
+        hipError_t e = held + nrec > room ? XY_LAUNCH(flush()) : hipSuccess;
+        if (e == hipSuccess) {
+            xyk::DeepPlan d = plan;
+            e = xyk::deep_region(q->L, n, &d)
+                    ? XY_LAUNCH(xyk::launch_deep_quad((k & 1) ? q->pingpong : q->state,
+                                                      (k & 1) ? q->state : q->pingpong, q->L, (uint32_t)q->sweep, p, d,
+                                                      n, me, phase, q->partials + (size_t)held * 4 * np * 8, q->stream))
+                    : hipErrorInvalidValue;
+        }
+        if (e != hipSuccess) {
+            const int rc = xyr::hip_fail(e, "xy_quad_sweep: launch");
+            (void)flush();
+            if (k & 1)       // so that the state agrees with the counter
+                (void)hipMemcpyAsync(q->state, q->pingpong, quad_state_bytes(q->L), hipMemcpyDeviceToDevice, q->stream);
+            return rc;
+        }
+        held += nrec;
+        j += n;
+        q->sweep += (uint64_t)n;
+    }
+    hipError_t e = XY_LAUNCH(flush());
+    return e == hipSuccess ? XY_OK : xyr::hip_fail(e, "xy_quad_sweep: finalize");
+}
+
+// Single sweeps of the four lattices apart.  The first sweep writes them (into the
+// second buffer), the last reads them; a copy takes the place of the last where
+// n_sweeps is odd, of both where every sweep is measured.  The sweeps between are an
+// even number, so the angles end in the caller's buffer.
+static int quad_plane_sweeps(xy_quad* q, int64_t n_sweeps, int32_t me, xy_obs* obs)
+{
+    const xyd::Params4 p = quad_params(q);
+    auto measured = [&](int64_t j) { return me > 0 && j % me == 0; };     // j = 1-based sweep in call
+    const bool first = (n_sweeps & 1) || !measured(1), last = !(n_sweeps & 1) && first;
+    int where = 0;           // the angles: 0 state, 1 lattices in pingpong, 2 lattices in state
+    int64_t j = 0;
+    auto sweep = [&](hipError_t e, int to, int nrec) {
+        if (e != hipSuccess) return e;
+        where = to;
+        ++j;
+        q->sweep += 1;
+        if (!measured(j)) return hipSuccess;
+        return XY_LAUNCH(xyk::launch_finalize_quad(q->partials, nrec, obs + (j / me - 1) * 4, q->sweep, q->chunks,
+                                                   q->arrive, q->stream));
+    };
+    auto convert = [&](bool in) {
+        const int tiles = (q->L / q->tile_x) * (q->L / q->tile_y);
+        return sweep(XY_LAUNCH(xyk::launch_quad_convert(in ? q->pingpong : q->state, in ? q->state : q->pingpong, q->L,
+                                                        (uint32_t)q->sweep, p, in, measured(j + 1), q->partials,
+                                                        q->stream)),
+                     in ? 0 : 1, 4 * tiles);
+    };
+    hipError_t e;
+    if (first) {
+        e = convert(false);
+    } else {
+        e = XY_LAUNCH(xyk::launch_quad_split(q->state, (float*)q->pingpong, q->L, q->stream));
+        if (e == hipSuccess) where = 1;
+    }
+    while (e == hipSuccess && j < n_sweeps - (last ? 1 : 0)) {
+        const bool back = where == 1;
+        e = sweep(XY_LAUNCH(xyk::launch_planes((const float*)(back ? q->pingpong : q->state),
+                                               (float*)(back ? q->state : q->pingpong), q->L, (uint32_t)q->sweep, p,
+                                               measured(j + 1), q->partials, q->stream)),
+                  back ? 2 : 1, xyk::planes_records(q->L));
+    }
+    if (e == hipSuccess && last) e = convert(true);
+    const int rc = e == hipSuccess ? XY_OK : xyr::hip_fail(e, "xy_quad_sweep: launch");
+    // also after a failed launch, so that the state agrees with the counter
+    if (where == 2)
+        (void)hipMemcpyAsync(q->pingpong, q->state, quad_state_bytes(q->L), hipMemcpyDeviceToDevice, q->stream);
+    if (where != 0) {
+        e = xyk::launch_quad_join((const float*)q->pingpong, q->state, q->L, q->stream);
+        if (rc == XY_OK && e != hipSuccess) return xyr::hip_fail(e, "xy_quad_sweep: launch");
+    }
+    return rc;
 }
 
 extern "C" {
@@ -217,6 +430,7 @@ int xy_quad_init(xy_quad** out, const uint64_t* seeds, int32_t L, const double* 
     q->sweep = 0;
     q->tile_x = L % 128 == 0 ? 128 : 32;
     q->tile_y = L % 128 == 0 ? 8 : 16;
+    q->tile_set = false;
     q->hmc_steps = kQuadHmcSteps;
     const int Hh = L / 2, P = (Hh + 1) / 2;
     hipLaunchKernelGGL(xyk::k_quad_init, dim3((P + 63) / 64, (L + 3) / 4, 2), dim3(64, 4), 0, q->stream, q->state, L,
@@ -238,6 +452,18 @@ int xy_quad_sweep(xy_quad* q, int64_t n_sweeps, int32_t measure_every, xy_obs* o
     if (n_sweeps < 0 || measure_every < 0) return XY_EINVAL;
     if (q->sweep + (uint64_t)n_sweeps >= 0xffffffffull) return XY_ERANGE;
     const bool meas = measure_every > 0 && obs_dev != nullptr;
+    // Where no tile was asked for: the whole quad in four workgroups, passes of
+    // several sweeps, or single sweeps of the lattices apart (a single sweep gains
+    // nothing from the latter two).
+    if (!q->tile_set && n_sweeps > 0) {
+        const int32_t me = meas ? measure_every : 0;
+        xyk::DeepPlan plan;
+        int nmax;
+        if (q->L == 32) return quad_resident_sweeps(q, n_sweeps, me, obs_dev);
+        if (n_sweeps > 1 && xyk::deep_choose_quad(q->L, &plan, &nmax))
+            return quad_deep_sweeps(q, plan, nmax, n_sweeps, me, obs_dev);
+        if (n_sweeps > 1 && q->L >= 256) return quad_plane_sweeps(q, n_sweeps, me, obs_dev);
+    }
     const xyd::Params4 p = quad_params(q);
     const int ntiles = (q->L / q->tile_x) * (q->L / q->tile_y);
     const int nrec = ntiles * 4;                      // records per replica
@@ -302,6 +528,7 @@ int xy_quad_set_tile(xy_quad* q, int32_t tile_x, int32_t tile_y)
     if (!xyk::quad_shape_ok(q->L, tile_x, tile_y)) return XY_EINVAL;
     q->tile_x = tile_x;
     q->tile_y = tile_y;
+    q->tile_set = true;
     return XY_OK;
 }
 

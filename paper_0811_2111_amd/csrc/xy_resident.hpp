@@ -35,7 +35,7 @@ __device__ __forceinline__ void resident_program(const T* __restrict__ src, T* _
     g.PC = g.cp = g.P;
     g.RY = g.cr = L;
     if (obs == nullptr) me = 0;
-    deep_program<T, NT, R, ODD, true, MEAS>(src, dst, g, sweep0, n, me, 0, 0, 0, k0, k1, p, smem, [&](int k, double s) {
+    deep_program<T, NT, R, ODD, true, MEAS, false>(src, dst, g, sweep0, n, me, 0, 0, 0, k0, k1, p, smem, [&](int k, double s) {
         // xy_obs: sweep, n_accept, then the six sums, eight bytes each
         const int t = (int)threadIdx.x;
         const uint64_t after = (uint64_t)sweep0 + (uint64_t)(k + 1) * (uint64_t)me;

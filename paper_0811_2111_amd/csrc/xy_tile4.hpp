@@ -46,9 +46,59 @@ __device__ __forceinline__ void st4(__amdgpu_buffer_rsrc_t rs, unsigned entry, f
                                            entry * 16u, 0, 0);
 }
 
+// A pair of entries (at, at + 1) of all four replicas, from the float4 state or
+// (PL) from four lattices of `plane` bytes each, back to back.
+template <bool PL>
+__device__ __forceinline__ void ld4_pair(__amdgpu_buffer_rsrc_t rs, unsigned at, unsigned plane, float4& a, float4& b)
+{
+    if constexpr (PL) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float2 v = __builtin_bit_cast(
+                float2, __builtin_amdgcn_raw_buffer_load_b64(rs, at * 4u, (unsigned)r * plane, 0));
+            f4set(a, r, v.x);
+            f4set(b, r, v.y);
+        }
+    } else {
+        a = ld4(rs, at);
+        b = ld4(rs, at + 1u);
+    }
+}
+template <bool PL>
+__device__ __forceinline__ void st4_pair(__amdgpu_buffer_rsrc_t rs, unsigned at, unsigned plane, const float4& a,
+                                         const float4& b)
+{
+    if constexpr (PL) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            __builtin_amdgcn_raw_buffer_store_b64(
+                __builtin_bit_cast(xu2, make_float2(f4c(a, r), f4c(b, r))), rs, at * 4u, (unsigned)r * plane, 0);
+    } else {
+        st4(rs, at, a);
+        st4(rs, at + 1u, b);
+    }
+}
+template <bool PL>
+__device__ __forceinline__ float4 ld4_one(__amdgpu_buffer_rsrc_t rs, unsigned at, unsigned plane)
+{
+    float4 v;
+    if constexpr (PL) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            f4set(v, r, __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, at * 4u, (unsigned)r * plane, 0)));
+    } else {
+        v = ld4(rs, at);
+    }
+    return v;
+}
+
 // LDS entry: cosines and sines of the four replicas.
 struct CS4 {
     float4 c, s;
+};
+
+struct T4Geom : T1Geom {
+    unsigned plane;     // bytes of one replica's lattice, where the replicas are apart
 };
 
 template <int TX, int TY, int NT>
@@ -149,8 +199,8 @@ __device__ __forceinline__ void meas_acc4(MeasAcc4& m, const CS4& b, const CS4& 
 
 // Red half-sweep; O = parity of this thread's red rows (left/right neighbours of
 // entry k are the other colour's entries k + O - 1 and k + O).
-template <int TX, int TY, int NT, int O, bool KEEP>
-__device__ __forceinline__ int tile4_red(const T1Geom& g, Lds4<Tile4<TX, TY, NT>> cs, __amdgpu_buffer_rsrc_t src,
+template <int TX, int TY, int NT, int O, bool KEEP, bool IN, bool OUT>
+__device__ __forceinline__ int tile4_red(const T4Geom& g, Lds4<Tile4<TX, TY, NT>> cs, __amdgpu_buffer_rsrc_t src,
                                          __amdgpu_buffer_rsrc_t dst, uint32_t sweep, const Params4& p, float4 the,
                                          int e, int e_row, int e_col, int e_red, int e_k,
                                          const float4 (&tr)[Tile4<TX, TY, NT>::NQR][2])
@@ -174,8 +224,7 @@ __device__ __forceinline__ int tile4_red(const T1Geom& g, Lds4<Tile4<TX, TY, NT>
             ta = tr[q][0];
             tb = tr[q][1];
         } else {
-            ta = ld4(src, at);
-            tb = ld4(src, at + 1u);
+            ld4_pair<IN>(src, at, g.plane, ta, tb);
         }
         u32x4 w[4];
 #pragma unroll
@@ -192,8 +241,7 @@ __device__ __forceinline__ int tile4_red(const T1Geom& g, Lds4<Tile4<TX, TY, NT>
         cs.put(row, c0 + 1, b);
         if (q < FULL || (row >= 1 && row <= TY)) {     // halo rows only feed the black half-sweep
             acc += ac;
-            st4(dst, at, ta);
-            st4(dst, at + 1u, tb);
+            st4_pair<OUT>(dst, at, g.plane, ta, tb);
         }
         // eight updates per item are enough independent work; keeping the items
         // apart holds the live registers to one item's
@@ -225,8 +273,8 @@ __device__ __forceinline__ int tile4_red(const T1Geom& g, Lds4<Tile4<TX, TY, NT>
 }
 
 // Black half-sweep of the interior rows; O = parity of this thread's black rows.
-template <int TX, int TY, int NT, int O, bool MEAS, bool KEEP>
-__device__ __forceinline__ int tile4_black(const T1Geom& g, Lds4<Tile4<TX, TY, NT>> cs, __amdgpu_buffer_rsrc_t src,
+template <int TX, int TY, int NT, int O, bool MEAS, bool KEEP, bool IN, bool OUT>
+__device__ __forceinline__ int tile4_black(const T4Geom& g, Lds4<Tile4<TX, TY, NT>> cs, __amdgpu_buffer_rsrc_t src,
                                            __amdgpu_buffer_rsrc_t dst, uint32_t sweep, const Params4& p, MeasAcc4& m,
                                            const float4 (&tb)[Tile4<TX, TY, NT>::NQB][2])
 {
@@ -246,8 +294,7 @@ __device__ __forceinline__ int tile4_black(const T1Geom& g, Lds4<Tile4<TX, TY, N
             t0 = tb[q][0];
             t1 = tb[q][1];
         } else {
-            t0 = ld4(src, at);
-            t1 = ld4(src, at + 1u);
+            ld4_pair<IN>(src, at, g.plane, t0, t1);
         }
         u32x4 w[4];
 #pragma unroll
@@ -260,8 +307,7 @@ __device__ __forceinline__ int tile4_black(const T1Geom& g, Lds4<Tile4<TX, TY, N
         CS4 a = cs.get(S::RR + row, c0), b = cs.get(S::RR + row, c0 + 1);
         const CS4 la = O ? h0 : side, ra = O ? h1 : h0, lb = O ? h1 : h0, rb = O ? side : h1;
         acc += pair_update4(t0, t1, a, b, la, ra, u0, d0, lb, rb, u1, d1, w, p);
-        st4(dst, at, t0);
-        st4(dst, at + 1u, t1);
+        st4_pair<OUT>(dst, at, g.plane, t0, t1);
         if constexpr (MEAS) {
             meas_acc4(m, a, la, ra, u0, d0);
             meas_acc4(m, b, lb, rb, u1, d1);
@@ -274,9 +320,10 @@ __device__ __forceinline__ int tile4_black(const T1Geom& g, Lds4<Tile4<TX, TY, N
 // One tile of a four-replica lattice; src/dst are the two float4 state buffers.
 // MEAS: one partial record per wave and replica, replica-major:
 // part[(r * rec_stride + wave) * 8 ..] = (Cx, Cy, Ix, Iy, Mx, My, accepts, 0)
-// of replica r, `part` already offset to this tile's first wave.
-template <int TX, int TY, int NT, bool MEAS>
-__device__ __forceinline__ void tile4_program(const float4* __restrict__ src, float4* __restrict__ dst,
+// of replica r, `part` already offset to this tile's first wave.  IN, OUT: src, dst
+// holds the replicas as four lattices back to back instead.
+template <int TX, int TY, int NT, bool MEAS, bool IN, bool OUT>
+__device__ __forceinline__ void tile4_program(const void* __restrict__ src, void* __restrict__ dst,
                                               unsigned state_bytes, int L, int x0, int y0, uint32_t sweep,
                                               const Params4& p, double* part, size_t rec_stride, char* smem)
 {
@@ -286,7 +333,8 @@ __device__ __forceinline__ void tile4_program(const float4* __restrict__ src, fl
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(src, state_bytes);
     const __amdgpu_buffer_rsrc_t rd = make_rsrc(dst, state_bytes);
 
-    T1Geom g;
+    T4Geom g;
+    g.plane = state_bytes >> 2;
     g.L = L;
     g.Hh = L >> 1;
     g.P = g.Hh >> 1;
@@ -309,8 +357,7 @@ __device__ __forceinline__ void tile4_program(const float4* __restrict__ src, fl
         if (red_valid<S>(g, q)) {
             const int yr = y0 - 1 + red_row<S>(g, q);
             const unsigned base = (unsigned)(g.edge_tile ? wrapi(yr, L) : yr) * (unsigned)g.Hh + col;
-            tr[q][0] = ld4(rs, base);
-            tr[q][1] = ld4(rs, base + 1u);
+            ld4_pair<IN>(rs, base, g.plane, tr[q][0], tr[q][1]);
         }
     }
 #pragma unroll
@@ -318,8 +365,7 @@ __device__ __forceinline__ void tile4_program(const float4* __restrict__ src, fl
         if (black_valid<S>(g, q)) {
             const int yb = y0 - 2 + black_row<S>(g, q);
             const unsigned base = ((unsigned)L + (unsigned)(g.edge_tile ? wrapi(yb, L) : yb)) * (unsigned)g.Hh + col;
-            tb[q][0] = ld4(rs, base);
-            tb[q][1] = ld4(rs, base + 1u);
+            ld4_pair<IN>(rs, base, g.plane, tb[q][0], tb[q][1]);
         }
     }
     const int e = NT - 1 - tid;
@@ -340,8 +386,8 @@ __device__ __forceinline__ void tile4_program(const float4* __restrict__ src, fl
         }
         e_k = side ? g.kb + TX / 2 : g.kb - 1;
         e_col = side ? TX / 2 + 2 : 1;
-        the = ld4(rs, ((unsigned)(e_red ? 0 : L) + (unsigned)wrapi(yl, L)) * (unsigned)g.Hh +
-                          (unsigned)wrapi(e_k, g.Hh));
+        the = ld4_one<IN>(rs, ((unsigned)(e_red ? 0 : L) + (unsigned)wrapi(yl, L)) * (unsigned)g.Hh +
+                                  (unsigned)wrapi(e_k, g.Hh), g.plane);
     }
 #pragma unroll
     for (int q = 0; q < S::NQR; ++q)
@@ -370,14 +416,14 @@ __device__ __forceinline__ void tile4_program(const float4* __restrict__ src, fl
     int acc = 0;
     const bool red_odd = __builtin_amdgcn_readfirstlane((y0 + g.rt) & 1) != 0;
     if (red_odd)
-        acc += tile4_red<TX, TY, NT, 1, KEEP>(g, cs, rs, rd, sweep, p, the, e, e_row, e_col, e_red, e_k, tr);
+        acc += tile4_red<TX, TY, NT, 1, KEEP, IN, OUT>(g, cs, rs, rd, sweep, p, the, e, e_row, e_col, e_red, e_k, tr);
     else
-        acc += tile4_red<TX, TY, NT, 0, KEEP>(g, cs, rs, rd, sweep, p, the, e, e_row, e_col, e_red, e_k, tr);
+        acc += tile4_red<TX, TY, NT, 0, KEEP, IN, OUT>(g, cs, rs, rd, sweep, p, the, e, e_row, e_col, e_red, e_k, tr);
     __syncthreads();
     if (red_odd)
-        acc += tile4_black<TX, TY, NT, 0, MEAS, KEEP>(g, cs, rs, rd, sweep, p, m, tb);
+        acc += tile4_black<TX, TY, NT, 0, MEAS, KEEP, IN, OUT>(g, cs, rs, rd, sweep, p, m, tb);
     else
-        acc += tile4_black<TX, TY, NT, 1, MEAS, KEEP>(g, cs, rs, rd, sweep, p, m, tb);
+        acc += tile4_black<TX, TY, NT, 1, MEAS, KEEP, IN, OUT>(g, cs, rs, rd, sweep, p, m, tb);
     if constexpr (MEAS) {
         const int lane = tid & 63, wv = tid >> 6;
 #pragma unroll
