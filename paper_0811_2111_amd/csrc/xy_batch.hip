@@ -44,6 +44,7 @@
 
 #include "xy.h"
 #include "xy_launch.hpp"
+#include "xy_reduce.hpp"
 #include "xy_resident.hpp"
 #include "xy_runtime.hpp"
 #include "xy_tile.hpp"
@@ -213,34 +214,11 @@ __device__ __forceinline__ int xlattice_of(const LatDesc* d, const int* ord, int
 }
 
 // Reduce the partials of lattice i for one measured pass (fixed order) into its record.
-template <int NT>
+// By a workgroup of 256 threads.
 __device__ void reduce_lattice(const LatDesc& d, const double* part, xy_obs* out, uint64_t sweep_after, double* red)
 {
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int t = threadIdx.x; t < d.ntiles; t += NT) {
-        const double* q = part + (size_t)(d.first_tile + t) * 8;
-#pragma unroll
-        for (int k = 0; k < 7; ++k) v[k] += q[k];
-    }
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < 7; ++k) v[k] = wave_sum(v[k]);
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < 7; ++k) red[wid * 7 + k] = v[k];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s[7];
-        for (int k = 0; k < 7; ++k) {
-            s[k] = 0.0;
-            for (int w = 0; w < NT / 64; ++w) s[k] += red[w * 7 + k];
-        }
-        xy_obs o;
-        o.sweep = sweep_after;
-        o.n_accept = (uint64_t)s[6];
-        o.cx = s[0]; o.cy = s[1]; o.ix = s[2]; o.iy = s[3]; o.mx = s[4]; o.my = s[5];
-        *out = o;
-    }
+    const double s = column_sums(part + (size_t)d.first_tile * 8, d.ntiles, red);
+    put_record(out, s, sweep_after, 0ull);
     __syncthreads();
 }
 
@@ -312,8 +290,9 @@ k_batch(T* __restrict__ state, T* __restrict__ pp, const LatDesc* __restrict__ l
     auto reduce_if_owner = [&](const LatDesc& d, int i, int p) {
         if (measured(p - 1) && t0 <= d.xfirst && d.xfirst < t1) {
             all_wait(tdone + d.first_tile, d.ntiles, (unsigned)p, ctrl);
-            reduce_lattice<NT>(d, slots(p - 1), obs + (size_t)i * nrec + (p / measure_every - 1),
-                               (uint64_t)sweep0 + (uint64_t)p, red);
+            static_assert(NT == 256);
+            reduce_lattice(d, slots(p - 1), obs + (size_t)i * nrec + (p / measure_every - 1),
+                           (uint64_t)sweep0 + (uint64_t)p, red);
             if (threadIdx.x == 0) __hip_atomic_fetch_add(&rdone[i], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     };
@@ -517,10 +496,10 @@ __global__ void __launch_bounds__(256)
 k_batch_reduce(const LatDesc* __restrict__ lat, const Ctrl* __restrict__ ctrl, int p, const double* __restrict__ part,
                xy_obs* __restrict__ obs, int nrec, int r)
 {
-    __shared__ double red[4 * 7];
+    __shared__ double red[32];
     const int i = (int)blockIdx.x;
     if (lat[i].resident) return;
-    reduce_lattice<256>(lat[i], part, obs + (size_t)i * nrec + r, (uint64_t)ctrl->sweep0 + (uint64_t)p + 1u, red);
+    reduce_lattice(lat[i], part, obs + (size_t)i * nrec + r, (uint64_t)ctrl->sweep0 + (uint64_t)p + 1u, red);
 }
 
 // The LDS-resident lattices of a per-sweep call: workgroup b runs every sweep of

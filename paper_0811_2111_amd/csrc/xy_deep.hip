@@ -272,22 +272,10 @@ hipError_t launch_resident_quad(float4* state, int L, uint32_t sweep, const Para
 __global__ void __launch_bounds__(256)
 k_finalize_many(const double* __restrict__ part, int np, xy_obs* __restrict__ out, uint64_t first, int every, int group)
 {
-    __shared__ double red[4 * 7];
+    __shared__ double red[32];
     const int k = (int)blockIdx.x;
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int i = threadIdx.x; i < np; i += 256) {
-        const double* q = part + ((size_t)k * np + i) * 8;
-#pragma unroll
-        for (int c = 0; c < 7; ++c) v[c] += q[c];
-    }
-    block_sum7_256(v, red);
-    if (threadIdx.x == 0) {
-        xy_obs o;
-        o.sweep = first + (uint64_t)(k / group) * (uint64_t)every;
-        o.n_accept = (unsigned long long)v[6];
-        o.cx = v[0]; o.cy = v[1]; o.ix = v[2]; o.iy = v[3]; o.mx = v[4]; o.my = v[5];
-        out[k] = o;
-    }
+    const double s = column_sums(part + (size_t)k * np * 8, np, red);
+    put_record(out + k, s, first + (uint64_t)(k / group) * (uint64_t)every, 0ull);
 }
 
 hipError_t launch_finalize_many(const double* part, int np, int nrec, xy_obs* out, uint64_t first, int every,

@@ -364,11 +364,9 @@ __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __res
                 deep_chains<NT>(red, blk, WS, g, rp, full, v);
             }
             v[6] = (double)acc;
-#pragma unroll
-            for (int q = 0; q < 7; ++q) v[q] = wave_sum_last(v[q]);
-            if (lane == 63)
-#pragma unroll
-                for (int q = 0; q < 7; ++q) sum[w * 7 + q] = v[q];
+            const double s = wave_sum7(v);
+            const int slot = wave_slot();
+            if ((tid & 7) == 0 && slot < 7) sum[w * 7 + slot] = s;
             until = me;
         }
         __syncthreads();
@@ -378,6 +376,7 @@ __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __res
             if (tid < 8) {
                 double s = 0.0;
                 if (tid < 7)
+#pragma unroll
                     for (int k = 0; k < NT / 64; ++k) s += sum[k * 7 + tid];
                 put(rec, s);
             }

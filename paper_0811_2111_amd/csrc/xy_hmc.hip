@@ -59,16 +59,9 @@ __device__ __forceinline__ Nb load_nb(const float* __restrict__ st, int L, int H
 // One partial record per wave: (Cx, Cy, Ix, Iy, Mx, My, K, 0).  Black sites add
 // their four bonds, their own spin and that of the red site to their right (as
 // the Metropolis measurement does); every site adds p^2 / 2.
-__device__ __forceinline__ void write_record(double v[7], double* __restrict__ rec, unsigned b)
+__device__ __forceinline__ void write_record(const double (&v)[7], double* __restrict__ rec, unsigned b)
 {
-#pragma unroll
-    for (int q = 0; q < 7; ++q) v[q] = wave_sum_last(v[q]);
-    if ((threadIdx.x & 63) == 63) {
-        double* r = rec + ((size_t)b * (kThreads / 64) + (threadIdx.x >> 6)) * 8;
-#pragma unroll
-        for (int q = 0; q < 7; ++q) r[q] = v[q];
-        r[7] = 0.0;
-    }
+    wave_record(v, rec + ((size_t)b * (kThreads / 64) + (threadIdx.x >> 6)) * 8);
 }
 
 __device__ __forceinline__ void accumulate(double v[7], const Nb& n, int c, float kin)
@@ -402,26 +395,6 @@ k_hmc_ends2(const float* __restrict__ st, float* __restrict__ p, float* __restri
     ends2_body<BEGIN>(st, p, copy, L, traj, k0, k1, nbeta_kick, cols, rb, rec, xcd_band(blockIdx.x, gridDim.x));
 }
 
-// Sum of one set of records in a fixed order (thread t: records t, t + 256, ...,
-// then the wave sums and the four waves in order); thread 0 gets the totals.
-__device__ void sum_records(const double* __restrict__ rec, int nrec, double out[7], double* red)
-{
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int r = threadIdx.x; r < nrec; r += kThreads)
-#pragma unroll
-        for (int q = 0; q < 7; ++q) v[q] += rec[(size_t)r * 8 + q];
-#pragma unroll
-    for (int q = 0; q < 7; ++q) v[q] = wave_sum(v[q]);
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-        for (int q = 0; q < 7; ++q) red[(threadIdx.x >> 6) * 7 + q] = v[q];
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int q = 0; q < 7; ++q) out[q] = (red[q] + red[7 + q]) + (red[14 + q] + red[21 + q]);
-    __syncthreads();
-}
-
 // Metropolis step of the trajectory.  Workgroup b sums chunk b % nchunk (256
 // records) of the old records, or of the new ones from nchunk on; the one that
 // arrives last (a counter behind the flag, zeroed by the begin kernel; released and
@@ -432,32 +405,27 @@ __device__ __forceinline__ void decide_body(const double* __restrict__ rec_old, 
                                             double* __restrict__ chunk_new, double beta, uint32_t traj, uint32_t k0,
                                             uint32_t k1, unsigned* __restrict__ flag, xy_hmc_obs* __restrict__ obs)
 {
-    __shared__ double red[4 * 7];
+    __shared__ double red[64], sums[16];
     __shared__ int last;
     const bool fresh = (int)blockIdx.x >= nchunk;
-    const int ch = (int)blockIdx.x - (fresh ? nchunk : 0), i = ch * 256 + (int)threadIdx.x;
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    if (i < nrec) {
-        const double* q = (fresh ? rec_new : rec_old) + (size_t)i * 8;
-#pragma unroll
-        for (int k = 0; k < 7; ++k) v[k] = q[k];
-    }
-    block_sum7_256(v, red);
-    if (threadIdx.x == 0) {
-        double* o = (fresh ? chunk_new : chunk_old) + (size_t)ch * 8;
-#pragma unroll
-        for (int k = 0; k < 7; ++k) o[k] = v[k];
-        o[7] = 0.0;
+    const int ch = (int)blockIdx.x - (fresh ? nchunk : 0), i = ch * 256;
+    const double s = column_sums((fresh ? rec_new : rec_old) + (size_t)i * 8, min(256, nrec - i), red);
+    if (threadIdx.x < 8) {
+        (fresh ? chunk_new : chunk_old)[(size_t)ch * 8 + threadIdx.x] = s;
         __threadfence();
-        last = atomicAdd(flag + 1, 1u) == gridDim.x - 1u;
+        // lanes of one wave: the stores above are done before lane 0's arrival
+        if (threadIdx.x == 0) last = atomicAdd(flag + 1, 1u) == gridDim.x - 1u;
     }
     __syncthreads();
     if (!last) return;
     __threadfence();
-    double o[7], n[7];
-    sum_records(chunk_old, nchunk, o, red);
-    sum_records(chunk_new, nchunk, n, red);
-    if (threadIdx.x == 0) decide_core(o, n, beta, traj, k0, k1, flag, obs);
+    const double o = column_sums(chunk_old, nchunk, red), n = column_sums(chunk_new, nchunk, red + 32);
+    if (threadIdx.x < 8) {
+        sums[threadIdx.x] = o;
+        sums[8 + threadIdx.x] = n;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) decide_core(sums, sums + 8, beta, traj, k0, k1, flag, obs);
 }
 
 __global__ void __launch_bounds__(kThreads)
@@ -609,41 +577,35 @@ k_bhmc_pass(const BhLat* __restrict__ d, const uint32_t* __restrict__ start, int
 }
 
 // One lattice's records summed as the single-lattice trajectory sums them: chunks
-// of 256 records as k_reduce_chunks forms them (into ch, LDS), then the chunk sums
-// as k_hmc_decide forms them.  Thread 0 gets the totals.
-__device__ void bh_sum(const double* __restrict__ rec, int nrec, double* ch, double out[7], double* red)
+// of 256 records (into ch, LDS), then the chunk sums.  Threads 0 .. 7 get their
+// column's total.
+__device__ double bh_sum(const double* __restrict__ rec, int nrec, double* ch, double* red)
 {
     const int nch = (nrec + 255) / 256;
     for (int c = 0; c < nch; ++c) {
-        const int i = c * 256 + threadIdx.x;
-        double v[7] = {0, 0, 0, 0, 0, 0, 0};
-        if (i < nrec) {
-            const double* r = rec + (size_t)i * 8;
-#pragma unroll
-            for (int k = 0; k < 7; ++k) v[k] = r[k];
-        }
-        block_sum7_256(v, red);
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int k = 0; k < 7; ++k) ch[c * 8 + k] = v[k];
-            ch[c * 8 + 7] = 0.0;
-        }
-        __syncthreads();
+        const double s = column_sums(rec + (size_t)c * 256 * 8, min(256, nrec - c * 256), red + (c & 1) * 32);
+        if (threadIdx.x < 8) ch[c * 8 + threadIdx.x] = s;
     }
-    sum_records(ch, nch, out, red);
+    __syncthreads();
+    return column_sums(ch, nch, red);
 }
 
 // Metropolis step of every lattice: workgroup i on lattice i.
 __global__ void __launch_bounds__(kThreads)
 k_bhmc_decide(const BhLat* __restrict__ d, const uint32_t* __restrict__ traj_dev)
 {
-    __shared__ double red[4 * 7];
+    __shared__ double red[64], sums[16];
     __shared__ double ch[kHmcMaxChunks * 8];
     const BhLat& q = d[blockIdx.x];
-    double o[7], nn[7];
-    bh_sum(q.w.rec_old, q.nrec, ch, o, red);
-    bh_sum(q.w.rec_new, q.nrec, ch, nn, red);
-    if (threadIdx.x == 0) decide_core(o, nn, q.beta, *traj_dev, q.k0, q.k1, q.w.flag, q.obs);
+    const double o = bh_sum(q.w.rec_old, q.nrec, ch, red);
+    __syncthreads();
+    const double n = bh_sum(q.w.rec_new, q.nrec, ch, red);
+    if (threadIdx.x < 8) {
+        sums[threadIdx.x] = o;
+        sums[8 + threadIdx.x] = n;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) decide_core(sums, sums + 8, q.beta, *traj_dev, q.k0, q.k1, q.w.flag, q.obs);
 }
 
 // Rejected trajectories: the saved angles back into the state.

@@ -288,50 +288,27 @@ hipError_t launch_measure(const void* st, int L, int precision, double* partials
 
 // Fixed-order reduction of nparts partial records (8 doubles: six sums, accepts,
 // unused) -> one xy_obs.  Large counts take two levels: k_reduce_chunks sums
-// consecutive chunks of 256 records (thread t takes record t of its chunk, then a
-// fixed tree, block_sum7_256), k_finalize sums the chunk results.  Both levels are
+// consecutive chunks of 256 records, k_finalize the chunk results (column_sums).  Both levels are
 // deterministic.
 
 __global__ void __launch_bounds__(256)
 k_reduce_chunks(const double* __restrict__ partials, int nparts, double* __restrict__ out)
 {
-    __shared__ double red[4 * 7];
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    if (i < nparts) {
-        const double* q = partials + (size_t)i * 8;
-#pragma unroll
-        for (int k = 0; k < 7; ++k) v[k] = q[k];
-    }
-    block_sum7_256(v, red);
-    if (threadIdx.x == 0) {
-        double* o = out + (size_t)blockIdx.x * 8;
-#pragma unroll
-        for (int k = 0; k < 7; ++k) o[k] = v[k];
-        o[7] = 0.0;
-    }
+    __shared__ double red[32];
+    const int i = (int)blockIdx.x * 256;
+    const double s = column_sums(partials + (size_t)i * 8, min(256, nparts - i), red);
+    if (threadIdx.x < 8) out[(size_t)blockIdx.x * 8 + threadIdx.x] = s;
 }
 
-__global__ void __launch_bounds__(256)
+template <int NT>
+__global__ void __launch_bounds__(NT)
 k_finalize(const double* __restrict__ partials, int nparts, unsigned long long* __restrict__ counter,
            xy_obs* __restrict__ out, uint64_t sweep_after)
 {
-    __shared__ double red[4 * 7];
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int i = threadIdx.x; i < nparts; i += 256) {
-        const double* q = partials + (size_t)i * 8;
-#pragma unroll
-        for (int k = 0; k < 7; ++k) v[k] += q[k];
-    }
-    block_sum7_256(v, red);
-    if (threadIdx.x == 0) {
-        xy_obs o;
-        o.sweep = sweep_after;
-        o.n_accept = (counter ? *counter : 0ull) + (unsigned long long)v[6];
-        o.cx = v[0]; o.cy = v[1]; o.ix = v[2]; o.iy = v[3]; o.mx = v[4]; o.my = v[5];
-        *out = o;
-        if (counter) *counter = 0ull;
-    }
+    __shared__ double red[NT / 8];
+    const double s = column_sums<NT>(partials, nparts, red);
+    put_record(out, s, sweep_after, counter && threadIdx.x == 6 ? *counter : 0ull);
+    if (counter && threadIdx.x == 6) *counter = 0ull;
 }
 
 hipError_t launch_reduce_chunks(const double* partials, int nparts, double* out, hipStream_t s)
@@ -354,48 +331,27 @@ k_reduce_finalize(const double* __restrict__ partials, int nparts, double* __res
                   unsigned* __restrict__ arrive, unsigned long long* __restrict__ counter, xy_obs* __restrict__ out,
                   uint64_t sweep_after)
 {
-    __shared__ double red[4 * 7];
+    __shared__ double red[32];
     __shared__ int last;
     partials += (size_t)blockIdx.y * nparts * 8;
     chunks += (size_t)blockIdx.y * gridDim.x * 8;
     arrive += blockIdx.y;
     out += blockIdx.y;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    if (i < nparts) {
-        const double* q = partials + (size_t)i * 8;
-#pragma unroll
-        for (int k = 0; k < 7; ++k) v[k] = q[k];
-    }
-    block_sum7_256(v, red);
-    if (threadIdx.x == 0) {
-        double* o = chunks + (size_t)blockIdx.x * 8;
-#pragma unroll
-        for (int k = 0; k < 7; ++k) o[k] = v[k];
-        o[7] = 0.0;
+    const int i = (int)blockIdx.x * 256;
+    const double s = column_sums(partials + (size_t)i * 8, min(256, nparts - i), red);
+    if (threadIdx.x < 8) {
+        chunks[(size_t)blockIdx.x * 8 + threadIdx.x] = s;
         __threadfence();
-        last = atomicAdd(arrive, 1u) == gridDim.x - 1u;
+        // lanes of one wave: the stores above are done before lane 0's arrival
+        if (threadIdx.x == 0) last = atomicAdd(arrive, 1u) == gridDim.x - 1u;
     }
     __syncthreads();
     if (!last) return;
     __threadfence();
-    const int nb = (int)gridDim.x;
-    double w[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int c = threadIdx.x; c < nb; c += 256) {
-        const double* q = chunks + (size_t)c * 8;
-#pragma unroll
-        for (int k = 0; k < 7; ++k) w[k] += q[k];
-    }
-    block_sum7_256(w, red);
-    if (threadIdx.x == 0) {
-        xy_obs o;
-        o.sweep = sweep_after;
-        o.n_accept = (counter ? *counter : 0ull) + (unsigned long long)w[6];
-        o.cx = w[0]; o.cy = w[1]; o.ix = w[2]; o.iy = w[3]; o.mx = w[4]; o.my = w[5];
-        *out = o;
-        if (counter) *counter = 0ull;
-        *arrive = 0u;
-    }
+    const double w = column_sums(chunks, (int)gridDim.x, red);
+    put_record(out, w, sweep_after, counter && threadIdx.x == 6 ? *counter : 0ull);
+    if (counter && threadIdx.x == 6) *counter = 0ull;
+    if (threadIdx.x == 0) *arrive = 0u;
 }
 
 hipError_t launch_finalize(const double* partials, int nparts, unsigned long long* counter, xy_obs* out,
@@ -408,9 +364,11 @@ hipError_t launch_finalize(const double* partials, int nparts, unsigned long lon
     } else if (nparts > 2048 && scratch) {
         const int nb = (nparts + 255) / 256;
         hipLaunchKernelGGL(k_reduce_chunks, dim3(nb), dim3(256), 0, s, partials, nparts, scratch);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, s, scratch, nb, counter, out, sweep_after);
+        hipLaunchKernelGGL(k_finalize<256>, dim3(1), dim3(256), 0, s, scratch, nb, counter, out, sweep_after);
+    } else if (nparts > 256) {
+        hipLaunchKernelGGL(k_finalize<1024>, dim3(1), dim3(1024), 0, s, partials, nparts, counter, out, sweep_after);
     } else {
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, s, partials, nparts, counter, out, sweep_after);
+        hipLaunchKernelGGL(k_finalize<256>, dim3(1), dim3(256), 0, s, partials, nparts, counter, out, sweep_after);
     }
     return hipGetLastError();
 }

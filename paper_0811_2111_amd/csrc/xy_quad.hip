@@ -95,7 +95,7 @@ hipError_t run_quad(const void* src, void* dst, int L, uint32_t sweep, const Par
 // bytes of (cos, sin) through LDS for every 4 updates' one, holds two to three times the
 // registers and runs three workgroups a CU to this one's four: measured, us a sweep
 // of all four, k_quad_fused against this: L = 1024 13.5 and 12.0, L = 2048 42.5 and
-// 31, L = 4096 160 and 123.5; measured sweeps 35 and 19 at L = 1024, 290 and 148 at
+// 31, L = 4096 160 and 123.5; measured sweeps 18 and 16 at L = 1024, 230 and 140 at
 // L = 4096.
 template <int TX, bool MEAS, bool ST>
 __global__ void __launch_bounds__(256)

@@ -353,16 +353,9 @@ __device__ __forceinline__ void strip_program(const T* __restrict__ src, T* __re
     }
 
     if constexpr (MEAS) {
-        double v[7] = {(double)m.cx, (double)m.cy, (double)m.ix, (double)m.iy, (double)m.mx, (double)m.my,
-                       (double)acc};
-#pragma unroll
-        for (int q = 0; q < 7; ++q) v[q] = wave_sum_last(v[q]);
-        if (lane == 63) {
-            double* o = part + (size_t)w * 8;
-#pragma unroll
-            for (int q = 0; q < 7; ++q) o[q] = v[q];
-            o[7] = 0.0;
-        }
+        const double v[7] = {(double)m.cx, (double)m.cy, (double)m.ix, (double)m.iy, (double)m.mx, (double)m.my,
+                             (double)acc};
+        wave_record(v, part + (size_t)w * 8);
     }
 }
 

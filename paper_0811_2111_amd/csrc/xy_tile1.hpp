@@ -154,27 +154,24 @@ struct Tile1 {
     static_assert(NEDGE <= NT, "edge columns must fit one pass");
     static constexpr int BLACK0 = RR * WS;             // black plane offset in LDS entries
     static constexpr size_t lds_bytes = (size_t)(RR + RB) * WS * sizeof(float2);
-    static constexpr size_t red_bytes = (size_t)NW * 7 * sizeof(double);
+    static constexpr size_t red_bytes = (size_t)NW * 8 * sizeof(double);
 };
 
-// 7-value workgroup sum in a fixed order; thread 0 receives the totals.
+// The workgroup's record of seven sums and a zero, in a fixed order; red: NT / 64 * 7
+// doubles of LDS.
 template <int NT>
-__device__ __forceinline__ void block_sum7(double v[7], double* red)
+__device__ __forceinline__ void block_record(const double (&v)[7], double* red, double* __restrict__ rec)
 {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int q = 0; q < 7; ++q) v[q] = wave_sum(v[q]);
-    if (lane == 0)
-#pragma unroll
-        for (int q = 0; q < 7; ++q) red[wid * 7 + q] = v[q];
+    const double s = wave_sum7(v);
+    const int slot = wave_slot();
+    if ((threadIdx.x & 7) == 0 && slot < 7) red[(threadIdx.x >> 6) * 7 + slot] = s;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 8) {
+        double t = 0.0;
+        if (threadIdx.x < 7)
 #pragma unroll
-        for (int q = 0; q < 7; ++q) {
-            double t = 0.0;
-            for (int w = 0; w < NT / 64; ++w) t += red[w * 7 + q];
-            v[q] = t;
-        }
+            for (int w = 0; w < NT / 64; ++w) t += red[w * 7 + threadIdx.x];
+        rec[threadIdx.x] = t;
     }
     __syncthreads();
 }
@@ -564,21 +561,9 @@ __device__ __forceinline__ void tile1_sweep(const T1Geom& g, float2* __restrict_
         }
         v[6] = (double)acc;
         if constexpr (MEAS > 0) {
-#pragma unroll
-            for (int q = 0; q < 7; ++q) v[q] = wave_sum_last(v[q]);
-            if ((tid & 63) == 63) {
-                double* w = part + (size_t)(tid >> 6) * 8;
-#pragma unroll
-                for (int q = 0; q < 7; ++q) w[q] = v[q];
-                w[7] = 0.0;
-            }
+            wave_record(v, part + (size_t)(tid >> 6) * 8);
         } else {
-            block_sum7<NT>(v, red);
-            if (tid == 0) {
-#pragma unroll
-                for (int q = 0; q < 7; ++q) part[q] = v[q];
-                part[7] = 0.0;
-            }
+            block_record<NT>(v, red, part);
         }
     } else {
         if (red_odd)

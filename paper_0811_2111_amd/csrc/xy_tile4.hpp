@@ -425,19 +425,11 @@ __device__ __forceinline__ void tile4_program(const void* __restrict__ src, void
     else
         acc += tile4_black<TX, TY, NT, 1, MEAS, KEEP, IN, OUT>(g, cs, rs, rd, sweep, p, m, tb);
     if constexpr (MEAS) {
-        const int lane = tid & 63, wv = tid >> 6;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            double v[7] = {(double)m.m[r].cx, (double)m.m[r].cy, (double)m.m[r].ix, (double)m.m[r].iy,
+            const double v[7] = {(double)m.m[r].cx, (double)m.m[r].cy, (double)m.m[r].ix, (double)m.m[r].iy,
                            (double)m.m[r].mx, (double)m.m[r].my, (double)((acc >> (8 * r)) & 0xff)};
-#pragma unroll
-            for (int q = 0; q < 7; ++q) v[q] = wave_sum_last(v[q]);
-            if (lane == 63) {
-                double* w = part + ((size_t)r * rec_stride + (size_t)wv) * 8;
-#pragma unroll
-                for (int q = 0; q < 7; ++q) w[q] = v[q];
-                w[7] = 0.0;
-            }
+            wave_record(v, part + ((size_t)r * rec_stride + (size_t)(tid >> 6)) * 8);
         }
     }
 }
