@@ -73,6 +73,14 @@ int fused_tiles(int L, int tile_x, int tile_y);
 int ragged_tile_x(int L);        // the faster width, 0 if the lattice is out of range
 int ragged_records(int L, int tile_x);
 hipError_t launch_ragged(const SweepArgs& a, int tile_x, bool meas, double* partials, hipStream_t s);
+// One sweep by strips of one wave (xy_walk.hip); measured: walk_records(L) partial
+// records.
+bool walk_supported(int L, int precision, bool meas);
+int walk_records(int L);
+hipError_t launch_walk(const SweepArgs& a, bool meas, double* partials, hipStream_t s);
+// An unmeasured sweep of the four lattices of a quad.
+bool walk_quad_supported(int L);
+hipError_t launch_walk_quad(const float* src, float* dst, int L, uint32_t sweep, const xyd::Params4& p, hipStream_t s);
 // Partial records one measured sweep of a fused launch writes (the sweep's
 // records start at partials + j * fused_records(...) * 8 for sub-sweep j).
 int fused_records(int L, int tile_x, int tile_y, int m);

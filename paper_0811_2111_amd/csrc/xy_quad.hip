@@ -95,7 +95,7 @@ hipError_t run_quad(const void* src, void* dst, int L, uint32_t sweep, const Par
 // bytes of (cos, sin) through LDS for every 4 updates' one, holds two to three times the
 // registers and runs three workgroups a CU to this one's four: measured, us a sweep
 // of all four, k_quad_fused against this: L = 1024 13.5 and 12.0, L = 2048 42.5 and
-// 31, L = 4096 160 and 123.5; measured sweeps 18 and 16 at L = 1024, 230 and 140 at
+// 32, L = 4096 160 and 123.5 (from L = 2800 the strips of xy_walk.hip, 115); measured sweeps 18 and 16 at L = 1024, 230 and 140 at
 // L = 4096.
 template <int TX, bool MEAS, bool ST>
 __global__ void __launch_bounds__(256)
@@ -152,6 +152,7 @@ int planes_records(int L) { return 4 * ((L + planes_tile_x(L) - 1) / planes_tile
 hipError_t launch_planes(const float* src, float* dst, int L, uint32_t sweep, const Params4& p, bool meas,
                          double* part, hipStream_t s)
 {
+    if (!meas && walk_quad_supported(L)) return launch_walk_quad(src, dst, L, sweep, p, s);
     const bool st = 2 * (size_t)L * L * sizeof(float4) > (size_t)256 << 20;     // beyond the MALL
 #define X(tx)                                                                                               \
     if (planes_tile_x(L) == tx)                                                                             \

@@ -447,8 +447,11 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
     if (own_schedule(h, n_sweeps, meas ? measure_every : 0, obs_dev, &own_rc)) return own_rc;
 
     // Where the plan is the library's choice, single sweeps take the faster of the
-    // ragged tiles in place of half-sweeps and, unmeasured, of a slower tile shape.
-    const int own_tx = h->own_plan && h->tcap == 0 ? xyk::ragged_tile_x(h->L) : 0;
+    // ragged tiles in place of half-sweeps and, unmeasured, of a slower tile shape,
+    // and large FP32 lattices strips of one wave.
+    const bool own = h->own_plan && h->tcap == 0;
+    const int own_tx = own ? xyk::ragged_tile_x(h->L) : 0;
+    auto walk = [&](bool meas_j) { return own && xyk::walk_supported(h->L, h->precision, meas_j); };
     const bool stream = h->plan.kind == XY_PLAN_STREAM;
 
     if (stream && !own_tx) {
@@ -474,7 +477,8 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
     const int m = strip ? 1 : h->plan.sweeps_per_pass;
     // (an odd last sweep is cheaper in place than with the copy back)
     const int64_t passes = stream && (n_sweeps & 1) && !measured(n_sweeps) ? n_sweeps - 1 : n_sweeps / m;
-    const int nrec = stream ? xyk::ragged_records(h->L, own_tx)
+    const int nrec = walk(true) ? xyk::walk_records(h->L)
+                   : stream ? xyk::ragged_records(h->L, own_tx)
                    : strip ? xyk::strip_records(h->L, h->plan.tile_x, h->plan.tile_y)
                            : xyk::fused_records(h->L, h->plan.tile_x, h->plan.tile_y, m);
     int64_t j = 0;  // sweeps done in this call
@@ -496,6 +500,7 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
         const bool timing = h->tn < h->tcap;
         if (timing) (void)hipEventRecord(h->tev[2 * h->tn], h->stream);
         auto launch = [&] {
+            if (walk(mask != 0)) return xyk::launch_walk(a, mask != 0, h->w.partials, h->stream);
             if (strip)
                 return xyk::launch_strip(a, h->plan.tile_x, h->plan.tile_y, mask != 0, h->w.partials, h->stream);
             if (stream || (own_tx && mask == 0))
