@@ -55,11 +55,13 @@ k_deep(const T* __restrict__ src, T* __restrict__ dst, int L, int tx, int ty, in
 // region is the share of one CU: 16 x 16 regions, or regions of 16 x 16 sites
 // where L <= 256, and as many sweeps as fit into the smallest workgroup that takes
 // at least four.  Measured, us a sweep over long calls: L = 256 1.40 (single-sweep
-// 256 x 16 tiles 4.84), L = 512 2.06 (4.97), L = 768 2.97 (5.13).  Below kDeepMinL
-// the whole lattice in one workgroup is faster (L = 48: 1.6 against 2.0), beyond
-// kDeepMaxL the halo's updates cost what the launches save (L = 1024: 4.4 over
-// long calls, 5.5 over ten sweeps, against 5.0 for 128 x 16 tiles).
-constexpr int kDeepMinL = 56, kDeepMaxL = 832, kDeepMaxSweeps = 8;
+// 256 x 16 tiles 4.84), L = 512 2.06 (4.97), L = 768 2.97 (5.13), L = 832 3.4 (4.9,
+// and 4.5 with two pairs a thread, which leave room for two sweeps a launch), L = 1024
+// 4.1 (4.9).  Below kDeepMinL the whole lattice in one workgroup is faster (L = 48:
+// 1.6 against 2.0), beyond kDeepMaxL the halo's updates cost what the launches save
+// (ten sweeps: L = 1000 4.3 against 5.0 for 128 x 16 tiles, L = 1088 4.5 and 5.7, L =
+// 1200 6.0 and 5.9, L = 1280 7.8 and 6.5).
+constexpr int kDeepMinL = 56, kDeepMaxL = 1100, kDeepMaxSweeps = 8;
 
 bool deep_region(int L, int n, DeepPlan* d)
 {
@@ -91,24 +93,29 @@ static int deep_depth(int L, DeepPlan* d)
     int n = depth(deep_fits<512, 1>);
     if (n < 4) n = depth(deep_fits<1024, 1>);
     if (n < 4) n = depth(deep_fits<1024, 2>);
+    if (n < 4) n = depth(deep_fits<1024, 4>);
     return n;
 }
 
-bool deep_choose(int L, bool meas, DeepPlan* d, int* nmax)
+bool deep_choose(int L, int64_t n, bool meas, DeepPlan* d, int* nmax)
 {
-    if (L < kDeepMinL || L > kDeepMaxL || L % 2) return false;
+    // a single sweep gains nothing, nor, with four pairs a thread, do four (L = 1000:
+    // 24.3 us against 20.4 by tiles, five 27.0 and 31.1 with the copy back)
+    if (L < kDeepMinL || L > kDeepMaxL || L % 2 || n < (L > 832 ? 5 : 2)) return false;
     d->tx = d->ty = std::min(16, (L + 15) / 16);
     d->rp = d->full = 0;
     if (meas && L % 64 == 0) {
         // the columns of the tile xy_get_plan reports: 256 x 16 (16 rows: four pairs,
         // 4 rows apart), 128 x 32 (32 rows: four, 8 apart), 64 x 32 (32 rows: two, 16
-        // apart).  Cores of whole blocks of rows, their width again for one region a CU.
+        // apart).  Cores of whole blocks of rows, one or, from four pairs a thread on, two
+        // (ten measured sweeps, one against two: L = 576 3.87 and 3.96 us a sweep, L =
+        // 640 7.5 and 5.4, L = 832 7.3 and 5.3), their width again for one region a CU.
         d->rp = L % 256 == 0 ? 4 : L % 128 == 0 ? 8 : 16;
         d->full = L % 128 == 0 ? 4 : 2;
         if (L % 256 != 0) {
             const int P = L / 4;
-            d->ty = L / 32;
-            d->tx = std::min(P / 2, std::max(8192 / L, (P + 11) / 12));
+            d->ty = L > 600 ? L / 64 : L / 32;
+            d->tx = L > 600 ? 256 / d->ty : std::min(P / 2, std::max(8192 / L, (P + 11) / 12));
         }
     }
     *nmax = deep_depth(L, d);
@@ -143,6 +150,7 @@ static hipError_t pick_deep(const SweepArgs& a, const DeepPlan& d, int n, int me
     XY_DEEP(512, 1);
     XY_DEEP(1024, 1);
     XY_DEEP(1024, 2);
+    XY_DEEP(1024, 4);
 #undef XY_DEEP
     return hipErrorInvalidValue;
 }
@@ -205,16 +213,16 @@ k_resident_quad(float* __restrict__ st, int L, uint32_t sweep0, int n, int me, P
         });
 }
 
-// A quad's replicas share the device, a quarter of it each: 8 x 8 regions, up to
-// the side where those hold four sweeps.  Measured, us for ten sweeps, against
-// single sweeps by tiles: L = 96 19.0 (64.8 one kernel for the four), L = 256 23.0
-// (53.9), L = 384 38.4 (53.2); 16 x 16 regions beyond take longer than the tiles
-// (L = 512 76.4 against 60.6).
-constexpr int kDeepQuadMaxL = 384;
+// A quad's replicas share the device, a quarter of it each: 8 x 8 regions.
+// Measured, us for ten sweeps, against single sweeps by tiles: L = 96 19.0 (64.8 one
+// kernel for the four), L = 256 23.0 (53.9), L = 384 31 (53.2), L = 512 43 (57), L =
+// 576 52 (61), L = 640 81 (68).  Beyond L = 384, where a thread has four pairs, two
+// sweeps take longer (L = 512 19.3 against 14.1), three less.
+constexpr int kDeepQuadMaxL = 576;
 
-bool deep_choose_quad(int L, DeepPlan* d, int* nmax)
+bool deep_choose_quad(int L, int64_t n, DeepPlan* d, int* nmax)
 {
-    if (L < kDeepMinL || L > kDeepQuadMaxL || L % 4) return false;
+    if (L < kDeepMinL || L > kDeepQuadMaxL || L % 4 || n < (L > 384 ? 3 : 2)) return false;
     d->rp = d->full = 0;
     d->tx = d->ty = std::min(8, (L + 15) / 16);
     *nmax = deep_depth(L, d);
@@ -249,6 +257,7 @@ hipError_t launch_deep_quad(const float4* src, float4* dst, int L, uint32_t swee
     XY_DEEP(512, 1);
     XY_DEEP(1024, 1);
     XY_DEEP(1024, 2);
+    XY_DEEP(1024, 4);
 #undef XY_DEEP
     return hipErrorInvalidValue;
 }

@@ -108,9 +108,9 @@ struct DeepPlan {
 };
 // The regions of d's tx x ty cores for n sweeps, if they fit into the lattice.
 bool deep_region(int L, int n, DeepPlan* d);
-// The regions and the most sweeps per launch for lattices that gain from it;
-// `meas`: for passes with a measured sweep.
-bool deep_choose(int L, bool meas, DeepPlan* d, int* nmax);
+// The regions and the most sweeps per launch for lattices and calls of n sweeps
+// that gain from it; `meas`: for passes with a measured sweep.
+bool deep_choose(int L, int64_t n, bool meas, DeepPlan* d, int* nmax);
 // n sweeps from a.src to a.dst (two buffers).  Sweep j (1-based) is measured when
 // me > 0 and (j + phase) % me == 0; the k-th measured one leaves a record of
 // region b at part[(k * tx * ty + b) * 8].
@@ -181,7 +181,7 @@ bool fused_supported(int L, int tile_x, int tile_y, int m);
 // Several sweeps per launch as launch_deep, from one float4 state to another; the
 // k-th measured sweep leaves a record of replica r, region b at
 // part[((4 k + r) * tx * ty + b) * 8].
-bool deep_choose_quad(int L, DeepPlan* d, int* nmax);
+bool deep_choose_quad(int L, int64_t n, DeepPlan* d, int* nmax);
 hipError_t launch_deep_quad(const float4* src, float4* dst, int L, uint32_t sweep, const xyd::Params4& p,
                             const DeepPlan& d, int n, int me, int phase, double* part, hipStream_t s);
 // The whole quad in four workgroups (L <= 32): n sweeps in place, records of every

@@ -461,7 +461,7 @@ int xy_quad_sweep(xy_quad* q, int64_t n_sweeps, int32_t measure_every, xy_obs* o
         xyk::DeepPlan plan;
         int nmax;
         if (q->L == 32) return quad_resident_sweeps(q, n_sweeps, me, obs_dev);
-        if (n_sweeps > 1 && xyk::deep_choose_quad(q->L, &plan, &nmax))
+        if (xyk::deep_choose_quad(q->L, n_sweeps, &plan, &nmax))
             return quad_deep_sweeps(q, plan, nmax, n_sweeps, me, obs_dev);
         if (n_sweeps > 1 && q->L >= 256) return quad_plane_sweeps(q, n_sweeps, me, obs_dev);
     }

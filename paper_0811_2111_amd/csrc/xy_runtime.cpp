@@ -421,15 +421,15 @@ static int deep_sweeps(xy_lattice* h, const xyk::DeepPlan plan[2], int nmax, int
 // launches are to be timed: the whole lattice in one workgroup while that is
 // faster than any tiling (L < 56: 0.7 to 1.8 us a sweep, 1.3 to 2.8 with a record
 // every sweep; two half-sweep launches take 6, with a record 12), then passes of
-// several sweeps (a single sweep gains nothing from them).  Returns false if neither applies.
+// several sweeps.  Returns false if neither applies.
 static bool own_schedule(xy_lattice* h, int64_t n_sweeps, int32_t me, xy_obs* obs, int* rc)
 {
     xyk::DeepPlan plan[2];
     int nmax, nmeas = 0;
     if (!h->own_plan || h->tcap > 0 || n_sweeps == 0) return false;
     if (h->L < 56) *rc = resident_sweeps(h, n_sweeps, me, obs, true);
-    else if (n_sweeps >= 2 && xyk::deep_choose(h->L, true, &plan[1], &nmeas) &&
-             xyk::deep_choose(h->L, false, &plan[0], &nmax))
+    else if (xyk::deep_choose(h->L, n_sweeps, true, &plan[1], &nmeas) &&
+             xyk::deep_choose(h->L, n_sweeps, false, &plan[0], &nmax))
         *rc = deep_sweeps(h, plan, me ? std::min(nmax, nmeas) : nmax, n_sweeps, me, obs);
     else return false;
     return true;

@@ -22,10 +22,10 @@ def pair(L):
 
 
 # 32: one workgroup a replica; 64: records fill the workspace after two sweeps; 96,
-# 160: uneven regions; 384, 416: the last side in passes, the first in tiles; 544:
-# 128-wide tiles, the last of 32 columns; 1024: whole 256-wide ones; 2976: stores
-# past the last-level cache, a last tile of 160 columns
-@pytest.mark.parametrize("L", [32, 64, 96, 160, 384, 416, 544, 1024, 2976])
+# 160: uneven regions; 384, 416: two and four pairs a thread; 576, 608: the last side
+# in passes, the first in tiles (128-wide, the last of 96 columns); 1024: whole
+# 256-wide ones; 2976: past the last-level cache
+@pytest.mark.parametrize("L", [32, 64, 96, 160, 384, 416, 576, 608, 1024, 2976])
 def test_quad_schedules_match_one_kernel(L):
     a, b = pair(L)
     for n, every in [(1, 1), (2, 1), (2, 0), (3, 1), (10, 1), (10, 10), (13, 3)]:
@@ -42,7 +42,7 @@ def test_quad_schedules_match_one_kernel(L):
 
 def test_quad_graph_replay():
     """Captured passes replayed with the state put back in between."""
-    for L in (96, 544):
+    for L in (96, 544, 864):
         a, b = pair(L)
         out = torch.empty((3, 4, 8), dtype=torch.float64, device="cuda")
         start = a.state.clone()
@@ -67,7 +67,7 @@ def test_quad_graph_replay():
                 assert torch.equal(out.view(torch.int64)[..., :2], ref.view(torch.int64)[..., :2])
 
 
-@pytest.mark.parametrize("L", [96, 544])
+@pytest.mark.parametrize("L", [96, 544, 864])
 def test_quad_injected_failure(L):
     n = 9
     _, ref = pair(L)

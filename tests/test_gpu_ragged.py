@@ -44,7 +44,7 @@ def test_ragged_tiles_nontemporal_stores():
 
 
 def test_injected_failure_on_ragged_tiles():
-    L, n = 1002, 6
+    L, n = 1202, 6
     ref = xy.Lattice(L, seed=77, beta=1.1, delta=1.0)
     ref.sweep(n, 2)
     for after in (0, 1, 3, 7):

@@ -16,8 +16,9 @@ STREAM = (1, 0, 0, 1)
 # 4, 6: one pair a row, two pairs with one entry missing; 32, 34: the last size of a
 # workgroup of 512 and the first beyond it; 54, 56, 58: the change-over and its
 # L % 4 == 2 neighbours; 256, 258: 16 x 16 sites a region and the first uneven
-# split; 512: two pairs a thread; 832, 834: the last size of several sweeps a launch
-SIZES = [4, 6, 32, 34, 54, 56, 58, 128, 256, 258, 386, 512, 832, 834]
+# split; 512: two pairs a thread; 800, 834, 1002: four; 576, 640, 832, 1088: cores of
+# whole blocks of rows for the records; 1100, 1102: the last size of several sweeps a launch
+SIZES = [4, 6, 32, 34, 54, 56, 58, 128, 256, 258, 386, 512, 576, 640, 800, 832, 834, 1002, 1088, 1100, 1102]
 
 
 @pytest.mark.parametrize("prec", ["fp32", "fp16"])
