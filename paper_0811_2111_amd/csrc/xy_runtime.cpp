@@ -427,7 +427,7 @@ static bool own_schedule(xy_lattice* h, int64_t n_sweeps, int32_t me, xy_obs* ob
     xyk::DeepPlan plan[2];
     int nmax, nmeas = 0;
     if (!h->own_plan || h->tcap > 0 || n_sweeps == 0) return false;
-    if (h->L < 56) *rc = resident_sweeps(h, n_sweeps, me, obs, true);
+    if (h->L < 56 || (n_sweeps == 1 && h->L < 64)) *rc = resident_sweeps(h, n_sweeps, me, obs, true);
     else if (xyk::deep_choose(h->L, n_sweeps, true, &plan[1], &nmeas) &&
              xyk::deep_choose(h->L, n_sweeps, false, &plan[0], &nmax))
         *rc = deep_sweeps(h, plan, me ? std::min(nmax, nmeas) : nmax, n_sweeps, me, obs);

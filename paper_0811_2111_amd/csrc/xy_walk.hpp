@@ -13,7 +13,8 @@
 // range, so that no step branches.  Steps are unrolled by six: three rows of (cos,
 // sin) and two row parities.
 //
-// What bounds it: the vector unit, 45 instructions an update (256 x 16 tiles: 55) of
+// What bounds it: the vector unit, 45 instructions an update, 52 with the halo rows and
+// lanes at L = 4096 (256 x 16 tiles: 55), of
 // which the eight v_mad_u64_u32 of Philox and the five transcendentals take as long
 // as 40 additions; 57 registers, so eight waves a SIMD.  Every site goes through
 // xyd::site_update with neighbour sums (left + right) + (up + down), so the
