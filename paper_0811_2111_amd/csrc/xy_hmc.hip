@@ -214,6 +214,14 @@ constexpr int kStepRows = 4;               // rows per thread of k_hmc_step2
 // L = 4096, 7 steps: 12 waves of six rows 95 us, 16 of four 97, 16 of eight 117 (one
 // workgroup a CU).
 constexpr int kMaxStepsPerPass = 8;
+// Steps of a trajectory's longest pass: the fewest passes that the setting allows, of
+// even length (ten steps, 5 and 5 against 7 and 3: L = 2048 77.9 us a trajectory
+// against 83.2, L = 3000 130.7 and 138.3, L = 4096 216 and 221).
+static int pass_steps(int n_md, int setting)
+{
+    const int most = std::min(std::min(setting, kMaxStepsPerPass), n_md), passes = (n_md + most - 1) / most;
+    return (n_md + passes - 1) / passes;
+}
 constexpr int kPassWaves = 8;
 constexpr int kPassFewRegions = 320;    // four rows a thread up to this many regions
 
@@ -754,7 +762,7 @@ hipError_t launch_hmc_trajectory(float* state, float* pingpong, const HmcWork& w
     if (steps_per_pass > 1) {
         // passes of up to steps_per_pass steps; the momenta ping-pong between p and p2
         float* pn = w.p2;
-        const int kmax = steps_per_pass < kMaxStepsPerPass ? steps_per_pass : kMaxStepsPerPass;
+        const int kmax = pass_steps(n_md, steps_per_pass);
         for (int q = 0; q < n_md;) {
             const int k = n_md - q < kmax ? n_md - q : kmax;
             launch_pass(s, src, dst, p, pn, L, k, q == 0 ? kick_half : kick_full, kick_full, drift);
@@ -807,10 +815,7 @@ void hmc_batch_describe(BhLat& d, int L, double beta, double eps)
 
 static uint32_t pad8(uint32_t v) { return (v + 7u) & ~7u; }
 
-int hmc_batch_steps(int n_md, int steps_per_pass)
-{
-    return std::min(n_md, std::min(steps_per_pass, kMaxStepsPerPass));
-}
+int hmc_batch_steps(int n_md, int steps_per_pass) { return pass_steps(n_md, steps_per_pass); }
 
 int hmc_batch_rows(int n, const int32_t* L, int kh)
 {
@@ -933,7 +938,7 @@ hipError_t launch_quad_hmc_trajectory(float* planes, float* second, const QuadHm
     hipLaunchKernelGGL(k_qhmc_ends<true>, grec, block, 0, s, planes, w.p, w.saved, L, traj, keys, kick_half, cols, runs,
                        w.flag, w.rec_old, nrec);
     float *src = planes, *dst = second, *p = w.p, *pn = w.p2;
-    const int kmax = std::min(steps_per_pass, kMaxStepsPerPass);
+    const int kmax = pass_steps(n_md, steps_per_pass);
     for (int q = 0; q < n_md;) {
         const int k = std::min(n_md - q, kmax);
         const bool tall = 4 * pass_tiles<kPassWaves, 4>(L, k) > kPassFewRegions;
