@@ -121,9 +121,10 @@ typedef struct xy_obs {
  *                   XY_PLAN_STREAM.  xy_get_plan reports that plan; where the plan
  *                   was not asked for by kind, small lattices run schedules of the
  *                   library's own in its place (L < 56: every sweep of a call in
- *                   one launch, the lattice on chip; up to L = 832: several sweeps
+ *                   one launch, the lattice on chip; up to L = 1100: several sweeps
  *                   per launch on overlapping regions) and larger ones single-sweep
- *                   tiles that need not divide L, unless xy_kernel_timer is on. */
+ *                   tiles that need not divide L or strips of one wave, unless
+ *                   xy_kernel_timer is on. */
 enum { XY_PLAN_AUTO = 0, XY_PLAN_STREAM = 1, XY_PLAN_FUSED = 2, XY_PLAN_STRIP = 3, XY_PLAN_RESIDENT = 4 };
 typedef struct xy_plan {
     int32_t kind;
@@ -309,7 +310,8 @@ int xy_hmc(xy_lattice* h, int64_t n_traj, int32_t n_md, double eps, void* hmc_wo
  * otherwise).  With more than one a workgroup loads a region of the lattice (128
  * sites wide, 32 or 64 high) into registers, runs the steps on it and writes back
  * the core that is that many sites away from its edge, so HBM traffic per site and
- * step falls by that factor; the trajectory is bit for bit the same.
+ * step falls by that factor; the trajectory is bit for bit the same.  A trajectory
+ * takes the fewest passes of at most that many steps, of even length.
  * xy_hmc_get_steps_per_pass reports the setting where L % 32 == 0, else 1 (such
  * lattices take the same passes). */
 int xy_hmc_set_steps_per_pass(xy_lattice* h, int32_t steps);
