@@ -84,18 +84,27 @@ __device__ __forceinline__ unsigned xcd_band(unsigned b, unsigned nb)
     return (b & 7u) * (nb >> 3) + (b >> 3);
 }
 
+// Whether the trajectory before this one in the same call was rejected: its begin
+// kernel's saved angles then are the state, which holds the rejected ones.  The
+// begin reads them there and writes them to the state, in place of the other way
+// round: a launch of 4.8 us a trajectory less than a copy back after each.
+__device__ __forceinline__ bool rejected_before(int again, const unsigned* flag) { return again && flag[0] == 0u; }
+
 // Record-writing passes: 1-D grid of cols x rb workgroups, cols = 2 ceil(Hh/256)
 // (column block, colour interleaved), rb row blocks; after the XCD remap t,
 // column t % cols takes the run of R = ceil(L / rb) consecutive rows starting at
 // (t / cols) R, so the rows above and the row itself that a thread needs from
 // the other plane were loaded in its previous iteration.  Record index: t.
-
+//
 // Momenta, saved angles and the partial records of H_old.
 __global__ void __launch_bounds__(kThreads)
-k_hmc_begin(const float* __restrict__ st, float* __restrict__ p, float* __restrict__ saved, int L, uint32_t traj,
-            uint32_t k0, uint32_t k1, int cols, int rb, unsigned* __restrict__ flag, double* __restrict__ rec)
+k_hmc_begin(float* st, float* __restrict__ p, float* copy, int L, uint32_t traj,
+            uint32_t k0, uint32_t k1, int cols, int rb, int again, unsigned* __restrict__ flag, double* __restrict__ rec)
 {
     if (blockIdx.x == 0 && threadIdx.x == 0) flag[1] = 0u;
+    const bool back = rejected_before(again, flag);
+    const float* from = back ? copy : st;
+    float* saved = back ? st : copy;
     const int Hh = L >> 1, P = (Hh + 1) >> 1;
     const unsigned t = xcd_band(blockIdx.x, gridDim.x);
     const int col = (int)(t % (unsigned)cols);
@@ -106,7 +115,7 @@ k_hmc_begin(const float* __restrict__ st, float* __restrict__ p, float* __restri
     if (k < Hh) {
         for (int y = y0; y < y1; ++y) {
             float th;
-            const Nb n = load_nb(st, L, Hh, c, y, k, th);
+            const Nb n = load_nb(from, L, Hh, c, y, k, th);
             const size_t i = ((size_t)c * L + y) * Hh + k;
             saved[i] = th;
             const u32x4 r = philox10(traj, (uint32_t)c, 2u, (uint32_t)y * (uint32_t)P + (uint32_t)(k >> 1), k0, k1);
@@ -395,12 +404,13 @@ __device__ __forceinline__ void ends2_body(const float* __restrict__ st, float* 
 
 template <bool BEGIN>
 __global__ void __launch_bounds__(kThreads)
-k_hmc_ends2(const float* __restrict__ st, float* __restrict__ p, float* __restrict__ copy, int L, uint32_t traj,
-            uint32_t k0, uint32_t k1, float nbeta_kick, int cols, int rb, unsigned* __restrict__ flag,
+k_hmc_ends2(float* st, float* __restrict__ p, float* copy, int L, uint32_t traj,
+            uint32_t k0, uint32_t k1, float nbeta_kick, int cols, int rb, int again, unsigned* __restrict__ flag,
             double* __restrict__ rec)
 {
     if (BEGIN && blockIdx.x == 0 && threadIdx.x == 0) flag[1] = 0u;
-    ends2_body<BEGIN>(st, p, copy, L, traj, k0, k1, nbeta_kick, cols, rb, rec, xcd_band(blockIdx.x, gridDim.x));
+    const bool back = BEGIN && rejected_before(again, flag);
+    ends2_body<BEGIN>(back ? copy : st, p, back ? st : copy, L, traj, k0, k1, nbeta_kick, cols, rb, rec, xcd_band(blockIdx.x, gridDim.x));
 }
 
 // Metropolis step of the trajectory.  Workgroup b sums chunk b % nchunk (256
@@ -478,14 +488,16 @@ k_quad_join(const float* __restrict__ planes, float4* __restrict__ st, size_t n)
 
 template <bool BEGIN>
 __global__ void __launch_bounds__(kThreads)
-k_qhmc_ends(const float* __restrict__ st, float* __restrict__ p, float* __restrict__ copy, int L, uint32_t traj,
-            QHmcKeys keys, float4 kick, int cols, int runs, unsigned* __restrict__ flag, double* __restrict__ rec,
-            int nrec)
+k_qhmc_ends(float* st, float* __restrict__ p, float* copy, int L, uint32_t traj,
+            QHmcKeys keys, float4 kick, int cols, int runs, int again, unsigned* __restrict__ flag,
+            double* __restrict__ rec, int nrec)
 {
     const int r = (int)blockIdx.y;
     const size_t o = (size_t)r * L * L;
     if (BEGIN && blockIdx.x == 0 && threadIdx.x == 0) flag[16 * r + 1] = 0u;
-    ends2_body<BEGIN>(st + o, p + o, copy ? copy + o : nullptr, L, traj, keys.k0[r], keys.k1[r],
+    float *from = st + o, *to = copy ? copy + o : nullptr;
+    const bool back = BEGIN && rejected_before(again, flag + 16 * r);
+    ends2_body<BEGIN>(back ? to : from, p + o, back ? from : to, L, traj, keys.k0[r], keys.k1[r],
                       r == 0 ? kick.x : r == 1 ? kick.y : r == 2 ? kick.z : kick.w, cols, runs,
                       rec + (size_t)r * nrec * 8, xcd_band(blockIdx.x, gridDim.x));
 }
@@ -740,7 +752,7 @@ HmcWork hmc_carve_compact(void* work, int L)
 
 hipError_t launch_hmc_trajectory(float* state, float* pingpong, const HmcWork& w, int L, double beta, double eps,
                                  int n_md, int steps_per_pass, uint32_t traj, uint32_t k0, uint32_t k1,
-                                 xy_hmc_obs* obs, hipStream_t s)
+                                 xy_hmc_obs* obs, bool again, hipStream_t s)
 {
     const bool pairs2 = hmc_pairs(L);
     const int cols = pairs2 ? hmc_cols2(L) : hmc_cols(L), rb = pairs2 ? hmc_runs2(L) : hmc_row_blocks(L);
@@ -751,10 +763,10 @@ hipError_t launch_hmc_trajectory(float* state, float* pingpong, const HmcWork& w
     const float drift = (float)(eps / (2.0 * 3.14159265358979323846));
     if (pairs2)
         hipLaunchKernelGGL(k_hmc_ends2<true>, grec, block, 0, s, state, w.p, w.saved, L, traj, k0, k1, 0.0f, cols, rb,
-                           w.flag, w.rec_old);
+                           (int)again, w.flag, w.rec_old);
     else
-        hipLaunchKernelGGL(k_hmc_begin, grec, block, 0, s, state, w.p, w.saved, L, traj, k0, k1, cols, rb, w.flag,
-                           w.rec_old);
+        hipLaunchKernelGGL(k_hmc_begin, grec, block, 0, s, state, w.p, w.saved, L, traj, k0, k1, cols, rb,
+                           (int)again, w.flag, w.rec_old);
     float* src = state;
     float* dst = pingpong;
     float* p = w.p;
@@ -790,15 +802,20 @@ hipError_t launch_hmc_trajectory(float* state, float* pingpong, const HmcWork& w
     }
     if (pairs2)
         hipLaunchKernelGGL(k_hmc_ends2<false>, grec, block, 0, s, src, p, src == state ? nullptr : state, L, traj, k0,
-                           k1, kick_half, cols, rb, w.flag, w.rec_new);
+                           k1, kick_half, cols, rb, 0, w.flag, w.rec_new);
     else
         hipLaunchKernelGGL(k_hmc_end, grec, block, 0, s, src, src == state ? nullptr : state, p, L, kick_half, cols,
                            rb, w.rec_new);
     hipLaunchKernelGGL(k_hmc_decide, dim3(2 * (unsigned)nchunk), block, 0, s, w.rec_old, w.rec_new, nrec, nchunk,
                        w.chunk_old, w.chunk_new, beta, traj, k0, k1, w.flag, obs);
+    return hipGetLastError();
+}
+
+hipError_t launch_hmc_restore(float* state, const HmcWork& w, int L, hipStream_t s)
+{
     const size_t n = (size_t)L * (size_t)L;
     const unsigned nb = (unsigned)((n + kThreads * 8 - 1) / (kThreads * 8));
-    hipLaunchKernelGGL(k_hmc_restore, dim3(nb < 4096 ? nb : 4096), block, 0, s, w.flag, w.saved, state, n);
+    hipLaunchKernelGGL(k_hmc_restore, dim3(nb < 4096 ? nb : 4096), dim3(kThreads), 0, s, w.flag, w.saved, state, n);
     return hipGetLastError();
 }
 
@@ -918,7 +935,7 @@ hipError_t launch_quad_join(const float* planes, float4* state, int L, hipStream
 
 hipError_t launch_quad_hmc_trajectory(float* planes, float* second, const QuadHmcWork& w, int L, const double beta[4],
                                       double eps, int n_md, int steps_per_pass, uint32_t traj, const QHmcKeys& keys,
-                                      xy_hmc_obs* obs, hipStream_t s)
+                                      xy_hmc_obs* obs, bool again, hipStream_t s)
 {
     const int cols = hmc_cols2(L), runs = hmc_runs2(L, quad_hmc_records(L));
     const int G = ends_group(L), nbr = (runs + G - 1) / G;
@@ -936,7 +953,7 @@ hipError_t launch_quad_hmc_trajectory(float* planes, float* second, const QuadHm
     const float4 kick_half = make_float4(kh[0], kh[1], kh[2], kh[3]);
     const float4 kick_full = make_float4(kf[0], kf[1], kf[2], kf[3]);
     hipLaunchKernelGGL(k_qhmc_ends<true>, grec, block, 0, s, planes, w.p, w.saved, L, traj, keys, kick_half, cols, runs,
-                       w.flag, w.rec_old, nrec);
+                       (int)again, w.flag, w.rec_old, nrec);
     float *src = planes, *dst = second, *p = w.p, *pn = w.p2;
     const int kmax = pass_steps(n_md, steps_per_pass);
     for (int q = 0; q < n_md;) {
@@ -954,12 +971,17 @@ hipError_t launch_quad_hmc_trajectory(float* planes, float* second, const QuadHm
         q += k;
     }
     hipLaunchKernelGGL(k_qhmc_ends<false>, grec, block, 0, s, src, p, src == planes ? nullptr : planes, L, traj, keys,
-                       kick_half, cols, runs, w.flag, w.rec_new, nrec);
+                       kick_half, cols, runs, 0, w.flag, w.rec_new, nrec);
     hipLaunchKernelGGL(k_qhmc_decide, dim3(2 * (unsigned)nchunk, 4), block, 0, s, w.rec_old, w.rec_new, nrec, nchunk,
                        w.chunk_old, w.chunk_new, qb, traj, keys, w.flag, obs);
+    return hipGetLastError();
+}
+
+hipError_t launch_quad_hmc_restore(float* planes, const QuadHmcWork& w, int L, hipStream_t s)
+{
     const size_t n = (size_t)L * (size_t)L;
     const unsigned nb = (unsigned)((n + kThreads * 8 - 1) / (kThreads * 8));
-    hipLaunchKernelGGL(k_qhmc_restore, dim3(nb < 2048 ? nb : 2048, 4), block, 0, s, w.flag, w.saved, planes, n);
+    hipLaunchKernelGGL(k_qhmc_restore, dim3(nb < 2048 ? nb : 2048, 4), dim3(kThreads), 0, s, w.flag, w.saved, planes, n);
     return hipGetLastError();
 }
 

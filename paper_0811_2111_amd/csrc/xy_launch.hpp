@@ -138,11 +138,15 @@ HmcWork hmc_carve(void* work, int L);
 int hmc_records(int L);
 // One trajectory from the FP32 angles in `state` (result back in `state`),
 // `pingpong` a second state-sized buffer; record to obs if not NULL.
+// again: another trajectory of the same call went before, and no restore since.
 // steps_per_pass > 1: leap-frog steps in passes of up to min(steps_per_pass, 8)
 // steps (temporal blocking); else one step per launch.
 hipError_t launch_hmc_trajectory(float* state, float* pingpong, const HmcWork& w, int L, double beta, double eps,
                                  int n_md, int steps_per_pass, uint32_t traj, uint32_t k0, uint32_t k1,
-                                 xy_hmc_obs* obs, hipStream_t s);
+                                 xy_hmc_obs* obs, bool again, hipStream_t s);
+// After the last trajectory of a call: the saved angles back into the state if it
+// was rejected.
+hipError_t launch_hmc_restore(float* state, const HmcWork& w, int L, hipStream_t s);
 // Workspace of one lattice with record arrays sized for its L only (batches).
 size_t hmc_work_bytes_compact(int L);
 HmcWork hmc_carve_compact(void* work, int L);
@@ -222,7 +226,8 @@ QuadHmcWork quad_hmc_carve(void* work, int L);
 // its lattice (its FP64 sums may be cut differently); obs: NULL or 4 records.
 hipError_t launch_quad_hmc_trajectory(float* planes, float* second, const QuadHmcWork& w, int L, const double beta[4],
                                       double eps, int n_md, int steps_per_pass, uint32_t traj, const QHmcKeys& keys,
-                                      xy_hmc_obs* obs, hipStream_t s);
+                                      xy_hmc_obs* obs, bool again, hipStream_t s);
+hipError_t launch_quad_hmc_restore(float* planes, const QuadHmcWork& w, int L, hipStream_t s);
 
 // Fill n u64 words with zero (kernel, not a memset node: safe inside graphs).
 hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t s);

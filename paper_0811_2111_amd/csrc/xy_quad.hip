@@ -577,9 +577,13 @@ int xy_quad_hmc(xy_quad* q, int64_t n_traj, int32_t n_md, double eps, void* hmc_
     for (int64_t j = 0; j < n_traj && rc == XY_OK; ++j) {
         e = XY_LAUNCH(xyk::launch_quad_hmc_trajectory(planes, (float*)q->state, w, q->L, q->beta, eps, n_md, steps,
                                                       (uint32_t)q->sweep, keys,
-                                                      obs_dev ? obs_dev + (size_t)j * 4 : nullptr, q->stream));
+                                                      obs_dev ? obs_dev + (size_t)j * 4 : nullptr, j > 0, q->stream));
         if (e != hipSuccess) rc = xyr::hip_fail(e, "xy_quad_hmc: launch");
         else q->sweep += 1;
+        if (rc == XY_OK ? j == n_traj - 1 : j > 0) {
+            e = xyk::launch_quad_hmc_restore(planes, w, q->L, q->stream);
+            if (rc == XY_OK && e != hipSuccess) rc = xyr::hip_fail(e, "xy_quad_hmc: launch");
+        }
     }
     // also after a failed trajectory, so that the state agrees with the counter
     e = xyk::launch_quad_join(planes, q->state, q->L, q->stream);

@@ -569,11 +569,18 @@ int xy_hmc(xy_lattice* h, int64_t n_traj, int32_t n_md, double eps, void* hmc_wo
     for (int64_t j = 0; j < n_traj; ++j) {
         hipError_t e = XY_LAUNCH(xyk::launch_hmc_trajectory((float*)h->state, (float*)h->w.pingpong, w, h->L,
                                                             h->beta, eps, n_md, h->hmc_steps, (uint32_t)h->sweep,
-                                                            k0, k1, obs_dev ? obs_dev + j : nullptr, h->stream));
-        if (e != hipSuccess) return hip_fail(e, "hmc trajectory launch");
+                                                            k0, k1, obs_dev ? obs_dev + j : nullptr, j > 0,
+                                                            h->stream));
+        if (e != hipSuccess) {
+            const int rc = hip_fail(e, "hmc trajectory launch");
+            if (j > 0) (void)xyk::launch_hmc_restore((float*)h->state, w, h->L, h->stream);
+            return rc;
+        }
         h->sweep += 1;
     }
-    return XY_OK;
+    if (n_traj == 0) return XY_OK;
+    hipError_t e = xyk::launch_hmc_restore((float*)h->state, w, h->L, h->stream);
+    return e == hipSuccess ? XY_OK : hip_fail(e, "hmc trajectory launch");
 }
 
 int xy_hmc_set_steps_per_pass(xy_lattice* h, int32_t steps)

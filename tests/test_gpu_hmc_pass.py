@@ -45,3 +45,36 @@ def test_batches_of_any_side_match_single_lattices(Ls):
             lat = xy.Lattice(L, seed=seeds[i], beta=betas[i])
             srec = xy.hmc_records(lat.hmc(2, 10, 0.1))
             assert srec.tobytes() == rec[i].tobytes() and torch.equal(b.lattice_state(i), lat.state), (steps, L)
+
+
+@pytest.mark.parametrize("L", [32, 34, 64, 300])
+def test_several_trajectories_a_call_match_single_calls(L):
+    """Rejected trajectories are undone by the next one of the call, the last by the call."""
+    a, b = (xy.Lattice(L, seed=(5 << 33) + L, beta=1.05) for _ in range(2))
+    seen = set()
+    for eps in (0.05, 0.2, 0.35, 2.5):
+        many = xy.hmc_records(a.hmc(6, 7, eps))
+        one = [xy.hmc_records(b.hmc(1, 7, eps)) for _ in range(6)]
+        assert many.tobytes() == b"".join(r.tobytes() for r in one) and torch.equal(a.state, b.state), eps
+        seen |= set(int(v) for v in many["accepted"])
+    assert seen == {0, 1}
+    if L % 32 == 0:
+        args = ([1, 2, 3, 4], [0.7, 0.9, 1.1, 1.3])
+        a, b = xy.Quad(L, *args), xy.Quad(L, *args)
+        for eps in (0.05, 0.2, 0.35, 2.5):
+            many = xy.hmc_records(a.hmc(6, 7, eps))
+            one = [xy.hmc_records(b.hmc(1, 7, eps)) for _ in range(6)]
+            assert many.tobytes() == b"".join(r.tobytes() for r in one) and torch.equal(a.state, b.state), eps
+
+
+def test_injected_failure_between_trajectories():
+    ref = xy.Lattice(64, seed=9, beta=1.1)
+    ref.hmc(2, 7, 2.5)                                     # rejected
+    lat = xy.Lattice(64, seed=9, beta=1.1)
+    xy.xy_test_inject_failure(2)
+    try:
+        with pytest.raises(xy.XYError):
+            lat.hmc(4, 7, 2.5)
+    finally:
+        xy.xy_test_inject_failure(-1)
+    assert lat.sweep_count == 2 and torch.equal(lat.state, ref.state)
