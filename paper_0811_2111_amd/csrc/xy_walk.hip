@@ -66,10 +66,14 @@ static int walk_runs(int L, int lattices)
 
 bool walk_supported(int L, int precision, bool meas)
 {
-    // a measured sweep by whole 256 x 16 tiles is the faster one (L = 4096: 38.9 us
-    // against 40.2; by tiles cut off at the edge L = 4100 44.6 and 39.6)
+    // a measured sweep by whole tiles is the faster one for 256 x 16 (L = 4096: 38.9 us
+    // against 40.2 with FP32 chains of three rows) and, while the lattice is small, for 128 x 32 (tiles and strips: L =
+    // 4224 44.8 and 47.2, 7040 113.3 and 113.4, 7296 122 and 119, 9600 212 and 203); not
+    // for 64 x 32 (4160 48.8 and 43.1, 6080 97.4 and 86.5) or tiles cut off at the edge
+    // (7000 119 and 114)
+    const bool tiles = L % 256 == 0 || (L % 128 == 0 && L < 7200);
     return precision == XY_FP32 && L % 4 == 0 && L >= kWalkMinL && L <= (L % 512 ? kWalkMaxL : kWalkMaxStripL) &&
-           !(meas && L % 256 == 0);
+           !(meas && tiles);
 }
 
 int walk_records(int L) { return walk_strips(L) * walk_runs(L, 1); }

@@ -16,9 +16,11 @@
 // What bounds it: the vector unit, 45 instructions an update, 52 with the halo rows and
 // lanes at L = 4096 (256 x 16 tiles: 55), of
 // which the eight v_mad_u64_u32 of Philox and the five transcendentals take as long
-// as 40 additions; 57 registers, so eight waves a SIMD.  Every site goes through
-// xyd::site_update with neighbour sums (left + right) + (up + down), so the
-// trajectory is that of every other schedule.
+// as 40 additions; 57 registers, so eight waves a SIMD.  A measured sweep adds every
+// black pair's FP32 terms to FP64 sums by itself (88.6 us at L = 6000; 83.0 with FP32
+// chains of three rows, which round about three times as much).  Every site goes through
+// xyd::site_update with neighbour sums (left + right) + (up + down), so the trajectory
+// is that of every other schedule.
 #pragma once
 
 #include "xy_tile1.hpp"
@@ -68,7 +70,6 @@ struct Walk {
     float4 R[3], B[3];                // new red, old black (cos, sin), rows modulo 3
     float2 tr[6], tb[6];              // angles, rows modulo 6
     int acc = 0;
-    MeasAcc m;
     double v[7] = {0, 0, 0, 0, 0, 0, 0};
 
     // rows past the run's halo are loaded too, wrapped into the lattice, and never used
@@ -90,12 +91,16 @@ struct Walk {
         sincos_turn(t.y, o.w, o.z);
         return o;
     }
-    // the FP32 sums of three rows into the FP64 ones
-    __device__ __forceinline__ void flush()
+    // A black pair's terms into the FP64 sums, gathered as k_measure does, so that a
+    // record is k_measure's but for the order of its FP64 sums.
+    template <int O>
+    __device__ __forceinline__ void measure(const float4& own, const WalkSide<O>& s, const float4& u, const float4& d)
     {
-        v[0] += (double)m.cx; v[1] += (double)m.cy; v[2] += (double)m.ix;
-        v[3] += (double)m.iy; v[4] += (double)m.mx; v[5] += (double)m.my;
-        m = MeasAcc();
+        Meas t{0, 0, 0, 0, 0, 0};
+        meas_black(t, own.x, own.y, s.la.x, s.la.y, s.ra.x, s.ra.y, u.x, u.y, d.x, d.y);
+        meas_black(t, own.z, own.w, s.lb.x, s.lb.y, s.rb.x, s.rb.y, u.z, u.w, d.z, d.w);
+        v[0] += (double)t.cx; v[1] += (double)t.cy; v[2] += (double)t.ix;
+        v[3] += (double)t.iy; v[4] += (double)t.mx; v[5] += (double)t.my;
     }
     // One pair: t, own angles and (cos, sin); s, u, d its neighbours; w its random words.
     template <int O>
@@ -138,9 +143,7 @@ struct Walk {
             store(rd, half + (unsigned)yb * pitch, t.x, t.y);
             if constexpr (MEAS) {
                 acc += ab;
-                meas_acc(m, own.x, own.y, s.la, s.ra, make_float2(u.x, u.y), make_float2(d.x, d.y));
-                meas_acc(m, own.z, own.w, s.lb, s.rb, make_float2(u.z, u.w), make_float2(d.z, d.w));
-                if constexpr (K % 3 == 1) flush();
+                measure<O>(own, s, u, d);
             }
         }
     }
@@ -172,10 +175,7 @@ struct Walk {
             step<1, true>(j);
             if (++j > n + 1) break;
         }
-        if constexpr (MEAS) {
-            flush();
-            v[6] = (double)acc;
-        }
+        if constexpr (MEAS) v[6] = (double)acc;
     }
 };
 
