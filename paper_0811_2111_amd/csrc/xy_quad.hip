@@ -274,14 +274,14 @@ static xyd::Params4 quad_params(const xy_quad* q)
     return p;
 }
 
-// Every sweep in one launch of four workgroups (L = 32).
+// Every sweep in one launch of four workgroups (L = 32; long calls in several).
 static int quad_resident_sweeps(xy_quad* q, int64_t n_sweeps, int32_t me, xy_obs* obs)
 {
     const xyd::Params4 p = quad_params(q);
-    const int64_t cap = me ? ((int64_t)1 << 30) / me * me : ((int64_t)1 << 30);
     for (int64_t done = 0; done < n_sweeps;) {
-        const int64_t m = std::min<int64_t>(cap, n_sweeps - done);
+        const int64_t m = std::min<int64_t>(xyk::resident_sweeps_max(q->L), n_sweeps - done);
         hipError_t e = XY_LAUNCH(xyk::launch_resident_quad(q->state, q->L, (uint32_t)q->sweep, p, (int)m, me,
+                                                           me ? (int)(done % me) : 0,
                                                            me ? obs + done / me * 4 : nullptr, q->stream));
         if (e != hipSuccess) return xyr::hip_fail(e, "xy_quad_sweep: launch");
         q->sweep += (uint64_t)m;
@@ -452,7 +452,7 @@ int xy_quad_sweep(xy_quad* q, int64_t n_sweeps, int32_t measure_every, xy_obs* o
     if (!quad_live(q)) return XY_ESTATE;
     if (n_sweeps < 0 || measure_every < 0) return XY_EINVAL;
     if (q->sweep + (uint64_t)n_sweeps >= 0xffffffffull) return XY_ERANGE;
-    const bool meas = measure_every > 0 && obs_dev != nullptr;
+    const bool meas = measure_every > 0 && obs_dev != nullptr && measure_every <= n_sweeps;
     // Where no tile was asked for: the whole quad in four workgroups, passes of
     // several sweeps, or single sweeps of the lattices apart (a single sweep gains
     // nothing from the latter two).

@@ -344,16 +344,15 @@ static int stream_sweep(xy_lattice* h, bool measured, xy_obs* rec, uint8_t* dbg_
     return XY_OK;
 }
 
-// Every sweep of a call in one launch of one workgroup; calls longer than 2^30
-// sweeps are split at a multiple of measure_every.
+// Every sweep of a call in one launch of one workgroup (long calls in several).
 static int resident_sweeps(xy_lattice* h, int64_t n_sweeps, int32_t me, xy_obs* obs, bool own)
 {
-    const int64_t cap = me ? ((int64_t)1 << 30) / me * me : ((int64_t)1 << 30);
     for (int64_t done = 0; done < n_sweeps;) {
-        const int64_t m = std::min<int64_t>(cap, n_sweeps - done);
+        const int64_t m = std::min<int64_t>(xyk::resident_sweeps_max(h->L), n_sweeps - done);
         xyk::SweepArgs a = args_of(h);
         auto launch = own ? xyk::launch_resident_any : xyk::launch_resident;
-        hipError_t e = XY_LAUNCH(launch(a, (int)m, me, me ? obs + done / me : nullptr, h->stream));
+        hipError_t e = XY_LAUNCH(launch(a, (int)m, me, me ? (int)(done % me) : 0, me ? obs + done / me : nullptr,
+                                        h->stream));
         if (e != hipSuccess) return hip_fail(e, "resident sweep launch");
         h->sweep += (uint64_t)m;
         done += m;
@@ -440,7 +439,7 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
     if (!live(h)) return XY_ESTATE;
     if (n_sweeps < 0 || measure_every < 0) return XY_EINVAL;
     if (h->sweep + (uint64_t)n_sweeps >= 0xffffffffull) return XY_ERANGE;
-    const bool meas = measure_every > 0 && obs_dev != nullptr;
+    const bool meas = measure_every > 0 && obs_dev != nullptr && measure_every <= n_sweeps;
     auto measured = [&](int64_t j) { return meas && (j % measure_every) == 0; };  // j = 1-based sweep in call
     auto rec_of = [&](int64_t j) { return obs_dev + (j / measure_every - 1); };
     int own_rc;

@@ -1,0 +1,106 @@
+"""Launch sequences of the library's host code on the CPU: its objects linked with
+hip_stub.cpp in place of the HIP runtime, which logs the kernels that would run."""
+from __future__ import annotations
+
+import ctypes
+import glob
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_0811_2111_amd")
+OK, EHIP = 0, -4
+i32, i64, u64, sz, dbl, vp = (ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64, ctypes.c_size_t, ctypes.c_double,
+                              ctypes.c_void_p)
+DEV = vp(1 << 20)                      # stands for device memory; never read
+INT32_MAX = 2 ** 31 - 1
+
+
+class Stub:
+    def __init__(self, lib):
+        self.lib = lib
+        lib.stub_log.restype = ctypes.c_char_p
+
+    def log(self, fn):
+        """The kernels that fn() launches."""
+        self.lib.stub_reset()
+        try:
+            fn()
+            return self.lib.stub_log().decode().split()
+        finally:
+            self.lib.stub_reset()
+
+    def lattice(self, L, prec=0):
+        h = vp()
+        assert self.lib.xy_init(ctypes.byref(h), u64(1), i32(L), dbl(1.0), dbl(1.0), 0, prec, DEV, sz(1 << 40), DEV,
+                                sz(1 << 40), None) == OK
+        return h
+
+    def quad(self, L):
+        h = vp()
+        d = (dbl * 4)(1, 1, 1, 1)
+        assert self.lib.xy_quad_init(ctypes.byref(h), (u64 * 4)(1, 2, 3, 4), i32(L), d, d, 0, DEV, sz(1 << 40), DEV,
+                                     sz(1 << 40), None) == OK
+        return h
+
+    def count(self, h, get="xy_get_sweep"):
+        v = u64()
+        assert getattr(self.lib, get)(h, ctypes.byref(v)) == OK
+        return v.value
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    objs = glob.glob(os.path.join(PKG, "_build", "*.o"))
+    if not objs or shutil.which("g++") is None:
+        pytest.skip("the library's objects are not built (run __graft_entry__.build())")
+    out = str(tmp_path_factory.mktemp("stub") / "libxystub.so")
+    # -Bsymbolic: the stub's functions, also where a HIP runtime is in the process
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
+                    os.path.join(ROOT, "tests", "hip_stub.cpp")] + objs + ["-o", out], check=True, capture_output=True)
+    return Stub(ctypes.CDLL(out))
+
+
+@pytest.mark.parametrize("L,n", [(32, 3), (62, 1), (256, 3)])
+def test_sweeps_shorter_than_the_record_interval_end(stub, L, n):
+    """A call whose first record lies beyond its last sweep is an unmeasured one."""
+    h = stub.lattice(L)
+    plain = stub.log(lambda: stub.lib.xy_sweep(h, i64(n), 0, None))
+
+    def go():
+        stub.lib.stub_fail_after(100)
+        assert stub.lib.xy_sweep(h, i64(n), i32(INT32_MAX), DEV) == OK
+    assert stub.log(go) == plain
+    assert stub.count(h) == 2 * n
+
+
+def test_quad_sweeps_shorter_than_the_record_interval_end(stub):
+    q = stub.quad(32)
+    plain = stub.log(lambda: stub.lib.xy_quad_sweep(q, i64(3), 0, None))
+
+    def go():
+        stub.lib.stub_fail_after(100)
+        assert stub.lib.xy_quad_sweep(q, i64(3), i32(INT32_MAX), DEV) == OK
+    assert stub.log(go) == plain
+    assert stub.count(q, "xy_quad_get_sweep") == 6
+
+
+@pytest.mark.parametrize("L,plan", [(4, 0), (32, 0), (54, 0), (128, 4)])
+def test_long_calls_on_chip_are_split(stub, L, plan):
+    """At most about a second of work a launch (2^30 site updates, 2^20 sweeps), also
+    where the record interval is longer than that."""
+    h = stub.lattice(L)
+    if plan:
+        assert stub.lib.xy_set_plan(h, (i32 * 4)(plan, 0, 0, 1)) == OK
+    n = 3 * 2 ** 20 + 1
+    most = min(2 ** 20, 2 ** 30 // L ** 2)
+    for me, obs in ((0, None), (10, DEV), (n - 2, DEV)):
+        got = stub.log(lambda: stub.lib.xy_sweep(h, i64(n), i32(me), obs))
+        assert len(got) == -(-n // most) and all("k_resident" in k for k in got)
+    q = stub.quad(32)
+    got = stub.log(lambda: stub.lib.xy_quad_sweep(q, i64(n), i32(n - 2), DEV))
+    assert len(got) == -(-n // 2 ** 20) and all("k_resident_quad" in k for k in got)
