@@ -158,7 +158,7 @@ static hipError_t pick_deep(const SweepArgs& a, const DeepPlan& d, int n, int me
 template <typename T>
 static hipError_t go_deep(const SweepArgs& a, const DeepPlan& d, int n, int me, int phase, double* part, hipStream_t s)
 {
-    const bool meas = me > 0 && (n + phase) / me > phase / me;
+    const bool meas = me > 0 && n >= me - phase;    // phase < me
     if (a.L % 4)
         return meas ? pick_deep<T, true, kMeasPair>(a, d, n, me, phase, part, s)
                     : pick_deep<T, true, kMeasNone>(a, d, n, me, phase, part, s);
@@ -250,7 +250,7 @@ static hipError_t run_deep_quad(const float4* src, float4* dst, int L, uint32_t 
 hipError_t launch_deep_quad(const float4* src, float4* dst, int L, uint32_t sweep, const Params4& p, const DeepPlan& d,
                             int n, int me, int phase, double* part, hipStream_t s)
 {
-    const bool meas = me > 0 && (n + phase) / me > phase / me;
+    const bool meas = me > 0 && n >= me - phase;    // phase < me
 #define XY_DEEP(nt, r)                                                                                           \
     if (deep_fits<nt, r>(d))                                                                                     \
         return meas ? run_deep_quad<nt, r, kMeasQuad>(src, dst, L, sweep, p, d, n, me, phase, part, s)            \

@@ -118,7 +118,7 @@ bool deep_region(int L, int n, DeepPlan* d);
 // that gain from it; `meas`: for passes with a measured sweep.
 bool deep_choose(int L, int64_t n, bool meas, DeepPlan* d, int* nmax);
 // n sweeps from a.src to a.dst (two buffers).  Sweep j (1-based) is measured when
-// me > 0 and (j + phase) % me == 0; the k-th measured one leaves a record of
+// me > 0 and (j + phase) % me == 0, phase < me; the k-th measured one leaves a record of
 // region b at part[(k * tx * ty + b) * 8].
 hipError_t launch_deep(const SweepArgs& a, const DeepPlan& d, int n, int me, int phase, double* part, hipStream_t s);
 // nrec records of np partial records each, back to back in `part`, into out[0 ..];

@@ -104,3 +104,14 @@ def test_long_calls_on_chip_are_split(stub, L, plan):
     q = stub.quad(32)
     got = stub.log(lambda: stub.lib.xy_quad_sweep(q, i64(n), i32(n - 2), DEV))
     assert len(got) == -(-n // 2 ** 20) and all("k_resident_quad" in k for k in got)
+
+
+@pytest.mark.parametrize("L,n,me,phase,measured", [
+    (256, 8, INT32_MAX, INT32_MAX - 1, True), (256, 8, INT32_MAX, INT32_MAX - 8, True),
+    (256, 8, INT32_MAX, INT32_MAX - 9, False), (1002, 4, 10, 6, True), (1002, 4, 10, 5, False), (64, 1, 1, 0, True),
+    (64, 3, 0, 0, False)])
+def test_passes_of_several_sweeps_measure_when_an_interval_ends_in_them(stub, L, n, me, phase, measured):
+    """The last template argument of k_deep says how a pass gathers records (0: none)."""
+    got = stub.log(lambda: stub.lib.stub_launch_deep(L, n, me, phase))
+    assert len(got) == 1 and got[0].startswith("_ZN3xyk6k_deepI")
+    assert ("ELi0EEE" not in got[0]) == measured, got
