@@ -306,14 +306,16 @@ static int quad_deep_sweeps(xy_quad* q, const xyk::DeepPlan& plan, int nmax, int
         if (held == 0) return hipSuccess;
         hipError_t e = xyk::launch_finalize_many(q->partials, np, 4 * held, obs + out * 4,
                                                  base + (uint64_t)(out + 1) * (uint64_t)me, me, q->stream, 4);
-        out += held;
-        held = 0;
+        if (e == hipSuccess) {
+            out += held;
+            held = 0;
+        }
         return e;
     };
     for (int64_t k = 0; k < passes; ++k) {
         const int n = (int)(n_sweeps / passes + (k < n_sweeps % passes));
         const int phase = me ? (int)(j % me) : 0, nrec = me ? (int)((j + n) / me - j / me) : 0;
-        hipError_t e = held + nrec > room ? XY_LAUNCH(flush()) : hipSuccess;
+        hipError_t e = held > 0 && held + nrec > room ? XY_LAUNCH(flush()) : hipSuccess;
         if (e == hipSuccess) {
             xyk::DeepPlan d = plan;
             e = xyk::deep_region(q->L, n, &d)
@@ -333,8 +335,11 @@ static int quad_deep_sweeps(xy_quad* q, const xyk::DeepPlan& plan, int nmax, int
         j += n;
         q->sweep += (uint64_t)n;
     }
-    hipError_t e = XY_LAUNCH(flush());
-    return e == hipSuccess ? XY_OK : xyr::hip_fail(e, "xy_quad_sweep: finalize");
+    hipError_t e = held > 0 ? XY_LAUNCH(flush()) : hipSuccess;
+    if (e == hipSuccess) return XY_OK;
+    const int rc = xyr::hip_fail(e, "xy_quad_sweep: finalize");
+    (void)flush();
+    return rc;
 }
 
 // Single sweeps of the four lattices apart.  The first sweep writes them (into the

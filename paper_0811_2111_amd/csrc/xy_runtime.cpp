@@ -413,7 +413,10 @@ static int deep_sweeps(xy_lattice* h, const xyk::DeepPlan plan[2], int nmax, int
         h->sweep += (uint64_t)n;
     }
     hipError_t e = flush(true);
-    return e == hipSuccess ? XY_OK : hip_fail(e, "finalize launch");
+    if (e == hipSuccess) return XY_OK;
+    const int rc = hip_fail(e, "finalize launch");
+    (void)flush(false);
+    return rc;
 }
 
 // Schedules the library takes on its own where no plan was asked for and no

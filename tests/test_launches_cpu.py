@@ -115,3 +115,20 @@ def test_passes_of_several_sweeps_measure_when_an_interval_ends_in_them(stub, L,
     got = stub.log(lambda: stub.lib.stub_launch_deep(L, n, me, phase))
     assert len(got) == 1 and got[0].startswith("_ZN3xyk6k_deepI")
     assert ("ELi0EEE" not in got[0]) == measured, got
+
+
+def fail_at(stub, fn, after):
+    """The kernels that a call launches whose (after + 1)-th launch point fails."""
+    def go():
+        assert stub.lib.xy_test_inject_failure(after) == OK
+        assert fn() == EHIP
+        assert stub.lib.xy_test_inject_failure(-1) == OK
+    return stub.log(go)
+
+
+def test_a_failed_last_reduction_keeps_the_records(stub):
+    """Passes of several sweeps reduce their records together at the end of a call."""
+    for h, fn in ((stub.lattice(256), stub.lib.xy_sweep), (stub.quad(256), stub.lib.xy_quad_sweep)):
+        full = stub.log(lambda: fn(h, i64(20), i32(2), DEV))
+        assert "finalize_many" in full[-1]
+        assert fail_at(stub, lambda: fn(h, i64(20), i32(2), DEV), len(full) - 1) == full
