@@ -274,6 +274,17 @@ static xyd::Params4 quad_params(const xy_quad* q)
     return p;
 }
 
+// A launch that the state needs to agree with the counter, also after a failed one:
+// launched again if it fails.
+template <typename F>
+static void quad_finish(int& rc, const char* what, F launch)
+{
+    hipError_t e = rc == XY_OK ? XY_LAUNCH(launch()) : launch();
+    if (e == hipSuccess) return;
+    if (rc == XY_OK) rc = xyr::hip_fail(e, what);
+    (void)launch();
+}
+
 // Every sweep in one launch of four workgroups (L = 32; long calls in several).
 static int quad_resident_sweeps(xy_quad* q, int64_t n_sweeps, int32_t me, xy_obs* obs)
 {
@@ -384,14 +395,13 @@ static int quad_plane_sweeps(xy_quad* q, int64_t n_sweeps, int32_t me, xy_obs* o
                   back ? 2 : 1, xyk::planes_records(q->L));
     }
     if (e == hipSuccess && last) e = convert(true);
-    const int rc = e == hipSuccess ? XY_OK : xyr::hip_fail(e, "xy_quad_sweep: launch");
+    int rc = e == hipSuccess ? XY_OK : xyr::hip_fail(e, "xy_quad_sweep: launch");
     // also after a failed launch, so that the state agrees with the counter
     if (where == 2)
         (void)hipMemcpyAsync(q->pingpong, q->state, quad_state_bytes(q->L), hipMemcpyDeviceToDevice, q->stream);
-    if (where != 0) {
-        e = xyk::launch_quad_join((const float*)q->pingpong, q->state, q->L, q->stream);
-        if (rc == XY_OK && e != hipSuccess) return xyr::hip_fail(e, "xy_quad_sweep: launch");
-    }
+    if (where != 0)
+        quad_finish(rc, "xy_quad_sweep: launch",
+                    [&] { return xyk::launch_quad_join((const float*)q->pingpong, q->state, q->L, q->stream); });
     return rc;
 }
 
@@ -579,20 +589,23 @@ int xy_quad_hmc(xy_quad* q, int64_t n_traj, int32_t n_md, double eps, void* hmc_
     hipError_t e = XY_LAUNCH(xyk::launch_quad_split(q->state, planes, q->L, q->stream));
     if (e != hipSuccess) return xyr::hip_fail(e, "xy_quad_hmc: launch");
     int rc = XY_OK;
-    for (int64_t j = 0; j < n_traj && rc == XY_OK; ++j) {
+    int64_t done = 0;
+    for (; done < n_traj && rc == XY_OK;) {
         e = XY_LAUNCH(xyk::launch_quad_hmc_trajectory(planes, (float*)q->state, w, q->L, q->beta, eps, n_md, steps,
                                                       (uint32_t)q->sweep, keys,
-                                                      obs_dev ? obs_dev + (size_t)j * 4 : nullptr, j > 0, q->stream));
-        if (e != hipSuccess) rc = xyr::hip_fail(e, "xy_quad_hmc: launch");
-        else q->sweep += 1;
-        if (rc == XY_OK ? j == n_traj - 1 : j > 0) {
-            e = xyk::launch_quad_hmc_restore(planes, w, q->L, q->stream);
-            if (rc == XY_OK && e != hipSuccess) rc = xyr::hip_fail(e, "xy_quad_hmc: launch");
+                                                      obs_dev ? obs_dev + (size_t)done * 4 : nullptr, done > 0,
+                                                      q->stream));
+        if (e != hipSuccess) {
+            rc = xyr::hip_fail(e, "xy_quad_hmc: launch");
+        } else {
+            q->sweep += 1;
+            ++done;
         }
     }
-    // also after a failed trajectory, so that the state agrees with the counter
-    e = xyk::launch_quad_join(planes, q->state, q->L, q->stream);
-    if (rc == XY_OK && e != hipSuccess) rc = xyr::hip_fail(e, "xy_quad_hmc: launch");
+    if (done > 0)
+        quad_finish(rc, "xy_quad_hmc: launch",
+                    [&] { return xyk::launch_quad_hmc_restore(planes, w, q->L, q->stream); });
+    quad_finish(rc, "xy_quad_hmc: launch", [&] { return xyk::launch_quad_join(planes, q->state, q->L, q->stream); });
     return rc;
 }
 

@@ -581,8 +581,12 @@ int xy_hmc(xy_lattice* h, int64_t n_traj, int32_t n_md, double eps, void* hmc_wo
         h->sweep += 1;
     }
     if (n_traj == 0) return XY_OK;
-    hipError_t e = xyk::launch_hmc_restore((float*)h->state, w, h->L, h->stream);
-    return e == hipSuccess ? XY_OK : hip_fail(e, "hmc trajectory launch");
+    hipError_t e = XY_LAUNCH(xyk::launch_hmc_restore((float*)h->state, w, h->L, h->stream));
+    if (e == hipSuccess) return XY_OK;
+    const int rc = hip_fail(e, "hmc restore launch");
+    // the counter stands after the last trajectory: its rejected angles must not stay
+    (void)xyk::launch_hmc_restore((float*)h->state, w, h->L, h->stream);
+    return rc;
 }
 
 int xy_hmc_set_steps_per_pass(xy_lattice* h, int32_t steps)

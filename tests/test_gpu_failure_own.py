@@ -54,3 +54,24 @@ def test_failure_at_every_launch_point(make, L, n, every, kept):
         h.sweep(n - s)
         assert torch.equal(h.state, ref.state) and h.sweep_count == n, after
     assert failed >= 3
+
+
+@pytest.mark.parametrize("make,L", [("lattice", 64), ("quad", 64)])
+def test_hmc_failure_at_every_launch_point(make, L):
+    """Trajectories that are rejected: the angles are those before them."""
+    make = globals()[make]
+    for eps in (0.1, 2.5):
+        for after in range(100):
+            h, ref = make(L), make(L)
+            xy.xy_test_inject_failure(after)
+            try:
+                h.hmc(3, 7, eps)
+                break
+            except xy.XYError as e:
+                assert e.code == xy.XY_EHIP
+            finally:
+                xy.xy_test_inject_failure(-1)
+            if h.sweep_count:
+                ref.hmc(h.sweep_count, 7, eps)
+            assert torch.equal(h.state, ref.state), (eps, after)
+        assert after >= 4                              # three trajectories and what follows them

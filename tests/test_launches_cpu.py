@@ -132,3 +132,20 @@ def test_a_failed_last_reduction_keeps_the_records(stub):
         full = stub.log(lambda: fn(h, i64(20), i32(2), DEV))
         assert "finalize_many" in full[-1]
         assert fail_at(stub, lambda: fn(h, i64(20), i32(2), DEV), len(full) - 1) == full
+
+
+def test_failed_last_launches_are_made_up_for(stub):
+    """The undoing of a call's last trajectory and the joining of a quad's lattices: the
+    call fails, but the angles are those of the sweep counter."""
+    h, q, w = stub.lattice(64), stub.quad(64), stub.quad(864)
+    hmc = lambda: stub.lib.xy_hmc(h, i64(2), 5, dbl(0.1), DEV, sz(1 << 40), None)  # noqa: E731
+    qhmc = lambda: stub.lib.xy_quad_hmc(q, i64(2), 5, dbl(0.1), DEV, sz(1 << 40), None)  # noqa: E731
+    sweeps = lambda: stub.lib.xy_quad_sweep(w, i64(9), 0, None)  # noqa: E731
+    # launch points: a trajectory is one; a quad's call splits first and joins last
+    for fn, points, counter in ((hmc, [2], (h, "xy_get_sweep")), (qhmc, [3, 4], (q, "xy_quad_get_sweep")),
+                                (sweeps, [9], (w, "xy_quad_get_sweep"))):
+        full = stub.log(lambda: fn())
+        per = stub.count(*counter)
+        for after in points:
+            assert fail_at(stub, fn, after) == full
+        assert stub.count(*counter) == per * (1 + len(points))
