@@ -334,9 +334,11 @@ int xy_hmc_get_steps_per_pass(const xy_lattice* h, int32_t* steps);
 int xy_quad_hmc_work_bytes(int32_t L, size_t* bytes);
 int xy_quad_hmc(xy_quad* q, int64_t n_traj, int32_t n_md, double eps, void* hmc_work, size_t hmc_len,
                 xy_hmc_obs* obs_dev);
-/* Leap-frog steps per pass of xy_quad_hmc (1 .. 4, default 4; XY_EINVAL
- * otherwise), as xy_hmc_set_steps_per_pass; 4 stands for that call's default, 7.
- * The trajectory is bit for bit the same. */
+/* Leap-frog steps per pass of xy_quad_hmc (1 .. 4; XY_EINVAL otherwise), as
+ * xy_hmc_set_steps_per_pass.  Until a setting is made the library chooses, at
+ * present passes of up to 7 steps (xy_hmc's default), and
+ * xy_quad_hmc_get_steps_per_pass reports 4, the largest setting.  The trajectory
+ * is bit for bit the same. */
 int xy_quad_hmc_set_steps_per_pass(xy_quad* q, int32_t steps);
 int xy_quad_hmc_get_steps_per_pass(const xy_quad* q, int32_t* steps);
 

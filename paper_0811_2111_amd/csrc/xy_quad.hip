@@ -220,7 +220,7 @@ static hipError_t launch_quad(const float4* src, float4* dst, int L, int tx, int
 namespace {
 
 constexpr uint32_t kQuadMagic = 0x51554144u;   // "QUAD"
-constexpr int kQuadHmcSteps = 4;               // largest (and default) steps-per-pass setting
+constexpr int kQuadHmcSteps = 4;               // largest steps-per-pass setting
 
 size_t quad_state_bytes(int L) { return (size_t)L * (size_t)L * sizeof(float4); }
 // one partial record per wave (4 per 256-thread tile) and replica; the smallest
@@ -256,7 +256,7 @@ struct xy_quad {
     uint64_t sweep;
     int32_t tile_x, tile_y;
     bool tile_set;         // the caller chose the tile: every sweep takes it
-    int32_t hmc_steps;     // leap-frog steps per pass of xy_quad_hmc (1 .. 4)
+    int32_t hmc_steps;     // leap-frog steps per pass of xy_quad_hmc (1 .. 4; 0: the library's choice)
 };
 
 static bool quad_live(const xy_quad* q) { return q && q->magic == kQuadMagic; }
@@ -447,7 +447,7 @@ int xy_quad_init(xy_quad** out, const uint64_t* seeds, int32_t L, const double* 
     q->tile_x = L % 128 == 0 ? 128 : 32;
     q->tile_y = L % 128 == 0 ? 8 : 16;
     q->tile_set = false;
-    q->hmc_steps = kQuadHmcSteps;
+    q->hmc_steps = 0;
     const int Hh = L / 2, P = (Hh + 1) / 2;
     hipLaunchKernelGGL(xyk::k_quad_init, dim3((P + 63) / 64, (L + 3) / 4, 2), dim3(64, 4), 0, q->stream, q->state, L,
                        quad_params(q), start == XY_HOT ? 1 : 0);
@@ -582,9 +582,9 @@ int xy_quad_hmc(xy_quad* q, int64_t n_traj, int32_t n_md, double eps, void* hmc_
     const xyk::QuadHmcWork w = xyk::quad_hmc_carve(hmc_work, q->L);
     // The replicas run as four lattices: split into the second buffer at the start of
     // the call, joined into the state at its end; the state is the second angle
-    // buffer of the trajectories meanwhile.  The setting's largest value stands for
-    // the passes xy_hmc takes by default.
-    const int steps = q->hmc_steps == kQuadHmcSteps ? 7 : q->hmc_steps;
+    // buffer of the trajectories meanwhile.  Passes as xy_hmc's default if none were
+    // asked for.
+    const int steps = q->hmc_steps ? q->hmc_steps : 7;
     float* planes = (float*)q->pingpong;
     hipError_t e = XY_LAUNCH(xyk::launch_quad_split(q->state, planes, q->L, q->stream));
     if (e != hipSuccess) return xyr::hip_fail(e, "xy_quad_hmc: launch");
@@ -620,7 +620,7 @@ int xy_quad_hmc_set_steps_per_pass(xy_quad* q, int32_t steps)
 int xy_quad_hmc_get_steps_per_pass(const xy_quad* q, int32_t* steps)
 {
     if (!quad_live(q) || !steps) return XY_ESTATE;
-    *steps = q->hmc_steps;
+    *steps = q->hmc_steps ? q->hmc_steps : kQuadHmcSteps;
     return XY_OK;
 }
 

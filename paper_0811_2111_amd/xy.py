@@ -555,6 +555,8 @@ class Quad:
 
     @property
     def hmc_steps_per_pass(self) -> int:
+        """The leap-frog steps per pass that are set (4, the largest, if none were: the
+        library then chooses, at present up to 7)."""
         v = ctypes.c_int32()
         check(_lib.xy_quad_hmc_get_steps_per_pass(self.h, ctypes.byref(v)), "xy_quad_hmc_get_steps_per_pass")
         return v.value

@@ -149,3 +149,14 @@ def test_failed_last_launches_are_made_up_for(stub):
         for after in points:
             assert fail_at(stub, fn, after) == full
         assert stub.count(*counter) == per * (1 + len(points))
+
+
+def test_quad_hmc_steps_per_pass_are_those_set(stub):
+    """Nine steps: in passes of at most the setting, of up to seven if none was made."""
+    q = stub.quad(64)
+    passes = lambda: sum("k_qhmc_pass" in k for k in stub.log(  # noqa: E731
+        lambda: stub.lib.xy_quad_hmc(q, i64(1), 9, dbl(0.1), DEV, sz(1 << 40), None)))
+    assert passes() == 2
+    for steps, want in ((1, 9), (2, 5), (3, 3), (4, 3)):
+        assert stub.lib.xy_quad_hmc_set_steps_per_pass(q, steps) == OK
+        assert passes() == want
