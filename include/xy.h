@@ -123,8 +123,7 @@ typedef struct xy_obs {
  *                   library's own in its place (L < 56: every sweep of a call in
  *                   one launch, the lattice on chip; up to L = 1100: several sweeps
  *                   per launch on overlapping regions) and larger ones single-sweep
- *                   tiles that need not divide L or strips of one wave, unless
- *                   xy_kernel_timer is on. */
+ *                   tiles that need not divide L or strips of one wave. */
 enum { XY_PLAN_AUTO = 0, XY_PLAN_STREAM = 1, XY_PLAN_FUSED = 2, XY_PLAN_STRIP = 3, XY_PLAN_RESIDENT = 4 };
 typedef struct xy_plan {
     int32_t kind;
@@ -372,9 +371,11 @@ int xy_batch_hmc(xy_batch* b, int64_t n_traj, int32_t n_md, double eps, void* hm
  * xy_hmc_set_steps_per_pass.  XY_EINVAL otherwise. */
 int xy_batch_hmc_set_steps_per_pass(xy_batch* b, int32_t steps);
 
-/* Profiling support: time the tiled sweep kernel launches (XY_PLAN_FUSED and
- * XY_PLAN_STRIP; one launch per pass) of the handle's next calls with HIP events
- * recorded on its stream right before and after each launch, for up to
+/* Profiling support: time the sweep kernel launches of XY_PLAN_FUSED and
+ * XY_PLAN_STRIP (one launch per pass) and of the library's own schedules
+ * (XY_PLAN_AUTO; one launch holds several sweeps of a small lattice) in the
+ * handle's next calls.  The timer does not change what a call launches: HIP events
+ * are recorded on its stream right before and after each launch, for up to
  * `capacity` launches (0 turns the timer off and frees its events; host objects
  * only).  xy_kernel_timer_read waits for the last timed launch, returns the sum
  * of their durations in ms and their number, and restarts the count.  The

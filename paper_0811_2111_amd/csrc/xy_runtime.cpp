@@ -215,6 +215,17 @@ static xyk::SweepArgs args_of(const xy_lattice* h)
     return a;
 }
 
+// A sweep launch between two events of the kernel timer while it has pairs left.
+template <typename F>
+static hipError_t timed(xy_lattice* h, F launch)
+{
+    const bool on = h->tn < h->tcap;
+    if (on) (void)hipEventRecord(h->tev[2 * h->tn], h->stream);
+    const hipError_t e = launch();
+    if (on && e == hipSuccess) (void)hipEventRecord(h->tev[2 * h->tn++ + 1], h->stream);
+    return e;
+}
+
 extern "C" {
 
 int xy_state_bytes(int32_t L, int32_t precision, size_t* state, size_t* workspace)
@@ -350,9 +361,11 @@ static int resident_sweeps(xy_lattice* h, int64_t n_sweeps, int32_t me, xy_obs* 
     for (int64_t done = 0; done < n_sweeps;) {
         const int64_t m = std::min<int64_t>(xyk::resident_sweeps_max(h->L), n_sweeps - done);
         xyk::SweepArgs a = args_of(h);
-        auto launch = own ? xyk::launch_resident_any : xyk::launch_resident;
-        hipError_t e = XY_LAUNCH(launch(a, (int)m, me, me ? (int)(done % me) : 0, me ? obs + done / me : nullptr,
-                                        h->stream));
+        const int phase = me ? (int)(done % me) : 0;
+        xy_obs* rec = me ? obs + done / me : nullptr;
+        hipError_t e = XY_LAUNCH(
+            own ? timed(h, [&] { return xyk::launch_resident_any(a, (int)m, me, phase, rec, h->stream); })
+                : xyk::launch_resident(a, (int)m, me, phase, rec, h->stream));
         if (e != hipSuccess) return hip_fail(e, "resident sweep launch");
         h->sweep += (uint64_t)m;
         done += m;
@@ -397,7 +410,9 @@ static int deep_sweeps(xy_lattice* h, const xyk::DeepPlan plan[2], int nmax, int
             a.dst = (k & 1) ? h->state : h->w.pingpong;
             xyk::DeepPlan d = plan[nrec > 0];
             e = xyk::deep_region(h->L, n, &d)
-                    ? XY_LAUNCH(xyk::launch_deep(a, d, n, me, phase, h->w.partials + (size_t)held * np * 8, h->stream))
+                    ? XY_LAUNCH(timed(h, [&] {
+                          return xyk::launch_deep(a, d, n, me, phase, h->w.partials + (size_t)held * np * 8, h->stream);
+                      }))
                     : hipErrorInvalidValue;
         }
         if (e != hipSuccess) {
@@ -419,8 +434,7 @@ static int deep_sweeps(xy_lattice* h, const xyk::DeepPlan plan[2], int nmax, int
     return rc;
 }
 
-// Schedules the library takes on its own where no plan was asked for and no
-// launches are to be timed: the whole lattice in one workgroup while that is
+// Schedules the library takes on its own where no plan was asked for: the whole lattice in one workgroup while that is
 // faster than any tiling (L < 56: 0.7 to 1.8 us a sweep, 1.3 to 2.8 with a record
 // every sweep; two half-sweep launches take 6, with a record 12), then passes of
 // several sweeps.  Returns false if neither applies.
@@ -428,7 +442,7 @@ static bool own_schedule(xy_lattice* h, int64_t n_sweeps, int32_t me, xy_obs* ob
 {
     xyk::DeepPlan plan[2];
     int nmax, nmeas = 0;
-    if (!h->own_plan || h->tcap > 0 || n_sweeps == 0) return false;
+    if (!h->own_plan || n_sweeps == 0) return false;
     if (h->L < 56 || (n_sweeps == 1 && h->L < 64)) *rc = resident_sweeps(h, n_sweeps, me, obs, true);
     else if (xyk::deep_choose(h->L, n_sweeps, true, &plan[1], &nmeas) &&
              xyk::deep_choose(h->L, n_sweeps, false, &plan[0], &nmax))
@@ -451,7 +465,7 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
     // Where the plan is the library's choice, single sweeps take the faster of the
     // ragged tiles in place of half-sweeps and, unmeasured, of a slower tile shape,
     // and large FP32 lattices strips of one wave.
-    const bool own = h->own_plan && h->tcap == 0;
+    const bool own = h->own_plan;
     const int own_tx = own ? xyk::ragged_tile_x(h->L) : 0;
     auto walk = [&](bool meas_j) { return own && xyk::walk_supported(h->L, h->precision, meas_j); };
     const bool stream = h->plan.kind == XY_PLAN_STREAM;
@@ -499,8 +513,6 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
         unsigned mask = 0;
         for (int js = 0; js < m; ++js)
             if (measured(j + js + 1)) mask |= 1u << js;
-        const bool timing = h->tn < h->tcap;
-        if (timing) (void)hipEventRecord(h->tev[2 * h->tn], h->stream);
         auto launch = [&] {
             if (walk(mask != 0)) return xyk::launch_walk(a, mask != 0, h->w.partials, h->stream);
             if (strip)
@@ -509,9 +521,8 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
                 return xyk::launch_ragged(a, own_tx, mask != 0, h->w.partials, h->stream);
             return xyk::launch_fused(a, h->plan.tile_x, h->plan.tile_y, m, mask, h->w.partials, h->stream);
         };
-        hipError_t e = XY_LAUNCH(launch());
+        hipError_t e = XY_LAUNCH(timed(h, launch));
         if (e != hipSuccess) return fail(e, "fused sweep launch");
-        if (timing) (void)hipEventRecord(h->tev[2 * h->tn++ + 1], h->stream);
         done_passes = q + 1;
         const uint64_t s0 = h->sweep;
         h->sweep += m;

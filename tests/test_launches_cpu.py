@@ -160,3 +160,17 @@ def test_quad_hmc_steps_per_pass_are_those_set(stub):
     for steps, want in ((1, 9), (2, 5), (3, 3), (4, 3)):
         assert stub.lib.xy_quad_hmc_set_steps_per_pass(q, steps) == OK
         assert passes() == want
+
+
+@pytest.mark.parametrize("L,kernel", [(32, "k_resident"), (256, "k_deep"), (1002, "k_deep"), (1202, "k_ragged"),
+                                      (2304, "k_fused"), (3500, "k_walk"), (4096, "k_walk"), (16384, "k_strip")])
+def test_kernel_timer_times_what_runs_without_it(stub, L, kernel):
+    h = stub.lattice(L)
+    go = lambda: stub.lib.xy_sweep(h, i64(20), i32(10), DEV)  # noqa: E731
+    plain = stub.log(go)
+    assert stub.lib.xy_kernel_timer(h, i32(100)) == OK
+    assert stub.log(go) == plain
+    ms, n = dbl(), i64()
+    assert stub.lib.xy_kernel_timer_read(h, ctypes.byref(ms), ctypes.byref(n)) == OK
+    sweeps = [k for k in plain if "finalize" not in k]
+    assert any(kernel in k for k in sweeps) and n.value == len(sweeps) and ms.value == len(sweeps)
