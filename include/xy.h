@@ -393,8 +393,11 @@ int xy_debug_sweep(xy_lattice* h, uint8_t* accept_dev, float* dE_dev);
 
 /* Time each candidate plan for `sweeps_per_trial` sweeps (after one untimed
  * trial) on the handle's stream, in two rounds over the candidates, and select
- * the one with the fastest trial; *best receives it and
- * the handle keeps it.  The plans differ in how sublattices are staged through
+ * the one with the fastest trial; *best receives it, to be given to xy_set_plan of
+ * other handles, and the handle keeps it.  Where the library's own schedule (see
+ * XY_PLAN_AUTO) is not the default plan it is timed in that plan's place, and *best
+ * is XY_PLAN_AUTO if it was the fastest; the cache file then holds the default plan,
+ * which stands for the library's choice there.  The plans differ in how sublattices are staged through
  * on-chip memory with duplicated borders (section 2.2), never in the trajectory.
  * The trials advance the handle's state and counter: run it on a scratch
  * lattice.  If cache_path != NULL the result is merged into that JSON file under
@@ -402,8 +405,8 @@ int xy_debug_sweep(xy_lattice* h, uint8_t* accept_dev, float* dE_dev);
  * cache file could not be written (the handle still keeps the best plan). */
 int xy_autotune(xy_lattice* h, int32_t sweeps_per_trial, const char* cache_path, xy_plan* best);
 
-/* Look up a tuned plan for (L, precision) in the JSON cache file written by
- * xy_autotune; XY_EINVAL if the file or the entry is missing. */
+/* Look up a tuned plan for (L, precision), as xy_autotune returned it, in the JSON
+ * cache file that it wrote; XY_EINVAL if the file or the entry is missing. */
 int xy_tuned_plan(const char* cache_path, int32_t L, int32_t precision, xy_plan* plan);
 
 /* ----------------------------------------------------------------- batches

@@ -3,6 +3,7 @@
 // error mapping and the plan autotuner.  Batches live in xy_batch.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -234,6 +235,21 @@ int xy_state_bytes(int32_t L, int32_t precision, size_t* state, size_t* workspac
     if (state) *state = xyk::state_bytes(L, precision);
     if (workspace) *workspace = xyk::work_bytes(L, precision);
     return XY_OK;
+}
+
+constexpr int64_t kManySweeps = 100;     // a call long enough for every schedule
+
+// Whether calls of n unmeasured sweeps run something else than the default plan where
+// no plan was asked for (see own_schedule and xy_sweep).
+static bool own_differs(int32_t L, int32_t precision, int64_t n)
+{
+    xyk::DeepPlan p;
+    int m;
+    if (L < 56 || xyk::deep_choose(L, n, false, &p, &m) || xyk::walk_supported(L, precision, false)) return true;
+    const xy_plan d = default_plan(L, precision);
+    const int tx = xyk::ragged_tile_x(L);
+    if (tx == 0 || d.kind == XY_PLAN_STRIP) return false;
+    return !(d.kind == XY_PLAN_FUSED && d.tile_x == tx && d.tile_y == 16);
 }
 
 // The tuned plan if one is cached, else the default.  A tuned plan that is the
@@ -737,6 +753,10 @@ int xy_autotune(xy_lattice* h, int32_t sweeps_per_trial, const char* cache_path,
 {
     if (!live(h)) return XY_ESTATE;
     if (sweeps_per_trial < 2) return XY_EINVAL;
+    // The library's own choice, where it is not the default plan, is a candidate in that
+    // plan's place: XY_PLAN_AUTO, which a handle it is given to runs the same way.
+    const xy_plan own = default_plan(h->L, h->precision);
+    const bool differs = own_differs(h->L, h->precision, sweeps_per_trial);
     std::vector<xy_plan> cands;
     cands.push_back({XY_PLAN_STREAM, 0, 0, 1});
     static const int shapes[][3] = {{64, 16, 1}, {64, 32, 1}, {128, 16, 1}, {128, 32, 1}, {128, 64, 1},
@@ -752,6 +772,11 @@ int xy_autotune(xy_lattice* h, int32_t sweeps_per_trial, const char* cache_path,
         xy_plan p{XY_PLAN_STRIP, s[0], s[1], 1};
         if (plan_ok(h->L, p)) cands.push_back(p);
     }
+    if (differs) {
+        cands.erase(std::remove_if(cands.begin(), cands.end(), [&](const xy_plan& p) { return same_plan(p, own); }),
+                    cands.end());
+        cands.push_back({XY_PLAN_AUTO, 0, 0, 1});
+    }
     hipEvent_t e0, e1;
     hipError_t e = hipEventCreate(&e0);
     if (e != hipSuccess) return hip_fail(e, "hipEventCreate");
@@ -760,15 +785,10 @@ int xy_autotune(xy_lattice* h, int32_t sweeps_per_trial, const char* cache_path,
         (void)hipEventDestroy(e0);
         return hip_fail(e, "hipEventCreate");
     }
-    // the library's own choice, which may run several sweeps per launch, is a
-    // candidate under the name of the plan it stands for
-    const xy_plan own = default_plan(h->L, h->precision);
-    cands.push_back({XY_PLAN_AUTO, 0, 0, 1});
     const xy_plan saved = h->plan;
     const bool saved_own = h->own_plan;
     double best_t = 1e300;
-    xy_plan best_p = saved;
-    bool best_own = saved_own;
+    xy_plan best_p = cands.front();
     int rc = XY_OK;
     // two rounds over the candidates, each candidate's best trial counting, so
     // that one slow trial (a clock change, another process) does not decide
@@ -776,8 +796,7 @@ int xy_autotune(xy_lattice* h, int32_t sweeps_per_trial, const char* cache_path,
     trials.insert(trials.end(), cands.begin(), cands.end());
     for (const xy_plan& t : trials) {
         h->own_plan = t.kind == XY_PLAN_AUTO;
-        const xy_plan p = h->own_plan ? own : t;
-        h->plan = p;
+        h->plan = h->own_plan ? own : t;
         if (h->sweep + 2ull * (uint64_t)sweeps_per_trial + 2 >= 0xffffffffull) h->sweep = 0;
         rc = xy_sweep(h, sweeps_per_trial, 0, nullptr);  // warm-up (sets LDS attributes, caches)
         if (rc != XY_OK) break;
@@ -790,19 +809,21 @@ int xy_autotune(xy_lattice* h, int32_t sweeps_per_trial, const char* cache_path,
         if ((e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess) { rc = hip_fail(e, "hipEventElapsedTime"); break; }
         if (ms < best_t) {
             best_t = ms;
-            best_p = p;
-            best_own = h->own_plan;
+            best_p = t;
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    h->plan = (rc == XY_OK) ? best_p : saved;
-    h->own_plan = (rc == XY_OK) ? best_own : saved_own;
+    h->plan = saved;
+    h->own_plan = saved_own;
     if (rc != XY_OK) return rc;
+    const xy_plan kept = best_p.kind == XY_PLAN_AUTO ? own : best_p;    // the plan reported and cached
+    h->plan = kept;
+    h->own_plan = same_plan(kept, own);
     if (best) *best = best_p;
     if (cache_path) {
         const double gupd = (double)h->L * h->L * sweeps_per_trial / (best_t * 1e-3) / 1e9;
-        if (!cache_store(cache_path, h->L, h->precision, best_p, gupd)) return XY_EIO;
+        if (!cache_store(cache_path, h->L, h->precision, kept, gupd)) return XY_EIO;
     }
     return XY_OK;
 }
@@ -811,7 +832,11 @@ int xy_tuned_plan(const char* cache_path, int32_t L, int32_t precision, xy_plan*
 {
     if (!plan || !cache_path) return XY_ESTATE;
     if (!valid_L(L)) return XY_EINVAL;
-    return cache_lookup(cache_path, L, precision, plan) ? XY_OK : XY_EINVAL;
+    if (!cache_lookup(cache_path, L, precision, plan)) return XY_EINVAL;
+    // the default plan's entry stands for the library's choice (see auto_plan)
+    if (same_plan(*plan, default_plan(L, precision)) && own_differs(L, precision, kManySweeps))
+        *plan = xy_plan{XY_PLAN_AUTO, 0, 0, 1};
+    return XY_OK;
 }
 
 }  // extern "C"

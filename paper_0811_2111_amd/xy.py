@@ -377,6 +377,8 @@ class Lattice:
         return t.value, n.value
 
     def autotune(self, sweeps_per_trial: int = 4, cache_path=None):
+        """Pick the fastest plan; returns it, to be given to other lattices (XY_PLAN_AUTO
+        where the library's own schedule is the fastest)."""
         p = xy_plan()
         cp = cache_path.encode() if cache_path else None
         check(_lib.xy_autotune(self.h, int(sweeps_per_trial), cp, ctypes.byref(p)), "xy_autotune")

@@ -174,3 +174,32 @@ def test_kernel_timer_times_what_runs_without_it(stub, L, kernel):
     assert stub.lib.xy_kernel_timer_read(h, ctypes.byref(ms), ctypes.byref(n)) == OK
     sweeps = [k for k in plain if "finalize" not in k]
     assert any(kernel in k for k in sweeps) and n.value == len(sweeps) and ms.value == len(sweeps)
+
+
+# the kernel made cheap, and whether the library's own schedule then wins
+@pytest.mark.parametrize("L,prec,cheap,own", [
+    (32, 0, "k_nothing", None), (54, 0, "k_nothing", True), (256, 0, "k_deep", True), (1002, 1, "k_deep", True),
+    (1202, 0, "k_ragged", True), (4096, 0, "k_walk", True), (8192, 0, "k_walk", True), (16384, 0, "k_strip", False),
+    (256, 0, "k_fusedIfLi64ELi16ELi1E", False), (4096, 0, "k_fusedIfLi128ELi32ELi1E", False),
+    (2304, 0, "k_stripIfLi256E", False)])
+def test_autotuned_plan_runs_the_same_on_another_handle(stub, L, prec, cheap, own, tmp_path):
+    """Given to xy_set_plan, looked up in the cache file, or found there by XY_PLAN_AUTO."""
+    path = str(tmp_path / "tune.json").encode()
+    run = lambda h: stub.log(lambda: stub.lib.xy_sweep(h, i64(8), 0, None))  # noqa: E731
+    tuned, best, found = stub.lattice(L, prec), (i32 * 4)(), (i32 * 4)()
+
+    def tune():
+        stub.lib.stub_cost(cheap.encode(), ctypes.c_float(0.05))
+        assert stub.lib.xy_autotune(tuned, 8, path, best) == OK
+    stub.log(tune)
+    want = run(tuned)
+    assert own is None or (best[0] == 0) == own
+    other = stub.lattice(L, prec)
+    assert stub.lib.xy_set_plan(other, best) == OK
+    assert run(other) == want
+    assert stub.lib.xy_tuned_plan(path, L, prec, found) == OK and list(found) == list(best)
+    ctypes.CDLL(None).setenv(b"XY_TUNE_CACHE", path, 1)
+    try:
+        assert run(stub.lattice(L, prec)) == want
+    finally:
+        ctypes.CDLL(None).unsetenv(b"XY_TUNE_CACHE")
