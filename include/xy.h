@@ -466,7 +466,10 @@ int xy_batch_set_schedule(xy_batch* b, int32_t schedule);   /* XY_EINVAL if not 
 int xy_batch_get_schedule(const xy_batch* b, int32_t* schedule);
 /* Time every candidate tile shape under every schedule for `sweeps_per_trial`
  * sweeps (after one untimed trial that also captures the graph) and keep the
- * fastest (shape and schedule).  The trials
+ * fastest (shape and schedule).  The batch's first shape, the one that
+ * xy_batch_get_tile reports when it is created, is timed as the batch runs without
+ * xy_batch_set_tile; if it is the fastest, other batches need the schedule only.
+ * The trials
  * advance the batch: run it on a scratch batch of the same sizes. */
 int xy_batch_autotune(xy_batch* b, int32_t sweeps_per_trial, int32_t* tile_x, int32_t* tile_y);
 /* Wait for the batch's stream and report whether any launch so far hit a barrier

@@ -1237,11 +1237,14 @@ int xy_batch_autotune(xy_batch* b, int32_t sweeps_per_trial, int32_t* tile_x, in
     double best = 1e300;
     Shape bs = b->shape;
     int bsched = b->sched;
+    bool bset = b->tile_set;
     int rc = XY_OK;
     static const int scheds[3] = {XY_BATCH_PASSES_WIDE, XY_BATCH_PASSES, XY_BATCH_PERSISTENT};
     for (int ci = 0; ci < 3 * (int)cands.size(); ++ci) {
         const Shape s = cands[ci / 3];
         b->sched = scheds[ci % 3];
+        // what a batch runs that is given this shape, the first one what it runs by itself
+        b->tile_set = ci >= 3;
         if ((rc = plan_batch(b, s)) != XY_OK) break;
         if ((rc = xy_batch_sweep(b, sweeps_per_trial, 0, nullptr)) != XY_OK) break;   // warm-up, capture
         if ((e = hipEventRecord(e0, b->stream)) != hipSuccess) { rc = xyr::hip_fail(e, "hipEventRecord"); break; }
@@ -1254,11 +1257,13 @@ int xy_batch_autotune(xy_batch* b, int32_t sweeps_per_trial, int32_t* tile_x, in
             best = ms;
             bs = s;
             bsched = b->sched;
+            bset = b->tile_set;
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     b->sched = bsched;
+    b->tile_set = bset;
     if (rc != XY_OK) return rc;
     if ((rc = plan_batch(b, bs)) != XY_OK) return rc;
     if (tile_x) *tile_x = bs.tx;

@@ -19,6 +19,7 @@ std::vector<std::pair<std::string, float>> g_costs;
 int g_left = -1;                     // launches until one fails (-1: never)
 hipError_t g_last = hipSuccess;
 float g_now = 0.f;                   // ms
+float g_start = 0.f;                 // of the capture
 struct Config {
     dim3 grid, block;
     size_t lds;
@@ -153,30 +154,36 @@ hipError_t hipStreamDestroy(hipStream_t s)
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-// A captured sequence runs as it is captured; a graph's launch is one log line.
-hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
-hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g)
+// A captured sequence is logged as it is captured; a graph's launch is one log line
+// and takes the time of the sequence.
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode)
 {
-    *g = (hipGraph_t) new int(0);
+    g_start = g_now;
     return hipSuccess;
 }
-hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t, hipGraphNode_t*, char*, size_t)
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g)
 {
-    *x = (hipGraphExec_t) new int(0);
+    *g = (hipGraph_t) new float(g_now - g_start);
+    return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t g, hipGraphNode_t*, char*, size_t)
+{
+    *x = (hipGraphExec_t) new float(*(float*)g);
     return hipSuccess;
 }
 hipError_t hipGraphDestroy(hipGraph_t g)
 {
-    delete (int*)g;
+    delete (float*)g;
     return hipSuccess;
 }
 hipError_t hipGraphExecDestroy(hipGraphExec_t x)
 {
-    delete (int*)x;
+    delete (float*)x;
     return hipSuccess;
 }
-hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t)
+hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t)
 {
+    g_now += *(float*)x;
     g_log += "graph\n";
     return hipSuccess;
 }

@@ -46,6 +46,13 @@ class Stub:
                                      sz(1 << 40), None) == OK
         return h
 
+    def batch(self, Ls):
+        h, n = vp(), len(Ls)
+        d = (dbl * n)(*[1.0] * n)
+        assert self.lib.xy_batch_init(ctypes.byref(h), n, (u64 * n)(*range(n)), (i32 * n)(*Ls), d, d, 0, 0, DEV,
+                                      sz(1 << 40), DEV, sz(1 << 40), None) == OK
+        return h
+
     def count(self, h, get="xy_get_sweep"):
         v = u64()
         assert getattr(self.lib, get)(h, ctypes.byref(v)) == OK
@@ -203,3 +210,25 @@ def test_autotuned_plan_runs_the_same_on_another_handle(stub, L, prec, cheap, ow
         assert run(stub.lattice(L, prec)) == want
     finally:
         ctypes.CDLL(None).unsetenv(b"XY_TUNE_CACHE")
+
+
+@pytest.mark.parametrize("Ls,cheap", [([64, 128], "k_batch_ragged"), ([64, 128], "k_batch_passIfLi32ELi16E"),
+                                      ([100, 200, 400], "k_batch_ragged"), ([100, 200, 400], "k_batch_pass"),
+                                      ([64, 1024], "k_batch_passIfLi64ELi32E")])
+def test_autotuned_batch_runs_the_same_on_another_handle(stub, Ls, cheap):
+    tuned, other = stub.batch(Ls), stub.batch(Ls)
+    tile, first, sched = (i32 * 2)(), (i32 * 2)(), i32()
+    at = lambda a, k: ctypes.byref(a, 4 * k)  # noqa: E731
+    run = lambda h: stub.log(lambda: stub.lib.xy_batch_sweep(h, i64(8), 0, None))  # noqa: E731
+
+    def tune():
+        stub.lib.stub_cost(cheap.encode(), ctypes.c_float(0.05))
+        assert stub.lib.xy_batch_autotune(tuned, 8, at(tile, 0), at(tile, 1)) == OK
+    stub.log(tune)
+    assert stub.lib.xy_batch_get_schedule(tuned, ctypes.byref(sched)) == OK
+    assert stub.lib.xy_batch_get_tile(other, at(first, 0), at(first, 1)) == OK
+    if list(tile) != list(first):
+        assert stub.lib.xy_batch_set_tile(other, tile[0], tile[1]) == OK
+    assert stub.lib.xy_batch_set_schedule(other, sched) == OK
+    names = lambda log: {k for k in log if "k_batch" in k}  # noqa: E731
+    assert names(run(tuned)) == names(run(other))
