@@ -239,7 +239,7 @@ __global__ void __launch_bounds__(kPassWaves * 64)
 k_hmc_pass(const float* __restrict__ src, float* __restrict__ dst, const float* __restrict__ psrc,
            float* __restrict__ pdst, int L, int K, float kick0, float kick, float drift)
 {
-    __shared__ float4 lds[2 * kPassWaves * 2 * 64];
+    __shared__ float4 lds[kPassLds<kPassWaves>];
     const int b = (int)xcd_band(blockIdx.x, gridDim.x);       // a grid of a multiple of 8
     if (b >= pass_tiles<kPassWaves, R>(L, K)) return;
     pass_body<kPassWaves, R>(src, dst, psrc, pdst, L, K, K, kick0, kick, drift, b, lds);
@@ -507,7 +507,7 @@ __global__ void __launch_bounds__(kPassWaves * 64)
 k_qhmc_pass(const float* __restrict__ src, float* __restrict__ dst, const float* __restrict__ psrc,
             float* __restrict__ pdst, int L, int K, float4 kick0, float4 kick, float drift)
 {
-    __shared__ float4 lds[2 * kPassWaves * 2 * 64];
+    __shared__ float4 lds[kPassLds<kPassWaves>];
     const int b = (int)xcd_band(blockIdx.x, gridDim.x), r = (int)blockIdx.y;
     if (b >= pass_tiles<kPassWaves, R>(L, K)) return;
     const size_t o = (size_t)r * L * L;
@@ -585,7 +585,7 @@ __global__ void __launch_bounds__(kPassWaves * 64)
 k_bhmc_pass(const BhLat* __restrict__ d, const uint32_t* __restrict__ start, int n, int KH, int K, int parity,
             int first, float drift)
 {
-    __shared__ float4 lds[2 * kPassWaves * 2 * 64];
+    __shared__ float4 lds[kPassLds<kPassWaves>];
     const int i = bh_find(start, n, blockIdx.x);
     const BhLat& q = d[i];
     const unsigned lb = blockIdx.x - start[i];

@@ -41,7 +41,7 @@ __host__ __device__ constexpr int pass_tiles(int L, int K)
     return ((L / 2 + pass_ce(K) - 1) / pass_ce(K)) * ((L + pass_cy<W, R>(K) - 1) / pass_cy<W, R>(K));
 }
 template <int W>
-__host__ __device__ constexpr size_t pass_lds_bytes() { return (size_t)2 * W * 2 * 64 * sizeof(float4); }
+constexpr int kPassLds = 2 * W * 2 * 64;       // float4s: two rows a wave, two buffers
 
 // The value of the lane below (0x138) or above (0x130); lanes at the wave's end read 0.
 template <int CTRL>
@@ -122,7 +122,7 @@ __device__ __forceinline__ int pmod(int v, int n)
 }
 
 // K steps of tile b of one lattice, cut into the cores of passes of KH >= K steps;
-// kick0: the first step's.  lds: pass_lds_bytes<W>().
+// kick0: the first step's.  lds: kPassLds<W> entries.
 template <int W, int R>
 __device__ __forceinline__ void pass_body(const float* __restrict__ src, float* __restrict__ dst,
                                           const float* __restrict__ psrc, float* __restrict__ pdst, int L, int KH,

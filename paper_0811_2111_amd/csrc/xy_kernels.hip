@@ -287,19 +287,8 @@ hipError_t launch_measure(const void* st, int L, int precision, double* partials
 }
 
 // Fixed-order reduction of nparts partial records (8 doubles: six sums, accepts,
-// unused) -> one xy_obs.  Large counts take two levels: k_reduce_chunks sums
-// consecutive chunks of 256 records, k_finalize the chunk results (column_sums).  Both levels are
-// deterministic.
-
-__global__ void __launch_bounds__(256)
-k_reduce_chunks(const double* __restrict__ partials, int nparts, double* __restrict__ out)
-{
-    __shared__ double red[32];
-    const int i = (int)blockIdx.x * 256;
-    const double s = column_sums(partials + (size_t)i * 8, min(256, nparts - i), red);
-    if (threadIdx.x < 8) out[(size_t)blockIdx.x * 8 + threadIdx.x] = s;
-}
-
+// unused) -> one xy_obs, by column_sums: up to 2048 in one workgroup, more in two
+// levels (k_reduce_finalize).
 template <int NT>
 __global__ void __launch_bounds__(NT)
 k_finalize(const double* __restrict__ partials, int nparts, unsigned long long* __restrict__ counter,
@@ -311,19 +300,10 @@ k_finalize(const double* __restrict__ partials, int nparts, unsigned long long* 
     if (counter && threadIdx.x == 6) *counter = 0ull;
 }
 
-hipError_t launch_reduce_chunks(const double* partials, int nparts, double* out, hipStream_t s)
-{
-    const int nb = (nparts + 255) / 256;
-    hipLaunchKernelGGL(k_reduce_chunks, dim3(nb), dim3(256), 0, s, partials, nparts, out);
-    return hipGetLastError();
-}
-
-// Both levels in one launch: every workgroup sums its chunk of 256 records as
-// k_reduce_chunks does and writes the result to `chunks`; the workgroup that
-// arrives last (a counter in device memory, released and acquired at device
-// scope) sums the chunk results as k_finalize does, writes the record and sets
-// the counter back to zero.  The sums, and their order, are those of the two
-// separate kernels.
+// Two levels in one launch: every workgroup sums a chunk of 256 records and writes
+// the result to `chunks`; the workgroup that arrives last (a counter in device
+// memory, released and acquired at device scope) sums the chunk results in their
+// order, writes the record and sets the counter back to zero.
 // blockIdx.y: one of several records, whose partials, chunks, counters and results
 // lie one after another.
 __global__ void __launch_bounds__(256)
@@ -357,14 +337,10 @@ k_reduce_finalize(const double* __restrict__ partials, int nparts, double* __res
 hipError_t launch_finalize(const double* partials, int nparts, unsigned long long* counter, xy_obs* out,
                            uint64_t sweep_after, hipStream_t s, double* scratch, unsigned* arrive)
 {
-    if (nparts > 2048 && scratch && arrive) {
+    if (nparts > 2048) {
         const int nb = (nparts + 255) / 256;
         hipLaunchKernelGGL(k_reduce_finalize, dim3(nb), dim3(256), 0, s, partials, nparts, scratch, arrive, counter,
                            out, sweep_after);
-    } else if (nparts > 2048 && scratch) {
-        const int nb = (nparts + 255) / 256;
-        hipLaunchKernelGGL(k_reduce_chunks, dim3(nb), dim3(256), 0, s, partials, nparts, scratch);
-        hipLaunchKernelGGL(k_finalize<256>, dim3(1), dim3(256), 0, s, scratch, nb, counter, out, sweep_after);
     } else if (nparts > 256) {
         hipLaunchKernelGGL(k_finalize<1024>, dim3(1), dim3(1024), 0, s, partials, nparts, counter, out, sweep_after);
     } else {

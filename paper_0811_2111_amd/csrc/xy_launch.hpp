@@ -49,17 +49,12 @@ hipError_t launch_half_sweep(const SweepArgs& a, int colour, unsigned long long*
 hipError_t launch_measure(const void* st, int L, int precision, double* partials, int max_parts,
                           int* nparts, hipStream_t s);
 
-// Reduce partials in a fixed order, take the accept counter (and clear it) plus
-// the accepts in slot 6 of the partials, write one xy_obs record.
-// Sums of 256 consecutive records (slots 0..6) into out[chunk * 8 ..], fixed order.
-hipError_t launch_reduce_chunks(const double* partials, int nparts, double* out, hipStream_t s);
-
-// partials -> one record.  More than 2048 partials take two levels through
-// `scratch`: in one launch when `arrive` (a zeroed u32 in device memory, zero again
-// afterwards) is given, else in two.
+// Reduce partials in a fixed order, take the accept counter (and clear it) plus the
+// accepts in slot 6 of the partials, write one xy_obs record.  More than 2048
+// partials take two levels in one launch, through `chunks` (the sums of 256 partials
+// each) and `arrive` (a zeroed u32 in device memory, zero again afterwards).
 hipError_t launch_finalize(const double* partials, int nparts, unsigned long long* counter,
-                           xy_obs* out, uint64_t sweep_after, hipStream_t s, double* scratch,
-                           unsigned* arrive = nullptr);
+                           xy_obs* out, uint64_t sweep_after, hipStream_t s, double* chunks, unsigned* arrive);
 
 // Fused tiled sweep(s): `m` sweeps (1 or 2) per launch from a.src to a.dst.
 // meas_mask bit j set: measure after sub-sweep j into the 8-double record
