@@ -99,9 +99,11 @@ static int deep_depth(int L, DeepPlan* d)
 
 bool deep_choose(int L, int64_t n, bool meas, DeepPlan* d, int* nmax)
 {
-    // a single sweep gains nothing, nor, with four pairs a thread, do four (L = 1000:
-    // 24.3 us against 20.4 by tiles, five 27.0 and 31.1 with the copy back)
-    if (L < kDeepMinL || L > kDeepMaxL || L % 2 || n < (L > 832 ? 5 : 2)) return false;
+    // a single sweep gains nothing, nor do two from L = 384 on (8.5 us against 7.8 by
+    // tiles; L = 512 10.2 and 7.9, 768 14.5 and 9.4; L = 256 7.6 and 9.8) and four where
+    // a thread has four pairs (L = 1000: 24.3 against 20.4, five 27.0 and 31.1 with the
+    // copy back)
+    if (L < kDeepMinL || L > kDeepMaxL || L % 2 || n < (L > 832 ? 5 : L >= 384 ? 3 : 2)) return false;
     d->tx = d->ty = std::min(16, (L + 15) / 16);
     d->rp = d->full = 0;
     if (meas && L % 64 == 0) {

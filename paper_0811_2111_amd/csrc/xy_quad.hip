@@ -469,9 +469,14 @@ int xy_quad_sweep(xy_quad* q, int64_t n_sweeps, int32_t measure_every, xy_obs* o
     if (q->sweep + (uint64_t)n_sweeps >= 0xffffffffull) return XY_ERANGE;
     const bool meas = measure_every > 0 && obs_dev != nullptr && measure_every <= n_sweeps;
     // Where no tile was asked for: the whole quad in four workgroups, passes of
-    // several sweeps, or single sweeps of the lattices apart (a single sweep gains
-    // nothing from the latter two).
-    if (!q->tile_set && n_sweeps > 0) {
+    // several sweeps, or single sweeps of the lattices apart.  A single sweep gains
+    // nothing from the latter two, nor do two unmeasured ones from L = 384 on (13.3 us
+    // against 14.2; L = 608 21.5 and 24.7, 4096 330 and 343; L = 320 13.2 and 12.8) and
+    // four up to L = 1024 (58.0 and 61.4; L = 1536 109 and 92) where the first and last
+    // sweep's tiles are the ones of one kernel: they need no copy back.
+    const bool short_even = !meas && ((n_sweeps == 2 && q->L >= 384) ||
+                                      (n_sweeps == 4 && q->L % 128 == 0 && q->L >= 640 && q->L <= 1024));
+    if (!q->tile_set && n_sweeps > 0 && !short_even) {
         const int32_t me = meas ? measure_every : 0;
         xyk::DeepPlan plan;
         int nmax;

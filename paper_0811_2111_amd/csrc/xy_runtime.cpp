@@ -481,8 +481,17 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
     // Where the plan is the library's choice, single sweeps take the faster of the
     // ragged tiles in place of half-sweeps and, unmeasured, of a slower tile shape,
     // and large FP32 lattices strips of one wave.
+    // In place of a slower shape not where a single sweep's two buffers about fill the
+    // L2s (32 MiB), nor where one of two sweeps is measured by that shape: the other
+    // buffer's lines then lie in other XCDs' L2s (us a call by the plan's tiles and the
+    // ragged ones: L = 1920, one sweep 20.8 and 23.3, ten 124 and 101; L = 1600, two
+    // sweeps and a record 26.7 and 29.8, one sweep 18.9 and 17.9).
     const bool own = h->own_plan;
-    const int own_tx = own ? xyk::ragged_tile_x(h->L) : 0;
+    const size_t two = 2 * xyk::state_bytes(h->L, h->precision);
+    const bool plans_tile = h->plan.kind == XY_PLAN_FUSED &&
+                            ((n_sweeps == 1 && two >= (22u << 20) && two <= (40u << 20)) ||
+                             (n_sweeps == 2 && meas && two >= (16u << 20) && two <= (32u << 20)));
+    const int own_tx = own && !plans_tile ? xyk::ragged_tile_x(h->L) : 0;
     auto walk = [&](bool meas_j) { return own && xyk::walk_supported(h->L, h->precision, meas_j); };
     const bool stream = h->plan.kind == XY_PLAN_STREAM;
 

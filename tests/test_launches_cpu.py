@@ -232,3 +232,23 @@ def test_autotuned_batch_runs_the_same_on_another_handle(stub, Ls, cheap):
     assert stub.lib.xy_batch_set_schedule(other, sched) == OK
     names = lambda log: {k for k in log if "k_batch" in k}  # noqa: E731
     assert names(run(tuned)) == names(run(other))
+
+
+@pytest.mark.parametrize("L,prec,n,me,kernel", [
+    (256, 0, 2, 0, "k_deep"), (382, 0, 2, 1, "k_deep"), (384, 0, 2, 1, "k_fused"), (450, 0, 2, 0, "k_ragged"),
+    (768, 1, 2, 0, "k_fusedI6__halfLi128ELi16E"), (768, 0, 3, 0, "k_deep"), (1920, 0, 1, 0, "k_fusedIfLi128ELi32E"),
+    (1920, 0, 10, 0, "k_raggedIfLi256E"), (1600, 0, 2, 2, "k_fusedIfLi64ELi32E"), (1600, 0, 1, 0, "k_raggedIfLi256E"),
+    (2496, 1, 1, 0, "k_fusedI6__halfLi64ELi32E"), (1860, 0, 2, 0, "k_ragged")])
+def test_first_kernel_of_short_calls(stub, L, prec, n, me, kernel):
+    h = stub.lattice(L, prec)
+    assert kernel in stub.log(lambda: stub.lib.xy_sweep(h, i64(n), i32(me), DEV if me else None))[0]
+
+
+@pytest.mark.parametrize("L,n,me,kernel", [
+    (320, 2, 0, "k_deep_quad"), (384, 2, 0, "k_quad_fusedILi128ELi8ELb0ELb0ELb0E"), (384, 2, 1, "k_deep_quad"),
+    (608, 2, 0, "k_quad_fusedILi32ELi16ELb0ELb0ELb0E"), (608, 2, 1, "k_quad_split"),
+    (608, 4, 0, "k_quad_fusedILi32ELi16ELb0ELb0ELb1E"), (1024, 4, 0, "k_quad_fusedILi128ELi8ELb0ELb0ELb0E"),
+    (1024, 5, 0, "k_quad_fusedILi128ELi8ELb0ELb0ELb1E"), (1152, 4, 0, "k_quad_fusedILi128ELi8ELb0ELb0ELb1E")])
+def test_first_kernel_of_short_quad_calls(stub, L, n, me, kernel):
+    q = stub.quad(L)
+    assert kernel in stub.log(lambda: stub.lib.xy_quad_sweep(q, i64(n), i32(me), DEV if me else None))[0]
