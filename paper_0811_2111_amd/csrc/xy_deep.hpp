@@ -115,6 +115,13 @@ __device__ __forceinline__ PairNb<O> deep_nb(const float2* __restrict__ plane, i
     return n;
 }
 
+// Pairs whose (cos, sin) a thread keeps in registers beside their angles.  Of eight it
+// reads them from LDS, too: 64 registers of state in a workgroup of 1024 threads, which
+// has 128, spilled 700 bytes a thread with the neighbours' addresses that the compiler
+// kept over the sweeps (L = 128, one sweep 32.0 us, ten 146; without spills 16.1 and 93;
+// L = 80, four pairs, ten sweeps 47.0 and 41.2).
+constexpr int deep_kept(int R) { return R <= 4 ? R : 1; }
+
 template <int R>
 struct DeepItems {
     int at[R];            // first entry within a plane
@@ -194,39 +201,48 @@ __device__ __forceinline__ void deep_put(float2* __restrict__ plane, int WS, int
 // One half-sweep of this thread's pairs; O = parity (colour + y) & 1 of its rows.
 template <typename T, int R, int O, bool ODD, bool WRAP, int MEAS, bool EARLY>
 __device__ __forceinline__ void deep_half(float2* __restrict__ own, const float2* __restrict__ oth, int WS, int L,
-                                          int Hh, const DeepItems<R>& it, float2 (&th)[R], float4 (&cs)[R],
+                                          int Hh, const DeepItems<R>& it, float2 (&th)[R], float4 (&kept)[deep_kept(R)],
                                           DeepPrep<R> (&r)[R], const DeepDraw& w, const Params& p, int& acc, MeasAcc& m, double (&v)[7])
 {
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-        if (!(it.flag[q] & kOn)) continue;
+        unsigned flag = it.flag[q];
+        int at = it.at[q];
+        // opaque, so that no addresses derived from them are kept over the sweeps (regions
+        // with a halo have the registers, and take 5% longer so)
+        if constexpr (WRAP && R >= 4) asm volatile("" : "+v"(flag), "+v"(at));
+        if (!(flag & kOn)) continue;
         if constexpr (!EARLY) r[q] = philox10(w.sweep, w.colour, 0u, it.idx[q], w.k0, w.k1);
-        const PairNb<O> n = deep_nb<O, ODD>(oth, WS, it.at[q]);
+        const PairNb<O> n = deep_nb<O, ODD>(oth, WS, at);
+        float4 cs;
+        if constexpr (R <= 4) cs = kept[q];
+        else cs = *(const float4*)&own[at];
         DeepProp pr;
         if constexpr (R == 1) pr = r[q];
         else pr = deep_propose<T>(r[q], th[q], p);
-        const int aa = decide(pr.a, th[q].x, cs[q].x, cs[q].y, nsum(n.la.x, n.ra.x, n.ua.x, n.da.x),
+        const int aa = decide(pr.a, th[q].x, cs.x, cs.y, nsum(n.la.x, n.ra.x, n.ua.x, n.da.x),
                               nsum(n.la.y, n.ra.y, n.ua.y, n.da.y), p);
-        const int ab = decide(pr.b, th[q].y, cs[q].z, cs[q].w, nsum(n.lb.x, n.rb.x, n.ub.x, n.db.x),
+        const int ab = decide(pr.b, th[q].y, cs.z, cs.w, nsum(n.lb.x, n.rb.x, n.ub.x, n.db.x),
                               nsum(n.lb.y, n.rb.y, n.ub.y, n.db.y), p);
-        deep_put<ODD, WRAP>(own, WS, L, Hh, it.at[q], it.flag[q], cs[q]);
-        if (it.flag[q] & kCore) {
-            const bool b = !ODD || (it.flag[q] & kHasB);
+        deep_put<ODD, WRAP>(own, WS, L, Hh, at, flag, cs);
+        if constexpr (R <= 4) kept[q] = cs;
+        if (flag & kCore) {
+            const bool b = !ODD || (flag & kHasB);
             acc += aa + (b ? ab : 0);
             if constexpr (MEAS == kMeasOwn) {
-                meas_acc(m, cs[q].x, cs[q].y, n.la, n.ra, n.ua, n.da);
-                if (b) meas_acc(m, cs[q].z, cs[q].w, n.lb, n.rb, n.ub, n.db);
+                meas_acc(m, cs.x, cs.y, n.la, n.ra, n.ua, n.da);
+                if (b) meas_acc(m, cs.z, cs.w, n.lb, n.rb, n.ub, n.db);
             } else if constexpr (MEAS == kMeasQuad) {
                 MeasAcc t;
-                meas_acc(t, cs[q].x, cs[q].y, n.la, n.ra, n.ua, n.da);
-                meas_acc(t, cs[q].z, cs[q].w, n.lb, n.rb, n.ub, n.db);
+                meas_acc(t, cs.x, cs.y, n.la, n.ra, n.ua, n.da);
+                meas_acc(t, cs.z, cs.w, n.lb, n.rb, n.ub, n.db);
                 v[0] += (double)t.cx; v[1] += (double)t.cy; v[2] += (double)t.ix;
                 v[3] += (double)t.iy; v[4] += (double)t.mx; v[5] += (double)t.my;
             } else if constexpr (MEAS == kMeasPair) {
                 Meas t{0, 0, 0, 0, 0, 0};
-                meas_black(t, cs[q].x, cs[q].y, n.la.x, n.la.y, n.ra.x, n.ra.y, n.ua.x, n.ua.y, n.da.x, n.da.y);
+                meas_black(t, cs.x, cs.y, n.la.x, n.la.y, n.ra.x, n.ra.y, n.ua.x, n.ua.y, n.da.x, n.da.y);
                 if (b)
-                    meas_black(t, cs[q].z, cs[q].w, n.lb.x, n.lb.y, n.rb.x, n.rb.y, n.ub.x, n.ub.y, n.db.x, n.db.y);
+                    meas_black(t, cs.z, cs.w, n.lb.x, n.lb.y, n.rb.x, n.rb.y, n.ub.x, n.ub.y, n.db.x, n.db.y);
                 v[0] += (double)t.cx; v[1] += (double)t.cy; v[2] += (double)t.ix;
                 v[3] += (double)t.iy; v[4] += (double)t.mx; v[5] += (double)t.my;
             }
@@ -273,6 +289,7 @@ __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __res
                                              uint32_t k1, const Params& p, char* smem, Put put)
 {
     static_assert(NT == 256 || NT % 512 == 0, "waves of both colours and parities");
+    static_assert(R <= 4 || !ODD, "own pairs are read from LDS as one");
     constexpr bool EARLY = R <= 2 || (R == 4 && MEAS == kMeasNone);
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // waves are dealt out to the four SIMDs in turn: four red, then four black ones
@@ -288,7 +305,7 @@ __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __res
     const unsigned half = col ? (unsigned)(g.L * g.Hh) : 0u;
     DeepItems<R> it;
     float2 th[R];
-    float4 cs[R];
+    float4 kept[deep_kept(R)];
     DeepPrep<R> r[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) {
@@ -322,9 +339,11 @@ __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __res
     DeepDraw dr{sweep0, (uint32_t)col, k0, k1};
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-        sincos_turn(th[q].x, cs[q].y, cs[q].x);
-        sincos_turn(th[q].y, cs[q].w, cs[q].z);
-        if (it.flag[q] & kOn) deep_put<ODD, WRAP>(own, WS, g.L, g.Hh, it.at[q], it.flag[q], cs[q]);
+        float4 cs;
+        sincos_turn(th[q].x, cs.y, cs.x);
+        sincos_turn(th[q].y, cs.w, cs.z);
+        if constexpr (R <= 4) kept[q] = cs;
+        if (it.flag[q] & kOn) deep_put<ODD, WRAP>(own, WS, g.L, g.Hh, it.at[q], it.flag[q], cs);
     }
     if (col == 0) deep_draw<T, R, EARLY>(r, it, th, dr, p);
     const bool o1 = ((g.ys + par + col) & 1) != 0;     // parity (colour + y) & 1 of this wave's sites (L is even)
@@ -336,8 +355,8 @@ __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __res
         MeasAcc m;
         double v[7] = {0, 0, 0, 0, 0, 0, 0};
         if (col == 0) {
-            if (o1) deep_half<T, R, 1, ODD, WRAP, kMeasNone, EARLY>(own, oth, WS, g.L, g.Hh, it, th, cs, r, dr, p, acc, m, v);
-            else deep_half<T, R, 0, ODD, WRAP, kMeasNone, EARLY>(own, oth, WS, g.L, g.Hh, it, th, cs, r, dr, p, acc, m, v);
+            if (o1) deep_half<T, R, 1, ODD, WRAP, kMeasNone, EARLY>(own, oth, WS, g.L, g.Hh, it, th, kept, r, dr, p, acc, m, v);
+            else deep_half<T, R, 0, ODD, WRAP, kMeasNone, EARLY>(own, oth, WS, g.L, g.Hh, it, th, kept, r, dr, p, acc, m, v);
             dr.sweep += 1u;
         } else {
             deep_draw<T, R, EARLY>(r, it, th, dr, p);
@@ -348,11 +367,11 @@ __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __res
             if (j < n) deep_draw<T, R, EARLY>(r, it, th, dr, p);
         } else {
             if (meas) {
-                if (o1) deep_half<T, R, 1, ODD, WRAP, MEAS, EARLY>(own, oth, WS, g.L, g.Hh, it, th, cs, r, dr, p, acc, m, v);
-                else deep_half<T, R, 0, ODD, WRAP, MEAS, EARLY>(own, oth, WS, g.L, g.Hh, it, th, cs, r, dr, p, acc, m, v);
+                if (o1) deep_half<T, R, 1, ODD, WRAP, MEAS, EARLY>(own, oth, WS, g.L, g.Hh, it, th, kept, r, dr, p, acc, m, v);
+                else deep_half<T, R, 0, ODD, WRAP, MEAS, EARLY>(own, oth, WS, g.L, g.Hh, it, th, kept, r, dr, p, acc, m, v);
             } else {
-                if (o1) deep_half<T, R, 1, ODD, WRAP, kMeasNone, EARLY>(own, oth, WS, g.L, g.Hh, it, th, cs, r, dr, p, acc, m, v);
-                else deep_half<T, R, 0, ODD, WRAP, kMeasNone, EARLY>(own, oth, WS, g.L, g.Hh, it, th, cs, r, dr, p, acc, m, v);
+                if (o1) deep_half<T, R, 1, ODD, WRAP, kMeasNone, EARLY>(own, oth, WS, g.L, g.Hh, it, th, kept, r, dr, p, acc, m, v);
+                else deep_half<T, R, 0, ODD, WRAP, kMeasNone, EARLY>(own, oth, WS, g.L, g.Hh, it, th, kept, r, dr, p, acc, m, v);
             }
             dr.sweep += 1u;
         }
