@@ -150,16 +150,18 @@ k_hmc_step(const float* __restrict__ src, float* __restrict__ dst, float* __rest
 // neighbours in the other plane are that plane's pair 2j, 2j+1 of the same row
 // and one more entry (2j-1 if o = 0, 2j+2 if o = 1); its vertical neighbours are
 // the other plane's pairs of the rows above and below, so the R rows share R + 2
-// rows of the other plane.  1-D grid of 2 ceil(J/256) (L/R) workgroups, J = L/4,
-// remapped by xcd_band.
+// rows of the other plane.  step2_blocks(L) workgroups, t after the XCD remap.
+constexpr int kStepRows = 4;
+__host__ __device__ constexpr unsigned step2_blocks(int L)
+{
+    return 2u * (((unsigned)(L / 4) + kThreads - 1) / kThreads) * (unsigned)(L / kStepRows);
+}
 template <int R>
-__global__ void __launch_bounds__(kThreads)
-k_hmc_step2(const float* __restrict__ src, float* __restrict__ dst, float* __restrict__ p, int L, float nbeta_kick,
-            float drift)
+__device__ __forceinline__ void step2_body(const float* __restrict__ src, float* __restrict__ dst,
+                                           float* __restrict__ p, int L, float nbeta_kick, float drift, unsigned t)
 {
     const int Hh = L >> 1, J = Hh >> 1;
     const int cols = 2 * ((J + kThreads - 1) / kThreads);
-    const unsigned t = xcd_band(blockIdx.x, gridDim.x);
     const int y0 = (int)(t / (unsigned)cols) * R, col = (int)(t % (unsigned)cols);
     const int c = col & 1;
     const int j = (col >> 1) * kThreads + threadIdx.x;
@@ -211,7 +213,12 @@ k_hmc_step2(const float* __restrict__ src, float* __restrict__ dst, float* __res
     }
 }
 
-constexpr int kStepRows = 4;               // rows per thread of k_hmc_step2
+__global__ void __launch_bounds__(kThreads)
+k_hmc_step2(const float* __restrict__ src, float* __restrict__ dst, float* __restrict__ p, int L, float nbeta_kick,
+            float drift)
+{
+    step2_body<kStepRows>(src, dst, p, L, nbeta_kick, drift, xcd_band(blockIdx.x, gridDim.x));
+}
 
 // Several leap-frog steps per pass (xy_hmc_pass.hpp) for any even L: 512 threads,
 // eight rows a thread (64 x 128 sites a region; 104 VGPRs, two workgroups a CU), or
@@ -502,6 +509,16 @@ k_qhmc_ends(float* st, float* __restrict__ p, float* copy, int L, uint32_t traj,
                       rec + (size_t)r * nrec * 8, xcd_band(blockIdx.x, gridDim.x));
 }
 
+__global__ void __launch_bounds__(kThreads)
+k_qhmc_step(const float* __restrict__ src, float* __restrict__ dst, float* __restrict__ p, int L, float4 kick,
+            float drift)
+{
+    const int r = (int)blockIdx.y;
+    const size_t o = (size_t)r * L * L;
+    step2_body<kStepRows>(src + o, dst + o, p + o, L, r == 0 ? kick.x : r == 1 ? kick.y : r == 2 ? kick.z : kick.w,
+                          drift, xcd_band(blockIdx.x, gridDim.x));
+}
+
 template <int R>
 __global__ void __launch_bounds__(kPassWaves * 64)
 k_qhmc_pass(const float* __restrict__ src, float* __restrict__ dst, const float* __restrict__ psrc,
@@ -557,13 +574,13 @@ __device__ __forceinline__ int bh_find(const uint32_t* __restrict__ start, int n
 }
 
 // Trajectory ends: BEGIN draws the momenta, saves the angles and writes the H_old
-// records; else the final half kick from the angles and momenta the leap-frog
-// passes left in the second buffers (parity odd, angles also copied back into the
-// state) or the first, and the H_new records.
+// records; else the final half kick from the angles that the leap-frog passes left in
+// the second buffer (parity odd, also copied back into the state) or the first, and
+// the momenta (pparity) likewise, and the H_new records.
 template <bool BEGIN>
 __global__ void __launch_bounds__(kThreads)
 k_bhmc_ends(const BhLat* __restrict__ d, const uint32_t* __restrict__ start, int n,
-            const uint32_t* __restrict__ traj_dev, int parity)
+            const uint32_t* __restrict__ traj_dev, int parity, int pparity)
 {
     const int i = bh_find(start, n, blockIdx.x);
     const BhLat& q = d[i];
@@ -574,8 +591,21 @@ k_bhmc_ends(const BhLat* __restrict__ d, const uint32_t* __restrict__ start, int
     if constexpr (BEGIN)
         ends2_body<true>(q.st, q.w.p, q.w.saved, q.L, *traj_dev, q.k0, q.k1, 0.0f, q.cols, q.rb, q.w.rec_old, t);
     else
-        ends2_body<false>(parity ? q.pp : q.st, parity ? q.w.p2 : q.w.p, parity ? q.st : nullptr, q.L, 0u, q.k0,
+        ends2_body<false>(parity ? q.pp : q.st, pparity ? q.w.p2 : q.w.p, parity ? q.st : nullptr, q.L, 0u, q.k0,
                           q.k1, q.kick_half, q.cols, q.rb, q.w.rec_new, t);
+}
+
+// One leap-frog step of every lattice (L % 4 == 0), the momenta in place; parity odd:
+// from the second angle buffer to the first.
+__global__ void __launch_bounds__(kThreads)
+k_bhmc_step(const BhLat* __restrict__ d, const uint32_t* __restrict__ start, int n, int parity, int first, float drift)
+{
+    const int i = bh_find(start, n, blockIdx.x);
+    const BhLat& q = d[i];
+    const unsigned t = xcd_band(blockIdx.x - start[i], start[i + 1] - start[i]);
+    if (t >= step2_blocks(q.L)) return;
+    step2_body<kStepRows>(parity ? q.pp : q.st, parity ? q.st : q.pp, q.w.p, q.L, first ? q.kick_half : q.kick_full,
+                          drift, t);
 }
 
 // K leap-frog steps of every lattice, on regions cut for passes of KH; parity odd:
@@ -788,11 +818,10 @@ hipError_t launch_hmc_trajectory(float* state, float* pingpong, const HmcWork& w
         }
     } else {
         const bool pairs = (L % (4 * kStepRows)) == 0;
-        const unsigned nstep2 = (unsigned)(2 * ((L / 4 + kThreads - 1) / kThreads)) * (unsigned)(L / kStepRows);
         for (int q = 0; q < n_md; ++q) {
             const float kick = q == 0 ? kick_half : kick_full;
             if (pairs)
-                hipLaunchKernelGGL(k_hmc_step2<kStepRows>, dim3(nstep2), block, 0, s, src, dst, p, L, kick, drift);
+                hipLaunchKernelGGL(k_hmc_step2, dim3(step2_blocks(L)), block, 0, s, src, dst, p, L, kick, drift);
             else
                 hipLaunchKernelGGL(k_hmc_step, gstep, block, 0, s, src, dst, p, L, kick, drift);
             float* t = src;
@@ -836,6 +865,9 @@ int hmc_batch_steps(int n_md, int steps_per_pass) { return pass_steps(n_md, step
 
 int hmc_batch_rows(int n, const int32_t* L, int kh)
 {
+    // one step a pass: a region's halo, and momenta that move to another buffer, are not
+    // worth it (four lattices of L = 2048, 20 steps: 2589 us a trajectory in regions, 1816)
+    if (kh == 1) return 0;
     long long tiles = 0;
     for (int i = 0; i < n; ++i) tiles += pass_tiles<kPassWaves, 4>(L[i], kh);
     return tiles > kPassFewRegions ? 8 : 4;
@@ -844,7 +876,7 @@ int hmc_batch_rows(int n, const int32_t* L, int kh)
 void hmc_batch_blocks(int L, int rows, int kh, uint32_t nb[3])
 {
     nb[0] = pad8((uint32_t)(hmc_cols2(L) * hmc_row_blocks2(L)));
-    nb[1] = pad8((uint32_t)(rows == 8 ? pass_tiles<kPassWaves, 8>(L, kh) : pass_tiles<kPassWaves, 4>(L, kh)));
+    nb[1] = pad8((uint32_t)(rows == 0 ? step2_blocks(L) : rows == 8 ? pass_tiles<kPassWaves, 8>(L, kh) : pass_tiles<kPassWaves, 4>(L, kh)));
     const size_t n = (size_t)L * (size_t)L;
     const size_t r = (n + kThreads * 8 - 1) / (kThreads * 8);
     nb[2] = pad8((uint32_t)(r < 4096 ? r : 4096));
@@ -859,20 +891,23 @@ hipError_t launch_hmc_batch_trajectory(const BhLat* d, const uint32_t* start, in
     const uint32_t* s_rest = start + 2 * (n + 1);
     const float drift = (float)(eps / (2.0 * 3.14159265358979323846));
     const dim3 block(kThreads);
-    hipLaunchKernelGGL(k_bhmc_ends<true>, dim3(totals[0]), block, 0, s, d, s_ends, n, traj_dev, 0);
+    hipLaunchKernelGGL(k_bhmc_ends<true>, dim3(totals[0]), block, 0, s, d, s_ends, n, traj_dev, 0, 0);
     const int kh = hmc_batch_steps(n_md, steps_per_pass);
     const dim3 bpass(kPassWaves * 64);
     int parity = 0;
     for (int q = 0; q < n_md;) {
         const int k = n_md - q < kh ? n_md - q : kh;
-        if (rows == 8)
+        if (rows == 0)
+            hipLaunchKernelGGL(k_bhmc_step, dim3(totals[1]), block, 0, s, d, s_pass, n, parity, q == 0, drift);
+        else if (rows == 8)
             hipLaunchKernelGGL(k_bhmc_pass<8>, dim3(totals[1]), bpass, 0, s, d, s_pass, n, kh, k, parity, q == 0, drift);
         else
             hipLaunchKernelGGL(k_bhmc_pass<4>, dim3(totals[1]), bpass, 0, s, d, s_pass, n, kh, k, parity, q == 0, drift);
         parity ^= 1;
         q += k;
     }
-    hipLaunchKernelGGL(k_bhmc_ends<false>, dim3(totals[0]), block, 0, s, d, s_ends, n, traj_dev, parity);
+    hipLaunchKernelGGL(k_bhmc_ends<false>, dim3(totals[0]), block, 0, s, d, s_ends, n, traj_dev, parity,
+                       rows == 0 ? 0 : parity);
     hipLaunchKernelGGL(k_bhmc_decide, dim3((unsigned)n), block, 0, s, d, traj_dev);
     hipLaunchKernelGGL(k_bhmc_restore, dim3(totals[2]), block, 0, s, d, s_rest, n);
     return hipGetLastError();
@@ -958,10 +993,16 @@ hipError_t launch_quad_hmc_trajectory(float* planes, float* second, const QuadHm
     const int kmax = pass_steps(n_md, steps_per_pass);
     for (int q = 0; q < n_md;) {
         const int k = std::min(n_md - q, kmax);
+        const float4 k0 = q == 0 ? kick_half : kick_full;
+        if (kmax == 1) {
+            hipLaunchKernelGGL(k_qhmc_step, dim3(step2_blocks(L), 4), block, 0, s, src, dst, p, L, k0, drift);
+            std::swap(src, dst);
+            ++q;
+            continue;
+        }
         const bool tall = 4 * pass_tiles<kPassWaves, 4>(L, k) > kPassFewRegions;
         const int nt = tall ? pass_tiles<kPassWaves, 8>(L, k) : pass_tiles<kPassWaves, 4>(L, k);
         const dim3 grid((unsigned)((nt + 7) & ~7), 4);
-        const float4 k0 = q == 0 ? kick_half : kick_full;
         if (tall)
             hipLaunchKernelGGL(k_qhmc_pass<8>, grid, bpass, 0, s, src, dst, p, pn, L, k, k0, kick_full, drift);
         else

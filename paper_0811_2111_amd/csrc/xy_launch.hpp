@@ -168,7 +168,8 @@ struct BhLat {
 };
 // Fill the geometry fields of d (cols, rb, nrec, kicks) for lattice L at beta, eps.
 void hmc_batch_describe(BhLat& d, int L, double beta, double eps);
-// Leap-frog steps of the longest pass, and the rows a thread takes in the passes.
+// Leap-frog steps of the longest pass, and the rows a thread takes in the passes (0:
+// one step a launch, not in regions).
 int hmc_batch_steps(int n_md, int steps_per_pass);
 int hmc_batch_rows(int n, const int32_t* L, int kh);
 // Workgroups lattice L takes in each stage grid: [0] ends, [1] leap-frog pass of kh

@@ -161,7 +161,7 @@ def test_failed_last_launches_are_made_up_for(stub):
 def test_quad_hmc_steps_per_pass_are_those_set(stub):
     """Nine steps: in passes of at most the setting, of up to seven if none was made."""
     q = stub.quad(64)
-    passes = lambda: sum("k_qhmc_pass" in k for k in stub.log(  # noqa: E731
+    passes = lambda: sum("k_qhmc_pass" in k or "k_qhmc_step" in k for k in stub.log(  # noqa: E731
         lambda: stub.lib.xy_quad_hmc(q, i64(1), 9, dbl(0.1), DEV, sz(1 << 40), None)))
     assert passes() == 2
     for steps, want in ((1, 9), (2, 5), (3, 3), (4, 3)):
