@@ -65,7 +65,7 @@ ALG_BYTES_STREAM = 12.0                  # two half-sweep passes: read both colo
 ALG_BYTES_HMC_STEP = 16.0                # one leap-frog step: read and write the angle and the momentum
 PLAN_NAMES = {1: "stream", 2: "fused", 3: "strip", 4: "resident"}
 BATCH_SCHEDULES = {0: "persistent", 1: "per-sweep launches", 2: "per-sweep launches, 256x16 tiles where L allows"}
-KERNEL_NAMES = {1: "k_half_sweep", 2: "k_fused (LDS-tiled fused red+black sweep)",
+KERNEL_NAMES = {0: "k_walk (strips of one wave, in registers)", 1: "k_half_sweep", 2: "k_fused (LDS-tiled fused red+black sweep)",
                 3: "k_strip (strip segment, rows streamed through LDS rings)"}
 # Counter profiles (FETCH_SIZE / WRITE_SIZE per launch) of the tiled sweep kernels,
 # valid while the kernel's sources hash as they did when the counters were taken.
@@ -327,8 +327,9 @@ def main():
 
 def l4096_leg(stream, steps=1000, warmup=100):
     """The MALL-resident L = 4096 lattice (beta = 1.12, delta = 1.0, a record every
-    10 sweeps): Gupd/s, and the dominant (unmeasured fused) launch against the ALU
-    and HBM peaks."""
+    10 sweeps): Gupd/s, and the dominant (unmeasured) launch against the ALU and HBM
+    peaks.  Where the autotuner picks the library's own schedule (XY_PLAN_AUTO) that
+    launch is a strip kernel of its own, else the chosen plan's."""
     import torch
 
     from paper_0811_2111_amd import workloads, xy
@@ -352,6 +353,7 @@ def l4096_leg(stream, steps=1000, warmup=100):
     ms = e0.elapsed_time(e1)
     gupd = float(N) * me * steps / (ms * 1e-3) / 1e9
     res = {"gupd_s": round(gupd, 2), "sweeps": me * steps, "ms": round(ms, 2), "plan": list(plan),
+           "tuned": list(tuned),
            "thermalisation_sweeps": me * warmup}
     tiled = plan[0] in (xy.XY_PLAN_FUSED, xy.XY_PLAN_STRIP)
     if tiled:
@@ -366,13 +368,14 @@ def l4096_leg(stream, steps=1000, warmup=100):
         upd = N * plan[3]
         slots = ALG_SLOTS_PER_UPDATE * upd / (per_launch_ms * 1e-3) / 1e12
         gbs = ALG_BYTES_FUSED * N / (per_launch_ms * 1e-3) / 1e9
-        res["roofline_alu"] = {"kernel": KERNEL_NAMES[plan[0]] + ", unmeasured sweep", "bound": "alu",
+        own = tuned[0] == xy.XY_PLAN_AUTO
+        res["roofline_alu"] = {"kernel": KERNEL_NAMES[tuned[0]] + ", unmeasured sweep", "bound": "alu",
                                "achieved": round(slots, 2), "peak": round(VALU_PEAK_TSLOTS, 2),
                                "unit": "T VALU-slot/s", "frac": round(slots / VALU_PEAK_TSLOTS, 4),
                                "alg_slots_per_update": ALG_SLOTS_PER_UPDATE,
                                "avg_launch_ms": round(per_launch_ms, 5), "launches_timed": k_n,
                                "kernel_gupd_s": round(upd / (per_launch_ms * 1e-3) / 1e9, 2),
-                               "traffic": measured_traffic(L, plan),
+                               "traffic": None if own else measured_traffic(L, plan),
                                "hbm": {"achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                        "frac": round(gbs / HBM_PEAK_GBS, 4),
                                        "alg_bytes_per_update": ALG_BYTES_FUSED}}
@@ -496,7 +499,7 @@ def extra_legs(stream, args=None):
     ex = {}
     # the MALL-resident single lattice (ALU-bound) with its roofline
     ex["L4096_mall_resident"] = l4096_leg(stream)
-    main_plan = tuple(ex["L4096_mall_resident"]["plan"])
+    main_plan = tuple(ex["L4096_mall_resident"]["tuned"])
 
     # batched temperature scan vs per-lattice launches
     sc = workloads.temperature_scan()
@@ -674,20 +677,21 @@ def quad_hmc_leg(stream, singles=True):
     out = torch.empty((hc["traj"], 4, 9), dtype=torch.float64, device="cuda")
     ms_q = timed(lambda: qd.hmc(hc["traj"], hc["n_md"], hc["eps"], out=out), stream)
     r = xy.hmc_records(out)
-    k = qd.hmc_steps_per_pass
+    k = 7                                        # the library's passes where no setting was made
     del qd
     torch.cuda.empty_cache()
     steps = 4.0 * float(hc["L"]) ** 2 * hc["n_md"] * hc["traj"]
     # algorithmic bytes per replica site of a trajectory: the begin (read 4, write
     # 8), ceil(n_md / k) passes of angle + momentum read and written (16 B), the
-    # end (read 8, plus the angles written back, 4, when the pass count is odd)
+    # end (read 8, plus the angles written back, 4, when the pass count is odd), and
+    # its share of the call's split into four lattices and joining (8 B each)
     passes = -(-hc["n_md"] // k)
-    traj_bytes = 12.0 + ALG_BYTES_HMC_STEP * passes + 8.0 + (4.0 if passes % 2 else 0.0)
+    traj_bytes = 12.0 + ALG_BYTES_HMC_STEP * passes + 8.0 + (4.0 if passes % 2 else 0.0) + 16.0 / hc["traj"]
     gbs = 4.0 * float(hc["L"]) ** 2 * traj_bytes * hc["traj"] / (ms_q * 1e-3) / 1e9
     res = {"g_replica_site_steps_s": round(steps / (ms_q * 1e-3) / 1e9, 2), "trajectories": hc["traj"],
            "n_md": hc["n_md"], "eps": hc["eps"], "betas": hc["betas"], "ms": round(ms_q, 2),
            "accept_rate": round(float(r["accepted"].mean()), 3), "steps_per_pass": k,
-           "alg_bytes_per_replica_site_traj": traj_bytes,
+           "alg_bytes_per_replica_site_traj": round(traj_bytes, 3),
            "hbm_GBps": round(gbs, 1), "frac_hbm": round(gbs / HBM_PEAK_GBS, 4)}
     if singles:
         lats = [xy.Lattice(hc["L"], seed=s_, beta=b_) for s_, b_ in zip(hc["seeds"], hc["betas"])]
