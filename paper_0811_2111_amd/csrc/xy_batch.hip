@@ -515,7 +515,7 @@ k_batch_resident(const T* __restrict__ state, T* __restrict__ out, const LatDesc
     const int i = ridx[blockIdx.x];
     const LatDesc d = lat[i];
     const Params prm{d.delta, d.nbl2e};
-    resident_program<T, kResNT, 1, false, kMeasOwn>(state + d.off, out + d.off, d.L, ctrl->sweep0, npass, me, 0, d.key0, d.key1, prm,
+    resident_program<T, kResNT, 1, false, kMeasOwn>(state + d.off, out + d.off, d.L, ctrl->sweep0, npass, me, d.key0, d.key1, prm,
                              (me > 0 && obs) ? obs + (size_t)i * nrec : nullptr, smem);
 }
 

@@ -198,21 +198,20 @@ k_deep_quad(const float* __restrict__ src, float* __restrict__ dst, int L, int t
 // in place; the partial record is the record.
 template <int NT, int MEAS>
 __global__ void __launch_bounds__(NT)
-k_resident_quad(float* __restrict__ st, int L, uint32_t sweep0, int n, int me, int phase, Params4 p,
-                xy_obs* __restrict__ obs)
+k_resident_quad(float* __restrict__ st, int L, uint32_t sweep0, int n, int me, Params4 p, xy_obs* __restrict__ obs)
 {
     extern __shared__ __align__(16) char smem[];
     const int r = (int)blockIdx.x;
     const Params pr{p.delta[r], p.nbl2e[r]};
     const DeepRegion g{L, L >> 1, L >> 2, 0, 0, L >> 2, L, 0, 0, L >> 2, L};
     deep_program<float, NT, 1, false, true, MEAS, true>(
-        st + r, st + r, g, sweep0, n, me, phase, 0, 0, p.k0[r], p.k1[r], pr, smem, [&](int k, double s) {
+        st + r, st + r, g, sweep0, n, me, 0, 0, 0, p.k0[r], p.k1[r], pr, smem, [&](int k, double s) {
             // xy_obs: sweep, n_accept, then the six sums, eight bytes each
             const int t = (int)threadIdx.x;
             unsigned long long* o = (unsigned long long*)(obs + (size_t)k * 4 + r);
             if (t < 6) o[2 + t] = (unsigned long long)__double_as_longlong(s);
             else if (t == 6) o[1] = (unsigned long long)s;
-            else o[0] = (uint64_t)sweep0 + (uint64_t)(k + 1) * (uint64_t)me - (uint64_t)phase;
+            else o[0] = (uint64_t)sweep0 + (uint64_t)(k + 1) * (uint64_t)me;
         });
 }
 
@@ -265,17 +264,17 @@ hipError_t launch_deep_quad(const float4* src, float4* dst, int L, uint32_t swee
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_resident_quad(float4* state, int L, uint32_t sweep, const Params4& p, int n, int me, int phase,
-                                xy_obs* obs, hipStream_t s)
+hipError_t launch_resident_quad(float4* state, int L, uint32_t sweep, const Params4& p, int n, int me, xy_obs* obs,
+                                hipStream_t s)
 {
     if (L % 4 || (L / 2) * (L / 4) > kDeepPairs<512, 1>) return hipErrorInvalidValue;
     const size_t lds = deep_lds_bytes(L / 4, L, 512);
     if (me > 0 && obs)
         hipLaunchKernelGGL((k_resident_quad<512, kMeasQuad>), dim3(4), dim3(512), lds, s, (float*)state, L, sweep, n, me,
-                           phase, p, obs);
+                           p, obs);
     else
         hipLaunchKernelGGL((k_resident_quad<512, kMeasNone>), dim3(4), dim3(512), lds, s, (float*)state, L, sweep, n, 0,
-                           0, p, obs);
+                           p, obs);
     return hipGetLastError();
 }
 

@@ -85,18 +85,12 @@ int fused_records(int L, int tile_x, int tile_y, int m);
 // partials[(segment * 4 + wave) * 8].
 bool strip_supported(int L, int tile_x, int tile_y);
 // Whole lattice resident in one workgroup's LDS (L <= 128, L % 4 == 0): n sweeps
-// in place from a.src (= a.dst), records of the sweeps j (1-based) with (j + phase) %
-// me == 0 to obs[0 ..] (none if me == 0 or obs == NULL).  Sweeps a launch takes at
-// most: about a second of work, so that a long call stays a sequence of launches.
-constexpr int64_t resident_sweeps_max(int L)
-{
-    const int64_t n = ((int64_t)1 << 30) / ((int64_t)L * L);
-    return n < (1 << 20) ? n : (1 << 20);
-}
+// in place from a.src (= a.dst), records of every me-th sweep of the call to
+// obs[0 ..] (none if me == 0 or obs == NULL).
 bool resident_supported(int L);
-hipError_t launch_resident(const SweepArgs& a, int n, int me, int phase, xy_obs* obs, hipStream_t s);
+hipError_t launch_resident(const SweepArgs& a, int n, int me, xy_obs* obs, hipStream_t s);
 // The same for any even L <= 62, the records' terms gathered as launch_measure does.
-hipError_t launch_resident_any(const SweepArgs& a, int n, int me, int phase, xy_obs* obs, hipStream_t s);
+hipError_t launch_resident_any(const SweepArgs& a, int n, int me, xy_obs* obs, hipStream_t s);
 hipError_t launch_strip(const SweepArgs& a, int tile_x, int tile_y, bool meas, double* partials, hipStream_t s);
 int strip_records(int L, int tile_x, int tile_y);
 
@@ -190,10 +184,10 @@ bool fused_supported(int L, int tile_x, int tile_y, int m);
 bool deep_choose_quad(int L, int64_t n, DeepPlan* d, int* nmax);
 hipError_t launch_deep_quad(const float4* src, float4* dst, int L, uint32_t sweep, const xyd::Params4& p,
                             const DeepPlan& d, int n, int me, int phase, double* part, hipStream_t s);
-// The whole quad in four workgroups (L <= 32): n sweeps in place, records as
-// launch_resident, four a measured sweep.
-hipError_t launch_resident_quad(float4* state, int L, uint32_t sweep, const xyd::Params4& p, int n, int me, int phase,
-                                xy_obs* obs, hipStream_t s);
+// The whole quad in four workgroups (L <= 32): n sweeps in place, records of every
+// me-th one to obs[0 .. 3], obs[4 .. 7] ... (none if me == 0 or obs == NULL).
+hipError_t launch_resident_quad(float4* state, int L, uint32_t sweep, const xyd::Params4& p, int n, int me, xy_obs* obs,
+                                hipStream_t s);
 // The four records of one sweep, replica r's from the nrec partial records at
 // partials + r * nrec * 8, through `chunks` (4 * ceil(nrec / 256) records) and the
 // arrival counters arrive[0 .. 3].

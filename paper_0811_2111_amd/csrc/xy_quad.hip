@@ -290,13 +290,12 @@ static int quad_resident_sweeps(xy_quad* q, int64_t n_sweeps, int32_t me, xy_obs
 {
     const xyd::Params4 p = quad_params(q);
     for (int64_t done = 0; done < n_sweeps;) {
-        const int64_t m = std::min<int64_t>(xyk::resident_sweeps_max(q->L), n_sweeps - done);
-        hipError_t e = XY_LAUNCH(xyk::launch_resident_quad(q->state, q->L, (uint32_t)q->sweep, p, (int)m, me,
-                                                           me ? (int)(done % me) : 0,
-                                                           me ? obs + done / me * 4 : nullptr, q->stream));
+        const xyr::OnChipLaunch c = xyr::on_chip_launch(q->L, n_sweeps, done, me);
+        hipError_t e = XY_LAUNCH(xyk::launch_resident_quad(q->state, q->L, (uint32_t)q->sweep, p, c.n, c.me,
+                                                           c.me ? obs + done / me * 4 : nullptr, q->stream));
         if (e != hipSuccess) return xyr::hip_fail(e, "xy_quad_sweep: launch");
-        q->sweep += (uint64_t)m;
-        done += m;
+        q->sweep += (uint64_t)c.n;
+        done += c.n;
     }
     return XY_OK;
 }

@@ -19,15 +19,13 @@ __host__ __device__ constexpr size_t resident_lds_bytes(int L, int nt)
 }
 
 // n sweeps of the L x L lattice in src (state layout) starting at sweep index
-// sweep0, result in dst (may equal src).  me > 0 and obs != NULL: the sweeps j = 1 ..
-// n with (j + phase) % me == 0 leave records obs[0], obs[1] ..., their terms gathered
-// as MEAS says (kMeasOwn or kMeasPair).  resident_fits<NT, R>(L); smem:
-// resident_lds_bytes(L, NT).
+// sweep0, result in dst (may equal src).  me > 0 and obs != NULL: after the j-th
+// sweep of the call (j = 1 .. n) with j % me == 0 the record j / me - 1 goes to
+// obs, its terms gathered as MEAS says (kMeasOwn or kMeasPair).  resident_fits<NT, R>(L); smem: resident_lds_bytes(L, NT).
 template <typename T, int NT, int R, bool ODD, int MEAS>
 __device__ __forceinline__ void resident_program(const T* __restrict__ src, T* __restrict__ dst, int L,
-                                                 uint32_t sweep0, int n, int me, int phase, uint32_t k0,
-                                                 uint32_t k1, const Params& p, xy_obs* __restrict__ obs,
-                                                 char* smem)
+                                                 uint32_t sweep0, int n, int me, uint32_t k0, uint32_t k1,
+                                                 const Params& p, xy_obs* __restrict__ obs, char* smem)
 {
     DeepRegion g;
     g.L = L;
@@ -37,10 +35,10 @@ __device__ __forceinline__ void resident_program(const T* __restrict__ src, T* _
     g.PC = g.cp = g.P;
     g.RY = g.cr = L;
     if (obs == nullptr) me = 0;
-    deep_program<T, NT, R, ODD, true, MEAS, false>(src, dst, g, sweep0, n, me, phase, 0, 0, k0, k1, p, smem, [&](int k, double s) {
+    deep_program<T, NT, R, ODD, true, MEAS, false>(src, dst, g, sweep0, n, me, 0, 0, 0, k0, k1, p, smem, [&](int k, double s) {
         // xy_obs: sweep, n_accept, then the six sums, eight bytes each
         const int t = (int)threadIdx.x;
-        const uint64_t after = (uint64_t)sweep0 + (uint64_t)(k + 1) * (uint64_t)me - (uint64_t)phase;
+        const uint64_t after = (uint64_t)sweep0 + (uint64_t)(k + 1) * (uint64_t)me;
         unsigned long long* o = (unsigned long long*)(obs + k);
         if (t < 6) o[2 + t] = (unsigned long long)__double_as_longlong(s);
         else if (t == 6) o[1] = (unsigned long long)s;

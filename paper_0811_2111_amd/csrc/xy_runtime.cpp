@@ -375,16 +375,15 @@ static int stream_sweep(xy_lattice* h, bool measured, xy_obs* rec, uint8_t* dbg_
 static int resident_sweeps(xy_lattice* h, int64_t n_sweeps, int32_t me, xy_obs* obs, bool own)
 {
     for (int64_t done = 0; done < n_sweeps;) {
-        const int64_t m = std::min<int64_t>(xyk::resident_sweeps_max(h->L), n_sweeps - done);
+        const OnChipLaunch c = on_chip_launch(h->L, n_sweeps, done, me);
         xyk::SweepArgs a = args_of(h);
-        const int phase = me ? (int)(done % me) : 0;
-        xy_obs* rec = me ? obs + done / me : nullptr;
+        xy_obs* rec = c.me ? obs + done / me : nullptr;
         hipError_t e = XY_LAUNCH(
-            own ? timed(h, [&] { return xyk::launch_resident_any(a, (int)m, me, phase, rec, h->stream); })
-                : xyk::launch_resident(a, (int)m, me, phase, rec, h->stream));
+            own ? timed(h, [&] { return xyk::launch_resident_any(a, c.n, c.me, rec, h->stream); })
+                : xyk::launch_resident(a, c.n, c.me, rec, h->stream));
         if (e != hipSuccess) return hip_fail(e, "resident sweep launch");
-        h->sweep += (uint64_t)m;
-        done += m;
+        h->sweep += (uint64_t)c.n;
+        done += c.n;
     }
     return XY_OK;
 }

@@ -18,6 +18,25 @@ bool inject_due();
 bool valid_L(int32_t L);
 bool valid_beta_delta(double beta, double delta);
 xyk::SweepArgs sweep_args(uint64_t seed, int L, int precision, double beta, double delta);
+// The launches of a call of n sweeps on chip with a record every me-th (0: none), `done`
+// of them enqueued: the sweeps of the next one and its record interval.  At most about
+// a second of work each (2^20 sweeps, 2^30 site updates), so that a long call stays a
+// sequence of launches; cut at records, and inside an interval longer than that into
+// launches without and a last one with a record of its own last sweep.
+struct OnChipLaunch {
+    int n, me;
+};
+inline OnChipLaunch on_chip_launch(int L, int64_t n, int64_t done, int32_t me)
+{
+    const int64_t w = ((int64_t)1 << 30) / ((int64_t)L * L), most = w < (1 << 20) ? w : (1 << 20);
+    const int64_t left = n - done;
+    if (me > most) {
+        const int64_t until = me - done % me, m = until < left ? until : left;
+        return m > most ? OnChipLaunch{(int)most, 0} : OnChipLaunch{(int)m, m == until ? (int)m : 0};
+    }
+    const int64_t m = me ? most / me * me : most;
+    return OnChipLaunch{(int)(m < left ? m : left), me};
+}
 xy_plan default_plan(int32_t L, int32_t precision);
 bool plan_ok(int32_t L, const xy_plan& p);
 bool cache_lookup(const char* path, int32_t L, int32_t precision, xy_plan* plan);

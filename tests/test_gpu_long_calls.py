@@ -12,9 +12,9 @@ if torch.cuda.is_available():
 STREAM = (1, 0, 0, 1)
 
 
-@pytest.mark.parametrize("L,n,every", [(54, 400_000, 1000), (54, 400_000, 390_000)])
+@pytest.mark.parametrize("L,n,every", [(54, 400_000, 1000), (54, 400_000, 390_000), (54, 740_000, 369_000)])
 def test_records_across_the_launches_of_a_long_call(L, n, every):
-    """368 225 sweeps a launch: the second one starts inside a record's interval."""
+    """368 225 sweeps a launch at most: cut at records, or inside a longer interval."""
     a, b = (xy.Lattice(L, seed=3, beta=1.0, delta=1.1) for _ in range(2))
     out = a.sweep(n, every)
     one = torch.cat([b.sweep(every, every) for _ in range(n // every)])

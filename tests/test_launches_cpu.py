@@ -105,12 +105,13 @@ def test_long_calls_on_chip_are_split(stub, L, plan):
         assert stub.lib.xy_set_plan(h, (i32 * 4)(plan, 0, 0, 1)) == OK
     n = 3 * 2 ** 20 + 1
     most = min(2 ** 20, 2 ** 30 // L ** 2)
-    for me, obs in ((0, None), (10, DEV), (n - 2, DEV)):
+    for me, obs, want in ((0, None, -(-n // most)), (10, DEV, -(-n // (most // 10 * 10))),
+                          (n - 2, DEV, -(-(n - 2) // most) + 1)):
         got = stub.log(lambda: stub.lib.xy_sweep(h, i64(n), i32(me), obs))
-        assert len(got) == -(-n // most) and all("k_resident" in k for k in got)
+        assert len(got) == want and all("k_resident" in k for k in got)
     q = stub.quad(32)
     got = stub.log(lambda: stub.lib.xy_quad_sweep(q, i64(n), i32(n - 2), DEV))
-    assert len(got) == -(-n // 2 ** 20) and all("k_resident_quad" in k for k in got)
+    assert len(got) == -(-(n - 2) // 2 ** 20) + 1 and all("k_resident_quad" in k for k in got)
 
 
 @pytest.mark.parametrize("L,n,me,phase,measured", [
