@@ -214,9 +214,10 @@ __device__ __forceinline__ void deep_half(float2* __restrict__ own, const float2
         if (!(flag & kOn)) continue;
         if constexpr (!EARLY) r[q] = philox10(w.sweep, w.colour, 0u, it.idx[q], w.k0, w.k1);
         const PairNb<O> n = deep_nb<O, ODD>(oth, WS, at);
-        float4 cs;
-        if constexpr (R <= 4) cs = kept[q];
-        else cs = *(const float4*)&own[at];
+        float4 copy;                               // (four pairs updated in place spill, too)
+        float4& cs = R < 4 ? kept[R < 4 ? q : 0] : copy;
+        if constexpr (R == 4) cs = kept[q];
+        if constexpr (R > 4) cs = *(const float4*)&own[at];
         DeepProp pr;
         if constexpr (R == 1) pr = r[q];
         else pr = deep_propose<T>(r[q], th[q], p);
@@ -225,7 +226,7 @@ __device__ __forceinline__ void deep_half(float2* __restrict__ own, const float2
         const int ab = decide(pr.b, th[q].y, cs.z, cs.w, nsum(n.lb.x, n.rb.x, n.ub.x, n.db.x),
                               nsum(n.lb.y, n.rb.y, n.ub.y, n.db.y), p);
         deep_put<ODD, WRAP>(own, WS, L, Hh, at, flag, cs);
-        if constexpr (R <= 4) kept[q] = cs;
+        if constexpr (R == 4) kept[q] = cs;
         if (flag & kCore) {
             const bool b = !ODD || (flag & kHasB);
             acc += aa + (b ? ab : 0);
@@ -339,10 +340,10 @@ __device__ __forceinline__ void deep_program(const T* __restrict__ src, T* __res
     DeepDraw dr{sweep0, (uint32_t)col, k0, k1};
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-        float4 cs;
+        float4 made;
+        float4& cs = R <= 4 ? kept[R <= 4 ? q : 0] : made;
         sincos_turn(th[q].x, cs.y, cs.x);
         sincos_turn(th[q].y, cs.w, cs.z);
-        if constexpr (R <= 4) kept[q] = cs;
         if (it.flag[q] & kOn) deep_put<ODD, WRAP>(own, WS, g.L, g.Hh, it.at[q], it.flag[q], cs);
     }
     if (col == 0) deep_draw<T, R, EARLY>(r, it, th, dr, p);
