@@ -483,12 +483,14 @@ int xy_sweep(xy_lattice* h, int64_t n_sweeps, int32_t measure_every, xy_obs* obs
     // In place of a slower shape not where a single sweep's two buffers about fill the
     // L2s (32 MiB), nor where one of two sweeps is measured by that shape: the other
     // buffer's lines then lie in other XCDs' L2s (us a call by the plan's tiles and the
-    // ragged ones: L = 1920, one sweep 20.8 and 23.3, ten 124 and 101; L = 1600, two
+    // ragged ones: L = 1920, one sweep 20.8 and 23.3, ten 124 and 101; 2240, one 24.4
+    // and 23.6; binary16 L = 2688, one 25.8 and 28.0, 3008 30.4 and 28.3; L = 1600, two
     // sweeps and a record 26.7 and 29.8, one sweep 18.9 and 17.9).
     const bool own = h->own_plan;
     const size_t two = 2 * xyk::state_bytes(h->L, h->precision);
+    const size_t full = (h->precision == XY_FP16 ? 28u : 37u) << 20;
     const bool plans_tile = h->plan.kind == XY_PLAN_FUSED &&
-                            ((n_sweeps == 1 && two >= (22u << 20) && two <= (40u << 20)) ||
+                            ((n_sweeps == 1 && two >= (22u << 20) && two <= full) ||
                              (n_sweeps == 2 && meas && two >= (16u << 20) && two <= (32u << 20)));
     const int own_tx = own && !plans_tile ? xyk::ragged_tile_x(h->L) : 0;
     auto walk = [&](bool meas_j) { return own && xyk::walk_supported(h->L, h->precision, meas_j); };

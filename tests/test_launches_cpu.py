@@ -239,7 +239,8 @@ def test_autotuned_batch_runs_the_same_on_another_handle(stub, Ls, cheap):
     (256, 0, 2, 0, "k_deep"), (382, 0, 2, 1, "k_deep"), (384, 0, 2, 1, "k_fused"), (450, 0, 2, 0, "k_ragged"),
     (768, 1, 2, 0, "k_fusedI6__halfLi128ELi16E"), (768, 0, 3, 0, "k_deep"), (1920, 0, 1, 0, "k_fusedIfLi128ELi32E"),
     (1920, 0, 10, 0, "k_raggedIfLi256E"), (1600, 0, 2, 2, "k_fusedIfLi64ELi32E"), (1600, 0, 1, 0, "k_raggedIfLi256E"),
-    (2496, 1, 1, 0, "k_fusedI6__halfLi64ELi32E"), (1860, 0, 2, 0, "k_ragged")])
+    (2496, 1, 1, 0, "k_fusedI6__halfLi64ELi32E"),
+    (3008, 1, 1, 0, "k_raggedI6__halfLi256E"), (2240, 0, 1, 0, "k_raggedIfLi256E"), (1860, 0, 2, 0, "k_ragged")])
 def test_first_kernel_of_short_calls(stub, L, prec, n, me, kernel):
     h = stub.lattice(L, prec)
     assert kernel in stub.log(lambda: stub.lib.xy_sweep(h, i64(n), i32(me), DEV if me else None))[0]
